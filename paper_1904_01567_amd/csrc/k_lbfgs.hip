@@ -129,49 +129,71 @@ __device__ inline void store_vec(float* __restrict__ dst, int lane, int Kp, cons
   }
 }
 
-// Sums over the S split-M partials of up to two float4 of a gradient row
-// (columns c0 and c0 + 64 of the row's float4, the second when two), each in
-// split order, with the loads of both columns in flight together (16 splits
-// at a time); stride4 = float4 between splits.
-__device__ inline void sum_partials2(const float4* __restrict__ src, size_t stride4, int S, bool two,
-                                     float4& acc0, float4& acc1) {
-  acc0 = acc1 = make_float4(0.f, 0.f, 0.f, 0.f);
-  auto add = [](float4& acc, const float4& v) {
-    acc.x += v.x;
-    acc.y += v.y;
-    acc.z += v.z;
-    acc.w += v.w;
-  };
+__device__ inline void add4(float4& acc, const float4& v) {
+  acc.x += v.x;
+  acc.y += v.y;
+  acc.z += v.z;
+  acc.w += v.w;
+}
+
+// Adds splits s .. s + N - 1 of NC float4 columns (64 apart; the second only
+// where two) to acc in split order, all loads in flight together.
+template <int NC, int N>
+__device__ inline void add_partials(const float4* __restrict__ src, size_t stride4, int s, bool two,
+                                    float4 (&acc)[2]) {
+  float4 v[NC][N];
+#pragma unroll
+  for (int u = 0; u < N; ++u) {
+    v[0][u] = src[(s + u) * stride4];
+    if constexpr (NC == 2) v[1][u] = two ? src[(s + u) * stride4 + 64] : make_float4(0.f, 0.f, 0.f, 0.f);
+  }
+#pragma unroll
+  for (int u = 0; u < N; ++u) {
+    add4(acc[0], v[0][u]);
+    if constexpr (NC == 2) add4(acc[1], v[1][u]);
+  }
+}
+
+// Sums over the S split-M partials of the NC float4 columns of a gradient
+// row that a lane owns (stride4 = float4 between splits), each in split
+// order, 32 float4 in flight per lane.
+template <int NC>
+__device__ inline void sum_partials(const float4* __restrict__ src, size_t stride4, int S, bool two,
+                                    float4 (&acc)[2]) {
+  acc[0] = acc[1] = make_float4(0.f, 0.f, 0.f, 0.f);
   int s = 0;
-  for (; s + 16 <= S; s += 16) {
-    float4 v0[16], v1[16];
-#pragma unroll
-    for (int u = 0; u < 16; ++u) {
-      v0[u] = src[(s + u) * stride4];
-      v1[u] = two ? src[(s + u) * stride4 + 64] : make_float4(0.f, 0.f, 0.f, 0.f);
-    }
-#pragma unroll
-    for (int u = 0; u < 16; ++u) {
-      add(acc0, v0[u]);
-      add(acc1, v1[u]);
-    }
+  for (; s + 32 / NC <= S; s += 32 / NC) add_partials<NC, 32 / NC>(src, stride4, s, two, acc);
+  if (NC == 1 && s + 16 <= S) {
+    add_partials<NC, 16>(src, stride4, s, two, acc);
+    s += 16;
   }
-  for (; s + 8 <= S; s += 8) {
-    float4 v0[8], v1[8];
-#pragma unroll
-    for (int u = 0; u < 8; ++u) {
-      v0[u] = src[(s + u) * stride4];
-      v1[u] = two ? src[(s + u) * stride4 + 64] : make_float4(0.f, 0.f, 0.f, 0.f);
-    }
-#pragma unroll
-    for (int u = 0; u < 8; ++u) {
-      add(acc0, v0[u]);
-      add(acc1, v1[u]);
-    }
+  if (s + 8 <= S) {
+    add_partials<NC, 8>(src, stride4, s, two, acc);
+    s += 8;
   }
-  for (; s < S; ++s) {
-    add(acc0, src[s * stride4]);
-    if (two) add(acc1, src[s * stride4 + 64]);
+  for (; s < S; ++s) add_partials<NC, 1>(src, stride4, s, two, acc);
+}
+
+// The same sums by kWideWaves wavefronts (threads t = 0 .. 64 kWideWaves - 1
+// of them) for a plan that has a compute unit to itself: each chunk of whole
+// splits goes through registers into LDS, kWideLoads float4 in flight per
+// thread, and the first 2 nq threads add two columns each of the chunk in
+// split order.  Every thread of the workgroup passes the same barriers: two
+// per chunk of wide_chunk(nq) splits.
+constexpr int kWideWaves = 7;
+constexpr int kWideLoads = 16;
+constexpr int kWideF4 = 64 * kWideWaves * kWideLoads;  // float4 of a chunk
+__device__ inline int wide_chunk(int nq) { return kWideF4 / nq; }
+
+__device__ inline void wide_load(const float4* __restrict__ src, size_t stride4, int n, int nq, unsigned magic,
+                                 int t, float4 (&v)[kWideLoads]) {
+#pragma unroll
+  for (int u = 0; u < kWideLoads; ++u) {
+    // i / nq by a reciprocal: exact, since i nq < 2^20 (i < 8,192, nq <= 128)
+    const unsigned i = t + 64 * kWideWaves * u;
+    const unsigned sp = (i * magic) >> 20;
+    v[u] = make_float4(0.f, 0.f, 0.f, 0.f);
+    if ((int)sp < n) v[u] = src[sp * stride4 + (i - sp * nq)];
   }
 }
 
@@ -192,16 +214,19 @@ __device__ inline void load_vec_lds(const float* src, int lane, int Kp, float (&
 // MH = register capacity for history pairs (MH >= m).  The pairs are held in
 // registers in age order (0 = newest) so every loop index is a compile-time
 // constant; all their loads are issued together before the recursion.
-// One workgroup of two wavefronts per plan.  Wavefront 1 sums the split-M
-// gradient partials of the plan's compact column, in split order, into LDS
-// (so the round needs no separate reduction launch) while wavefront 0 loads
-// the plan's vectors and history; wavefront 0 then advances the plan with G
-// from LDS.  (Two wavefronts of up to 256 VGPRs per plan keep a 1,024-plan
-// batch resident at once.)
-template <int E, int MH>
+// One workgroup per plan.  Wavefront 0 loads the plan's vectors and history
+// and advances the plan; the others sum the split-M gradient partials of the
+// plan's compact column, in split order, into LDS meanwhile (so the round
+// needs no separate reduction launch).  Two wavefronts of up to 256 VGPRs per
+// plan keep a 1,024-plan batch resident at once.  With few plans (WIDE) the
+// point range is split up to 256 ways and one wavefront would wait for the
+// partials trip after trip, so kWideWaves of them load them, two wavefronts
+// per SIMD.
+template <int E, int MH, bool WIDE>
 __device__ inline void update_plans(const UpdateArgs& a, int p, int round) {
   __shared__ __attribute__((aligned(16))) float sGs[kKpMax];
-  const int wave = threadIdx.x >> 6;
+  __shared__ __attribute__((aligned(16))) float4 sR[WIDE ? kWideF4 : 1];
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);  // uniform per wavefront
   const int lane = threadIdx.x & 63;
   if (p == 0 && threadIdx.x == 0) a.active_count[(round + 1) & 1] = 0;
   if (p >= a.Pp) return;
@@ -218,20 +243,51 @@ __device__ inline void update_plans(const UpdateArgs& a, int p, int round) {
   const size_t col = (size_t)a.slot[p];
   if (!state_active(st.status)) return;  // (the same for the whole workgroup)
   const size_t stride = (size_t)rt.ntiles * kPT;
-  if (wave == 1) {
-    const int nq = Kp / 4;  // float4 of a row (Kp at most 512: two per lane)
-    static_assert(kKpMax / 4 <= 128, "two float4 of a row per lane");
-    if (lane < nq) {
-      const float4* src = reinterpret_cast<const float4*>(a.Gpart + col * Kp) + lane;
-      const bool two = lane + 64 < nq;
-      float4 g0, g1;
-      sum_partials2(src, stride * Kp / 4, rt.S, two, g0, g1);
-      *reinterpret_cast<float4*>(&sGs[4 * lane]) = g0;
-      if (two) *reinterpret_cast<float4*>(&sGs[4 * (lane + 64)]) = g1;
+  const int nq = Kp / 4;  // float4 of a row (Kp at most 512: two per lane)
+  static_assert(kKpMax / 4 <= 128, "two float4 of a row per lane");
+  const float4* gsrc = reinterpret_cast<const float4*>(a.Gpart + col * Kp);
+  const size_t stride4 = stride * Kp / 4;
+  const int chunk = WIDE ? wide_chunk(nq) : 0;
+  if (wave > 0) {
+    if constexpr (WIDE) {
+      const unsigned magic = ((1u << 20) + nq - 1) / nq;
+      const int t = (int)threadIdx.x - 64;
+      float4 v[kWideLoads];
+      float2 acc = make_float2(0.f, 0.f);
+      const float2* sR2 = reinterpret_cast<const float2*>(sR) + t;
+      wide_load(gsrc, stride4, min(chunk, rt.S), nq, magic, t, v);
+      for (int s0 = 0; s0 < rt.S; s0 += chunk) {
+        const int n = min(chunk, rt.S - s0);
+#pragma unroll
+        for (int u = 0; u < kWideLoads; ++u) sR[t + 64 * kWideWaves * u] = v[u];
+        __syncthreads();
+        if (s0 + chunk < rt.S)
+          wide_load(gsrc + (s0 + chunk) * stride4, stride4, min(chunk, rt.S - s0 - chunk), nq, magic, t, v);
+        if (t < 2 * nq) {
+#pragma unroll 16
+          for (int u = 0; u < n; ++u) {
+            const float2 r = sR2[u * 2 * nq];
+            acc.x += r.x;
+            acc.y += r.y;
+          }
+          if (s0 + chunk >= rt.S) *reinterpret_cast<float2*>(&sGs[2 * t]) = acc;
+        }
+        __syncthreads();
+      }
+    } else {
+      if (lane < nq) {
+        const bool two = lane + 64 < nq;
+        float4 acc[2];
+        sum_partials<E / 4>(gsrc + lane, stride4, rt.S, two, acc);
+        *reinterpret_cast<float4*>(&sGs[4 * lane]) = acc[0];
+        if (two) *reinterpret_cast<float4*>(&sGs[4 * (lane + 64)]) = acc[1];
+      }
+      __syncthreads();
     }
+    return;
   }
   // Wavefront 0 issues its loads before the barrier, so that they are in
-  // flight while wavefront 1 sums the partials: the plan's vectors, the
+  // flight while the others sum the partials: the plan's vectors, the
   // stored history pairs in age order (0 = newest before this round; a pair
   // pushed this round is prepended from registers below, and a push
   // overwrites the oldest slot only after these loads) and the split
@@ -242,32 +298,36 @@ __device__ inline void update_plans(const UpdateArgs& a, int p, int round) {
   float ohs[MH][E], ohy[MH][E];
   double ohr[MH];
   double fpart = 0.0;
-  if (wave == 0) {
-    load_vec(a.xt + row, lane, Kp, xt);
-    load_vec(a.x + row, lane, Kp, x);
-    load_vec(a.g + row, lane, Kp, g);
-    load_vec(a.dir + row, lane, Kp, d);
+  load_vec(a.xt + row, lane, Kp, xt);
+  load_vec(a.x + row, lane, Kp, x);
+  load_vec(a.g + row, lane, Kp, g);
+  load_vec(a.dir + row, lane, Kp, d);
 #pragma unroll
-    for (int i = 0; i < MH; ++i) {
-      ohr[i] = 0.0;
+  for (int i = 0; i < MH; ++i) {
+    ohr[i] = 0.0;
 #pragma unroll
-      for (int j = 0; j < E; ++j) {
-        ohs[i][j] = 0.f;
-        ohy[i][j] = 0.f;
-      }
-      if (i < hc0) {
-        const int slot = (st.hhead - 1 - i + 2 * m) % m;
-        const float* Sd = a.Sh + ((size_t)p * m + slot) * Kp;
-        const float* Yd = a.Yh + ((size_t)p * m + slot) * Kp;
-        ohr[i] = a.rho[(size_t)p * m + slot];
-        load_vec(Sd, lane, Kp, ohs[i]);
-        load_vec(Yd, lane, Kp, ohy[i]);
-      }
+    for (int j = 0; j < E; ++j) {
+      ohs[i][j] = 0.f;
+      ohy[i][j] = 0.f;
     }
-    for (int s = lane; s < rt.S; s += 64) fpart += a.Fpart[s * stride + col];
+    if (i < hc0) {
+      const int slot = (st.hhead - 1 - i + 2 * m) % m;
+      const float* Sd = a.Sh + ((size_t)p * m + slot) * Kp;
+      const float* Yd = a.Yh + ((size_t)p * m + slot) * Kp;
+      ohr[i] = a.rho[(size_t)p * m + slot];
+      load_vec(Sd, lane, Kp, ohs[i]);
+      load_vec(Yd, lane, Kp, ohy[i]);
+    }
   }
-  __syncthreads();
-  if (wave > 0) return;
+  for (int s = lane; s < rt.S; s += 64) fpart += a.Fpart[s * stride + col];
+  if constexpr (WIDE) {
+    for (int s0 = 0; s0 < rt.S; s0 += chunk) {  // two barriers per chunk, as the summing wavefronts
+      __syncthreads();
+      __syncthreads();
+    }
+  } else {
+    __syncthreads();
+  }
 
   // ---- objective and gradient at the evaluated point ----
   // gradient of this round's compact column, summed above; F from its
@@ -416,9 +476,9 @@ __device__ inline void update_plans(const UpdateArgs& a, int p, int round) {
   }
 }
 
-template <int E, int MH>
-__global__ __launch_bounds__(128) void k_update(UpdateArgs a) {
-  update_plans<E, MH>(a, blockIdx.x, a.round);
+template <int E, int MH, bool WIDE>
+__global__ __launch_bounds__(WIDE ? 64 * (kWideWaves + 1) : 128, (MH <= 10) ? 2 : 1) void k_update(UpdateArgs a) {
+  update_plans<E, MH, WIDE>(a, blockIdx.x, a.round);
 }
 
 // Grouped form: case blockIdx.y of n, its arguments from args (their round
@@ -429,16 +489,33 @@ __global__ __launch_bounds__(128) void k_update(UpdateArgs a) {
 template <int E, int MH>
 __global__ __launch_bounds__(128, (MH <= 10) ? 2 : 1) void k_update_grouped(const UpdateArgs* __restrict__ args,
                                                                            int round) {
-  update_plans<E, MH>(args[blockIdx.y], blockIdx.x, round);
+  update_plans<E, MH, false>(args[blockIdx.y], blockIdx.x, round);
+}
+
+// Batches of at most this many plan slots run the wide form: one workgroup
+// of eight wavefronts and 114 KB of LDS fits a compute unit at a time, so a
+// larger batch would run in several passes over the chip.  Measured at 8
+// plans of 160 dwells, 150 splits: 14.4 us per running round in the two-wavefront form,
+// 10.0 in this one.
+constexpr int kWidePlans = 256;
+
+template <int E, int MH>
+void launch_update_mh(const UpdateArgs& a, hipStream_t st) {
+  if constexpr (MH <= 10) {
+    if (a.Pp <= kWidePlans) {
+      hipLaunchKernelGGL((k_update<E, MH, true>), dim3(a.Pp), dim3(64 * (kWideWaves + 1)), 0, st, a);
+      return;
+    }
+  }
+  hipLaunchKernelGGL((k_update<E, MH, false>), dim3(a.Pp), dim3(128), 0, st, a);
 }
 
 template <int E>
 hipError_t launch_update_e(const UpdateArgs& a, hipStream_t st) {
-  const dim3 grid(a.Pp), block(128);
-  if (a.m <= 4) hipLaunchKernelGGL((k_update<E, 4>), grid, block, 0, st, a);
-  else if (a.m <= 10) hipLaunchKernelGGL((k_update<E, 10>), grid, block, 0, st, a);
-  else if (a.m <= 16) hipLaunchKernelGGL((k_update<E, 16>), grid, block, 0, st, a);
-  else hipLaunchKernelGGL((k_update<E, GMCO_MAX_HISTORY>), grid, block, 0, st, a);
+  if (a.m <= 4) launch_update_mh<E, 4>(a, st);
+  else if (a.m <= 10) launch_update_mh<E, 10>(a, st);
+  else if (a.m <= 16) launch_update_mh<E, 16>(a, st);
+  else launch_update_mh<E, GMCO_MAX_HISTORY>(a, st);
   return hipGetLastError();
 }
 

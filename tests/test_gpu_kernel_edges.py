@@ -41,3 +41,23 @@ def test_evaluation_sums_every_split(M, splits, P, n_cath, n_dw):
         F, g = pl.evaluate(x)
         assert np.max(np.abs(F - Fr) / Fr) <= 2e-5, s
         assert np.abs(g - gr).max() <= 2e-4 * np.abs(gr).max(), s
+
+
+# The update kernel sums the split partials with seven wavefronts in batches of
+# at most 256 plan slots and with one above; both in split order, so the same
+# plans in a small and in a large context give the same bits.  Sizes: one and
+# two float4 columns per lane, splits at and past a chunk of 56 (512 padded
+# dwells), short and full histories.
+@pytest.mark.parametrize("n_cath,n_dw,M,m", [(5, 6, 64, 4), (16, 10, 2400, 10), (20, 25, 896, 10),
+                                             (20, 25, 928, 4), (20, 25, 1824, 10), (18, 20, 4096, 10)])
+def test_update_forms_agree_bitwise(n_cath, n_dw, M, m):
+    announce(f"update forms K={n_cath * n_dw} M={M} m={m}")
+    c = _case(n_cath, n_dw, M)
+    W = cases.hidden_weights(3, seed=6)
+    out = []
+    for cap in (3, 300):
+        pl = planner(c, W, max_plans=cap, history=m)
+        pl.optimize(max_iter=15)
+        out.append((pl.weights_x(), pl.metrics()["F_run"], pl.metrics()["evaluations"]))
+    for a, b in zip(*out):
+        np.testing.assert_array_equal(a, b)
