@@ -334,7 +334,7 @@ UpdateArgs update_args(gmco_ctx* c, const gmco_run* r) {
   u.flag = c->at<int>(L.flag);
   u.rt = c->at<RoundTable>(L.rt);
   u.Kp = d.Kp;
-  u.Pp = d.Pp;
+  u.P = c->P;
   u.m = c->m;
   u.K = d.K;
   u.max_iter = r->max_iter;
@@ -892,7 +892,7 @@ int gmco_optimize_many(gmco_ctx* const* ctxs, int n, const gmco_run* r, gmco_run
   struct Bucket {
     int key0, key1, key2;     // (Kp, dtype, BF16 / FP8 shape) or (E, MH, 0)
     std::vector<int> cases;
-    int off = 0, soff = 0, grid = 0, pp_max = 0;
+    int off = 0, soff = 0, grid = 0, p_max = 0;
   };
   std::vector<Bucket> eb, ub;
   void* dtab = nullptr;
@@ -936,7 +936,7 @@ int gmco_optimize_many(gmco_ctx* const* ctxs, int n, const gmco_run* r, gmco_run
       b.off = (int)hu.size();
       for (int i : b.cases) {
         hu.push_back(us[i]);
-        b.pp_max = std::max(b.pp_max, ctxs[i]->dim.Pp);
+        b.p_max = std::max(b.p_max, ctxs[i]->P);
       }
     }
     const size_t be = align256(he.size() * sizeof(EvalArgs)), bs = align256(hs.size() * sizeof(int));
@@ -960,7 +960,7 @@ int gmco_optimize_many(gmco_ctx* const* ctxs, int n, const gmco_run* r, gmco_run
         GMCO_HIP(c0, launch_eval_grouped(d_eargs + b.off, d_start + b.soff, (int)b.cases.size(), b.grid, b.key0,
                                          b.key1, b.key2, st));
       for (const Bucket& b : ub)
-        GMCO_HIP(c0, launch_update_grouped(d_uargs + b.off, (int)b.cases.size(), b.key0, b.pp_max, b.key1,
+        GMCO_HIP(c0, launch_update_grouped(d_uargs + b.off, (int)b.cases.size(), b.key0, b.p_max, b.key1,
                                            (int)rd, st));
       return GMCO_OK;
     }

@@ -143,7 +143,7 @@ struct UpdateArgs {
   int* flag;          // [Pp] 1 while the plan runs, for the next compaction
   const int* slot;    // [Pp] compact column of each active plan
   const RoundTable* rt;
-  int Kp, Pp, m, K;
+  int Kp, P, m, K;  // P: plans of the batch (slots past it are inactive)
   int max_iter, max_ls;
   double eps, c1, beta;
   int round;
@@ -175,8 +175,8 @@ hipError_t launch_eval(const EvalArgs& a, int dtype, hipStream_t st);
 hipError_t launch_eval_grouped(const EvalArgs* args, const int* start, int n, int grid, int Kp, int dtype,
                                int lp_shape, hipStream_t st);
 // Update of n cases in one launch (cases of one update width E); the grid is
-// sized for the largest case.
-hipError_t launch_update_grouped(const UpdateArgs* args, int n, int E, int Pp_max, int m, int round,
+// sized for the case of most plans, P_max.
+hipError_t launch_update_grouped(const UpdateArgs* args, int n, int E, int P_max, int m, int round,
                                  hipStream_t st);
 hipError_t launch_update(const UpdateArgs& a, hipStream_t st);
 hipError_t launch_finish_eval(const float* Gpart, const double* Fpart, const float* x, int S,

@@ -147,6 +147,9 @@ __device__ inline void add_partials(const float4* __restrict__ src, size_t strid
     v[0][u] = src[(s + u) * stride4];
     if constexpr (NC == 2) v[1][u] = two ? src[(s + u) * stride4 + 64] : make_float4(0.f, 0.f, 0.f, 0.f);
   }
+  // all loads before the first addition: the scheduler would otherwise trade
+  // loads in flight for registers (41 against 22 us per grouped launch)
+  __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
   for (int u = 0; u < N; ++u) {
     add4(acc[0], v[0][u]);
@@ -229,7 +232,7 @@ __device__ inline void update_plans(const UpdateArgs& a, int p, int round) {
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);  // uniform per wavefront
   const int lane = threadIdx.x & 63;
   if (p == 0 && threadIdx.x == 0) a.active_count[(round + 1) & 1] = 0;
-  if (p >= a.Pp) return;
+  if (p >= a.P) return;
   const int Kp = a.Kp;
   const int m = a.m;
   const size_t row = (size_t)p * Kp;
@@ -492,22 +495,23 @@ __global__ __launch_bounds__(128, (MH <= 10) ? 2 : 1) void k_update_grouped(cons
   update_plans<E, MH, false>(args[blockIdx.y], blockIdx.x, round);
 }
 
-// Batches of at most this many plan slots run the wide form: one workgroup
-// of eight wavefronts and 114 KB of LDS fits a compute unit at a time, so a
+// Batches of at most this many plans run the wide form: one workgroup of
+// eight wavefronts and 114 KB of LDS fits a compute unit at a time, so a
 // larger batch would run in several passes over the chip.  Measured at 8
 // plans of 160 dwells, 150 splits: 14.4 us per running round in the two-wavefront form,
-// 10.0 in this one.
+// 10.0 in this one.  (Grouped launches keep the two-wavefront form: 8 cases of
+// 11 plans took 36.0 us a round in this one against 35.6.)
 constexpr int kWidePlans = 256;
 
 template <int E, int MH>
 void launch_update_mh(const UpdateArgs& a, hipStream_t st) {
   if constexpr (MH <= 10) {
-    if (a.Pp <= kWidePlans) {
-      hipLaunchKernelGGL((k_update<E, MH, true>), dim3(a.Pp), dim3(64 * (kWideWaves + 1)), 0, st, a);
+    if (a.P <= kWidePlans) {
+      hipLaunchKernelGGL((k_update<E, MH, true>), dim3(a.P), dim3(64 * (kWideWaves + 1)), 0, st, a);
       return;
     }
   }
-  hipLaunchKernelGGL((k_update<E, MH, false>), dim3(a.Pp), dim3(128), 0, st, a);
+  hipLaunchKernelGGL((k_update<E, MH, false>), dim3(a.P), dim3(128), 0, st, a);
 }
 
 template <int E>
@@ -520,9 +524,8 @@ hipError_t launch_update_e(const UpdateArgs& a, hipStream_t st) {
 }
 
 template <int E>
-hipError_t launch_update_grouped_e(const UpdateArgs* args, int n, int Pp_max, int m, int round,
-                                   hipStream_t st) {
-  const dim3 grid(Pp_max, n), block(128);
+hipError_t launch_update_grouped_e(const UpdateArgs* args, int n, int P_max, int m, int round, hipStream_t st) {
+  const dim3 grid(P_max, n), block(128);
   if (m <= 4) hipLaunchKernelGGL((k_update_grouped<E, 4>), grid, block, 0, st, args, round);
   else if (m <= 10) hipLaunchKernelGGL((k_update_grouped<E, 10>), grid, block, 0, st, args, round);
   else if (m <= 16) hipLaunchKernelGGL((k_update_grouped<E, 16>), grid, block, 0, st, args, round);
@@ -634,10 +637,9 @@ hipError_t launch_update(const UpdateArgs& a, hipStream_t st) {
   return hipErrorInvalidValue;
 }
 
-hipError_t launch_update_grouped(const UpdateArgs* args, int n, int E, int Pp_max, int m, int round,
-                                 hipStream_t st) {
-  if (E == 4) return launch_update_grouped_e<4>(args, n, Pp_max, m, round, st);
-  if (E == 8) return launch_update_grouped_e<8>(args, n, Pp_max, m, round, st);
+hipError_t launch_update_grouped(const UpdateArgs* args, int n, int E, int P_max, int m, int round, hipStream_t st) {
+  if (E == 4) return launch_update_grouped_e<4>(args, n, P_max, m, round, st);
+  if (E == 8) return launch_update_grouped_e<8>(args, n, P_max, m, round, st);
   return hipErrorInvalidValue;
 }
 
