@@ -610,17 +610,17 @@ int gmco_load_case(gmco_ctx* c, const gmco_case* cs) {
                                (float)c->gt.prm64[j][2], (float)c->gt.prm64[j][3]);
   }
 
-  GMCO_HIP(c, launch_dose_rate(st_dw, cs->point_xyz ? st_pt : nullptr, cs->dose_rate ? st_D : nullptr,
-                               c->at<int>(L.perm), M, K, d.Mp, d.Kp, c->at<double>(L.D64), c->stream));
-  GMCO_HIP(c, launch_cast_dose(c->at<double>(L.D64), d.Mp, d.Kp, c->dtype, c->at<float>(L.D32),
-                               c->at<void>(L.Dlp), c->at<void>(L.DTlp), c->at<float>(L.colscale),
-                               c->stream));
+  // (the doses' array is free until the metrics: scratch of the row sums and column maxima)
+  const int r0 = c->offsets[cs->target_group];
+  GMCO_HIP(c, launch_dose_setup(st_dw, cs->point_xyz ? st_pt : nullptr, cs->dose_rate ? st_D : nullptr,
+                                c->at<int>(L.perm), M, K, d.Mp, d.Kp, c->dtype, r0,
+                                r0 + ocounts[cs->target_group], c->rx, c->at<double>(L.D64),
+                                c->at<float>(L.D32), c->at<void>(L.Dlp), c->at<void>(L.DTlp),
+                                c->at<float>(L.colscale), c->at<double>(L.d64), c->at<double>(L.t_bar),
+                                c->stream));
   if (Md > 0)  // the DVH points: point-source law, organ order
     GMCO_HIP(c, launch_dose_rate(st_dw, c->at<double>(L.dstage), nullptr, c->at<int>(L.dperm), Md, K,
                                  d.Mdp, d.Kp, c->at<double>(L.D64d), c->stream));
-  const int r0 = c->offsets[cs->target_group];
-  GMCO_HIP(c, launch_start_time(c->at<double>(L.D64), d.Kp, r0, r0 + ocounts[cs->target_group], c->rx,
-                                c->at<double>(L.t_bar), c->stream));
   GMCO_HIP(c, hipStreamSynchronize(c->stream));
   c->has_points = cs->point_xyz != nullptr;
   c->case_loaded = true;

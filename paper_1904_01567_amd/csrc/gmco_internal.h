@@ -158,12 +158,17 @@ constexpr int kKpMax = 512;  // largest padded dwell count the update supports
 hipError_t launch_dose_rate(const double* dwell_xyz, const double* pt_xyz, const double* user_D,
                             const int* perm, int M, int K, int Mp, int Kp, double* D64,
                             hipStream_t st);
-hipError_t launch_cast_dose(const double* D64, int Mp, int Kp, int dtype, float* D32, void* Dlp,
-                            void* DTlp, float* colscale, hipStream_t st);
+// launch_dose_rate, the run-dtype copies of the matrix (D32, for BF16 and FP8
+// also Dlp, DTlp and, for FP8, colscale) and the default start time from rows
+// row_begin .. row_end - 1.  scratch holds at least dose_scratch(Mp, Kp) doubles.
+hipError_t launch_dose_setup(const double* dwell_xyz, const double* pt_xyz, const double* user_D,
+                             const int* perm, int M, int K, int Mp, int Kp, int dtype, int row_begin,
+                             int row_end, double prescription, double* D64, float* D32, void* Dlp, void* DTlp,
+                             float* colscale, double* scratch, double* t_bar, hipStream_t st);
+// row sums, and the column maxima of each 32-point block
+inline size_t dose_scratch(int Mp, int Kp) { return (size_t)Mp + (size_t)(Mp / 32) * Kp; }
 hipError_t launch_widen_fp8(const void* D8, const float* colscale, int Mp, int Kp, double* out,
                             hipStream_t st);
-hipError_t launch_start_time(const double* D64, int Kp, int row_begin, int row_end,
-                             double prescription, double* t_bar, hipStream_t st);
 hipError_t launch_init_plans(int P, int Pp, int K, int Kp, const double* t0, const double* t_bar,
                              const double* W, int G, int O, const int* gorg, const int* norm,
                              float* xt, float* x, float* wn, double* W64, PlanState* ps,

@@ -5,38 +5,6 @@
 namespace gmco {
 namespace {
 
-// Point-source law of the synthetic cases: (1 - 0.01 r) / max(r, 0.1 cm)^2.
-// Rows follow the library's point order (grouped by structure): row i is the
-// caller's point perm[i].  Padding rows and columns are zero.
-__global__ void k_dose_rate(const double* __restrict__ dwell, const double* __restrict__ pts,
-                            const double* __restrict__ user_D, const int* __restrict__ perm,
-                            int M, int K, int Mp, int Kp, double* __restrict__ D64) {
-  const int l = blockIdx.x * blockDim.x + threadIdx.x;
-  const int i = blockIdx.y;
-  if (l >= Kp || i >= Mp) return;
-  double v = 0.0;
-  if (i < M && l < K) {
-    const int src = perm[i];
-    if (user_D != nullptr) {
-      v = user_D[(size_t)src * K + l];
-    } else {
-      const double dx = pts[3 * src + 0] - dwell[3 * l + 0];
-      const double dy = pts[3 * src + 1] - dwell[3 * l + 1];
-      const double dz = pts[3 * src + 2] - dwell[3 * l + 2];
-      const double r = sqrt(dx * dx + dy * dy + dz * dz);
-      const double rc = r > 0.1 ? r : 0.1;
-      v = (1.0 - 0.01 * r) / (rc * rc);
-    }
-  }
-  D64[(size_t)i * Kp + l] = v;
-}
-
-__global__ void k_cast_f32(const double* __restrict__ D64, size_t n, float* __restrict__ out) {
-  for (size_t idx = blockIdx.x * (size_t)blockDim.x + threadIdx.x; idx < n;
-       idx += (size_t)gridDim.x * blockDim.x)
-    out[idx] = (float)D64[idx];
-}
-
 // Round an FP32 value to BF16, nearest with ties to even (finite inputs).
 __device__ inline uint16_t bf16_rne(float f) {
   uint32_t u = __float_as_uint(f);
@@ -51,51 +19,157 @@ __device__ inline int tpos32(int r) {
   return r < 16 ? 8 * (r >> 2) + (r & 3) : 8 * ((r - 16) >> 2) + 4 + ((r - 16) & 3);
 }
 
-// BF16 copies of the dose-rate matrix, row-major (points x dwells) for the
-// dose product and dwell-major for the back-projection, the latter with the
-// points of each 32-point block in the tile order above (Mp is a multiple of
-// 32).
-__global__ void k_cast_bf16(const double* __restrict__ D64, int Mp, int Kp,
-                            uint16_t* __restrict__ D, uint16_t* __restrict__ DT) {
-  const size_t n = (size_t)Mp * Kp;
-  for (size_t idx = blockIdx.x * (size_t)blockDim.x + threadIdx.x; idx < n;
-       idx += (size_t)gridDim.x * blockDim.x) {
-    const size_t i = idx / Kp, l = idx - i * Kp;
-    const uint16_t v = bf16_rne((float)D64[idx]);
-    D[idx] = v;
-    DT[l * Mp + (i & ~(size_t)31) + tpos32((int)(i & 31))] = v;
+// The dose-rate matrix and everything that is read off it, in one pass: per
+// 32-point block a workgroup computes 64 columns at a time and writes
+//   D64                the matrix in FP64 (every mode)
+//   D32                its FP32 copy (all but DVH points)
+//   D16, DT16          BF16 row-major, for the dose product (BF16 only), and
+//                      dwell-major with the points of the block in the tile
+//                      order above (BF16 and FP8)
+//   colmax             the block's largest |D| per column (FP8: one row of
+//                      the partial maxima of the column scales)
+//   rowsum             sum over the columns of rows r0 .. r1 - 1, in column
+//                      order (the start time's mean)
+// so that the FP64 matrix is not read back.  Bound by the bytes written (16
+// per element in BF16) and, close behind, by the FP64 square root and
+// division: 42 us at 20,000 x 360 in BF16 (2.9 TB/s), where separate passes
+// took 33 + 15 + 64 us, and 1,832 us for the start time by one workgroup with
+// a row per thread; that case's load, weights and first evaluation of 1,000
+// plans went from 2,609 to 708 us.
+// Point-source law of the synthetic cases: (1 - 0.01 r) / max(r, 0.1 cm)^2.
+// Rows follow the library's point order (grouped by structure): row i is the
+// caller's point perm[i].  Padding rows and columns are zero.
+enum { DOSE_D64 = 0, DOSE_F32 = 1, DOSE_BF16 = 2, DOSE_FP8 = 3 };
+struct DoseArgs {
+  const double* dwell;
+  const double* pts;
+  const double* user_D;
+  const int* perm;
+  int M, K, Mp, Kp, r0, r1;
+  double* D64;
+  float* D32;
+  uint16_t* D16;
+  uint16_t* DT16;
+  double* colmax;  // [Mp / 32][Kp]
+  double* rowsum;  // [Mp]
+};
+
+template <int MODE>
+__global__ __launch_bounds__(256) void k_dose_matrix(DoseArgs a) {
+  constexpr int NR = 32, NC = 64, RS = NC + 1;
+  constexpr int TS = NR + 8;  // 80-byte rows: 16-byte aligned, the columns' writes spread over the banks
+  __shared__ double sD[NR * RS];
+  __shared__ __attribute__((aligned(16))) uint16_t sT[MODE >= DOSE_BF16 ? NC * TS : 8];
+  __shared__ double sM[MODE == DOSE_FP8 ? 4 * NC : 1];
+  const int i0 = blockIdx.x * NR;
+  const int c = threadIdx.x & 63, w = threadIdx.x >> 6;  // column; rows 8 w .. 8 w + 7
+  const bool sums = MODE != DOSE_D64 && i0 < a.r1 && i0 + NR > a.r0;
+  double rs = 0.0;  // row i0 + threadIdx.x (first 32 threads)
+  // the rows' points, the same for every chunk of columns (a wavefront's rows are uniform)
+  int src[NR / 4];
+#pragma unroll
+  for (int k = 0; k < NR / 4; ++k) src[k] = i0 + 8 * w + k < a.M ? a.perm[i0 + 8 * w + k] : -1;
+  for (int l0 = 0; l0 < a.Kp; l0 += NC) {
+    const int l = l0 + c;
+    const bool col = l < a.K;
+    double dwx = 0.0, dwy = 0.0, dwz = 0.0, cm = 0.0;
+    uint16_t t16[NR / 4] = {};
+    if (col && a.user_D == nullptr) {
+      dwx = a.dwell[3 * l + 0];
+      dwy = a.dwell[3 * l + 1];
+      dwz = a.dwell[3 * l + 2];
+    }
+#pragma unroll
+    for (int k = 0; k < NR / 4; ++k) {
+      const int r = 8 * w + k;
+      double v = 0.0;
+      if (src[k] >= 0 && col) {
+        if (a.user_D != nullptr) {
+          v = a.user_D[(size_t)src[k] * a.K + l];
+        } else {
+          const double dx = a.pts[3 * src[k] + 0] - dwx;
+          const double dy = a.pts[3 * src[k] + 1] - dwy;
+          const double dz = a.pts[3 * src[k] + 2] - dwz;
+          const double r2 = sqrt(dx * dx + dy * dy + dz * dz);
+          const double rc = r2 > 0.1 ? r2 : 0.1;
+          v = (1.0 - 0.01 * r2) / (rc * rc);
+        }
+      }
+      if (l < a.Kp) {
+        const size_t at = (size_t)(i0 + r) * a.Kp + l;
+        a.D64[at] = v;
+        if constexpr (MODE >= DOSE_F32) a.D32[at] = (float)v;
+        if constexpr (MODE >= DOSE_BF16) {
+          const uint16_t h = bf16_rne((float)v);
+          if constexpr (MODE == DOSE_BF16) a.D16[at] = h;
+          t16[k] = h;
+        }
+      }
+      if constexpr (MODE == DOSE_FP8) cm = fmax(cm, fabs(v));
+      if (sums) sD[r * RS + c] = v;
+    }
+    if constexpr (MODE >= DOSE_BF16) {
+      // rows 8 w .. 8 w + 3 and 8 w + 4 .. 8 w + 7 are runs of four positions
+#pragma unroll
+      for (int h = 0; h < 2; ++h)
+        *reinterpret_cast<uint2*>(&sT[c * TS + tpos32(8 * w + 4 * h)]) =
+            make_uint2(t16[4 * h] | (unsigned)t16[4 * h + 1] << 16, t16[4 * h + 2] | (unsigned)t16[4 * h + 3] << 16);
+    }
+    if constexpr (MODE == DOSE_FP8) sM[w * NC + c] = cm;
+    if (MODE >= DOSE_BF16 || sums) __syncthreads();
+    if constexpr (MODE >= DOSE_BF16) {
+      // 64 bytes of a dwell's points by four threads
+      const int lc = threadIdx.x >> 2, part = threadIdx.x & 3;
+      if (l0 + lc < a.Kp)
+        *reinterpret_cast<uint4*>(a.DT16 + (size_t)(l0 + lc) * a.Mp + i0 + 8 * part) =
+            *reinterpret_cast<const uint4*>(&sT[lc * TS + 8 * part]);
+    }
+    if constexpr (MODE == DOSE_FP8) {
+      if (threadIdx.x < NC && l < a.Kp)
+        a.colmax[(size_t)blockIdx.x * a.Kp + l] =
+            fmax(fmax(sM[c], sM[NC + c]), fmax(sM[2 * NC + c], sM[3 * NC + c]));
+    }
+    if (sums && threadIdx.x < NR) {
+      const int n = min(NC, a.Kp - l0);  // 32 or 64
+#pragma unroll 32
+      for (int j = 0; j < n; ++j) rs += sD[threadIdx.x * RS + j];
+    }
+    if (MODE >= DOSE_BF16 || sums) __syncthreads();
   }
+  if (sums && threadIdx.x < NR) a.rowsum[i0 + threadIdx.x] = rs;
 }
 
 // Per-dwell-column scale for the FP8 copy: s_l = max_i D_il / 224 (1 for an
-// all-zero column), one workgroup per column, fixed reduction order.
-__global__ void k_colscale(const double* __restrict__ D64, int Mp, int Kp, float* __restrict__ cs) {
-  __shared__ double red[256];
-  const int l = blockIdx.x;
+// all-zero column), from the blocks' partial maxima.  A workgroup takes 64
+// columns, its 16 wavefronts every 16th block.
+__global__ __launch_bounds__(1024) void k_colscale(const double* __restrict__ colmax, int nb, int Kp,
+                                                   float* __restrict__ cs) {
+  __shared__ double red[16][64];
+  const int c = threadIdx.x & 63, w = threadIdx.x >> 6;
+  const int l = blockIdx.x * 64 + c;
   double m = 0.0;
-  for (int i = threadIdx.x; i < Mp; i += blockDim.x) m = fmax(m, fabs(D64[(size_t)i * Kp + l]));
-  red[threadIdx.x] = m;
-  __syncthreads();
-  for (int o = 128; o > 0; o >>= 1) {
-    if ((int)threadIdx.x < o) red[threadIdx.x] = fmax(red[threadIdx.x], red[threadIdx.x + o]);
-    __syncthreads();
+  if (l < Kp) {
+#pragma unroll 8
+    for (int b = w; b < nb; b += 16) m = fmax(m, colmax[(size_t)b * Kp + l]);
   }
-  if (threadIdx.x == 0) cs[l] = red[0] > 0.0 ? (float)(red[0] / 224.0) : 1.f;
+  red[w][c] = m;
+  __syncthreads();
+  if (w > 0 || l >= Kp) return;
+#pragma unroll
+  for (int k = 1; k < 16; ++k) m = fmax(m, red[k][c]);
+  cs[l] = m > 0.0 ? (float)(m / 224.0) : 1.f;
 }
 
-// FP8 (hardware e4m3 encoding) copy of D_il / s_l, row-major, and the BF16
-// dwell-major copy for the back-projection, its points in the tile order of
-// each 32-point block (Mp is a multiple of 32).
-__global__ void k_cast_fp8(const double* __restrict__ D64, int Mp, int Kp,
-                           const float* __restrict__ cs, unsigned char* __restrict__ D8,
-                           uint16_t* __restrict__ DT) {
-  const size_t n = (size_t)Mp * Kp;
-  for (size_t idx = blockIdx.x * (size_t)blockDim.x + threadIdx.x; idx < n;
+// FP8 (hardware e4m3 encoding) copy of D_il / s_l, row-major, four columns
+// per thread.
+__global__ void k_cast_fp8(const float* __restrict__ D32, size_t n4, int Kp4, const float* __restrict__ cs,
+                           unsigned* __restrict__ D8) {
+  for (size_t idx = blockIdx.x * (size_t)blockDim.x + threadIdx.x; idx < n4;
        idx += (size_t)gridDim.x * blockDim.x) {
-    const size_t i = idx / Kp, l = idx - i * Kp;
-    const float v = (float)D64[idx];
-    D8[idx] = (unsigned char)(__builtin_amdgcn_cvt_pk_fp8_f32(v / cs[l], 0.f, 0, false) & 0xff);
-    DT[l * Mp + (i & ~(size_t)31) + tpos32((int)(i & 31))] = bf16_rne(v);
+    const float4 v = reinterpret_cast<const float4*>(D32)[idx];
+    const float4 s = reinterpret_cast<const float4*>(cs)[idx % Kp4];
+    const int lo = __builtin_amdgcn_cvt_pk_fp8_f32(v.x / s.x, v.y / s.y, 0, false);
+    D8[idx] = (unsigned)__builtin_amdgcn_cvt_pk_fp8_f32(v.z / s.z, v.w / s.w, lo, true);
   }
 }
 
@@ -110,17 +184,14 @@ __global__ void k_widen_fp8(const unsigned char* __restrict__ D8, const float* _
   }
 }
 
-// t_bar = Rx / mean over the target rows of sum_l D_il, one workgroup, fixed
-// summation order.
-__global__ void k_start_time(const double* __restrict__ D64, int Kp, int r0, int r1, double rx,
-                             double* __restrict__ t_bar) {
+// t_bar = Rx / mean over the target rows of sum_l D_il, from the row sums:
+// one workgroup, fixed summation order.
+__global__ __launch_bounds__(1024) void k_start_time(const double* __restrict__ rowsum, int r0, int r1, double rx,
+                                                     double* __restrict__ t_bar) {
   __shared__ double red[1024];
   double acc = 0.0;
-  for (int i = r0 + threadIdx.x; i < r1; i += blockDim.x) {
-    double rs = 0.0;
-    for (int l = 0; l < Kp; ++l) rs += D64[(size_t)i * Kp + l];
-    acc += rs;
-  }
+#pragma unroll 8
+  for (int i = r0 + threadIdx.x; i < r1; i += 1024) acc += rowsum[i];
   red[threadIdx.x] = acc;
   __syncthreads();
   for (int o = blockDim.x / 2; o > 0; o >>= 1) {
@@ -265,46 +336,62 @@ hipError_t launch_pick_start(const double* F_warm, const double* F_uniform, cons
 hipError_t launch_dose_rate(const double* dwell_xyz, const double* pt_xyz, const double* user_D,
                             const int* perm, int M, int K, int Mp, int Kp, double* D64,
                             hipStream_t st) {
-  dim3 grid((Kp + 127) / 128, Mp);
-  hipLaunchKernelGGL(k_dose_rate, grid, dim3(128), 0, st, dwell_xyz, pt_xyz, user_D, perm, M, K,
-                     Mp, Kp, D64);
+  DoseArgs a{};
+  a.dwell = dwell_xyz;
+  a.pts = pt_xyz;
+  a.user_D = user_D;
+  a.perm = perm;
+  a.M = M;
+  a.K = K;
+  a.Mp = Mp;
+  a.Kp = Kp;
+  a.D64 = D64;
+  hipLaunchKernelGGL((k_dose_matrix<DOSE_D64>), dim3(Mp / 32), dim3(256), 0, st, a);
   return hipGetLastError();
 }
 
-hipError_t launch_cast_dose(const double* D64, int Mp, int Kp, int dtype, float* D32, void* Dlp,
-                            void* DTlp, float* colscale, hipStream_t st) {
-  (void)colscale;
-  const size_t n = (size_t)Mp * Kp;
-  hipLaunchKernelGGL(k_cast_f32, dim3(1024), dim3(256), 0, st, D64, n, D32);
+hipError_t launch_dose_setup(const double* dwell_xyz, const double* pt_xyz, const double* user_D,
+                             const int* perm, int M, int K, int Mp, int Kp, int dtype, int row_begin,
+                             int row_end, double prescription, double* D64, float* D32, void* Dlp, void* DTlp,
+                             float* colscale, double* scratch, double* t_bar, hipStream_t st) {
+  DoseArgs a{};
+  a.dwell = dwell_xyz;
+  a.pts = pt_xyz;
+  a.user_D = user_D;
+  a.perm = perm;
+  a.M = M;
+  a.K = K;
+  a.Mp = Mp;
+  a.Kp = Kp;
+  a.r0 = row_begin;
+  a.r1 = row_end;
+  a.D64 = D64;
+  a.D32 = D32;
+  a.D16 = (uint16_t*)Dlp;
+  a.DT16 = (uint16_t*)DTlp;
+  a.rowsum = scratch;
+  a.colmax = scratch + Mp;
+  const dim3 grid(Mp / 32), block(256);
+  if (dtype == GMCO_DTYPE_BF16) hipLaunchKernelGGL((k_dose_matrix<DOSE_BF16>), grid, block, 0, st, a);
+  else if (dtype == GMCO_DTYPE_FP8) hipLaunchKernelGGL((k_dose_matrix<DOSE_FP8>), grid, block, 0, st, a);
+  else hipLaunchKernelGGL((k_dose_matrix<DOSE_F32>), grid, block, 0, st, a);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
-  if (dtype == GMCO_DTYPE_BF16) {
-    hipLaunchKernelGGL(k_cast_bf16, dim3(1024), dim3(256), 0, st, D64, Mp, Kp, (uint16_t*)Dlp,
-                       (uint16_t*)DTlp);
-    return hipGetLastError();
-  }
   if (dtype == GMCO_DTYPE_FP8) {
-    hipLaunchKernelGGL(k_colscale, dim3(Kp), dim3(256), 0, st, D64, Mp, Kp, colscale);
+    hipLaunchKernelGGL(k_colscale, dim3((Kp + 63) / 64), dim3(1024), 0, st, a.colmax, Mp / 32, Kp, colscale);
+    hipLaunchKernelGGL(k_cast_fp8, dim3(1024), dim3(256), 0, st, D32, (size_t)Mp * Kp / 4, Kp / 4, colscale,
+                       (unsigned*)Dlp);
     e = hipGetLastError();
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(k_cast_fp8, dim3(1024), dim3(256), 0, st, D64, Mp, Kp, colscale,
-                       (unsigned char*)Dlp, (uint16_t*)DTlp);
-    return hipGetLastError();
   }
-  return hipSuccess;
+  hipLaunchKernelGGL(k_start_time, dim3(1), dim3(1024), 0, st, a.rowsum, row_begin, row_end, prescription, t_bar);
+  return hipGetLastError();
 }
 
 hipError_t launch_widen_fp8(const void* D8, const float* colscale, int Mp, int Kp, double* out,
                             hipStream_t st) {
   hipLaunchKernelGGL(k_widen_fp8, dim3(1024), dim3(256), 0, st, (const unsigned char*)D8,
                      colscale, Mp, Kp, out);
-  return hipGetLastError();
-}
-
-hipError_t launch_start_time(const double* D64, int Kp, int row_begin, int row_end,
-                             double prescription, double* t_bar, hipStream_t st) {
-  hipLaunchKernelGGL(k_start_time, dim3(1), dim3(1024), 0, st, D64, Kp, row_begin, row_end,
-                     prescription, t_bar);
   return hipGetLastError();
 }
 

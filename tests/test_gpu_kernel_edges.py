@@ -61,3 +61,41 @@ def test_update_forms_agree_bitwise(n_cath, n_dw, M, m):
         out.append((pl.weights_x(), pl.metrics()["F_run"], pl.metrics()["evaluations"]))
     for a, b in zip(*out):
         np.testing.assert_array_equal(a, b)
+
+
+# The set-up kernel takes 32 rows and 64 columns at a time; the row sums of the
+# start time start and end inside a block of rows when the target does not
+# come first.  Tolerances: the matrix within 8 FP64 roundings of the oracle's,
+# the start time within 1e-13; the run-precision copies bit for bit.
+@pytest.mark.parametrize("n_cath,n_dw,M", [(1, 1, 15), (3, 11, 75), (5, 13, 160), (8, 12, 1005), (20, 25, 333)])
+@pytest.mark.parametrize("dtype", ["f32", "bf16", "fp8"])
+def test_dose_setup_edges(n_cath, n_dw, M, dtype):
+    import torch
+    announce(f"dose set-up K={n_cath * n_dw} M={M} {dtype}")
+    c = _case(n_cath, n_dw, M)
+    target = 2 if M > 100 else 0
+    D = O.dose_rate_matrix(c.dwell_xyz, c.pt_xyz)
+    from paper_1904_01567_amd import Planner
+    pl = Planner(dtype=dtype, max_plans=2)
+    pl.load(c, PARAMS, target_group=target)
+    Dg = pl.dose_rate()
+    np.testing.assert_allclose(Dg, D, rtol=4e-16 * 8, atol=0)
+    tb = 15.0 / Dg[c.group == target].sum(axis=1).mean()
+    assert pl.start_time() == pytest.approx(tb, rel=1e-13)
+    D32 = Dg.astype(np.float32)
+    if dtype == "f32":
+        ref = D32.astype(np.float64)
+    elif dtype == "bf16":
+        ref = torch.tensor(D32).to(torch.bfloat16).double().numpy()
+    else:
+        s = (Dg.max(axis=0) / 224.0).astype(np.float32)
+        ref = torch.tensor(D32 / s[None, :]).to(torch.float8_e4m3fn).double().numpy() * s[None, :].astype(np.float64)
+    np.testing.assert_array_equal(pl.dose_rate(run_dtype=True), ref)
+    # the dwell-major copy feeds the back-projection: the gradient of one plan
+    x = np.full((1, c.K), np.sqrt(tb)) * (0.3 + cases.uniform_draws((1, c.K), seed=9))
+    W = cases.hidden_weights(1, seed=3)
+    pl.set_weights(W)
+    _, g = pl.evaluate(x)
+    _, gr = O.objective_and_gradient_x(D, x, c.group, PARAMS, W)
+    tol = {"f32": 2e-4, "bf16": 5e-2, "fp8": 0.25}[dtype]
+    assert np.abs(g - gr).max() <= tol * np.abs(gr).max()
