@@ -19,145 +19,293 @@ namespace {
 typedef float f4v __attribute__((ext_vector_type(4)));
 typedef __bf16 bf8v __attribute__((ext_vector_type(8)));
 
+// The network's products C[i][j] = sum_k A[i][k] B[k][j] on 16x16x32 BF16
+// matrix ops, in the three forms of a training step:
+//   FWD   act' = relu?(act W^T + b): A and B contiguous in k;
+//   DACT  dact = (G W) masked by act > 0: A contiguous in k, B in j;
+//   DW    dW = G^T act, contraction over the batch: A contiguous in i, B in j.
+// A workgroup of four wavefronts (2 x 2) computes a T x T tile.  Slices of 64
+// k are read along the contiguous dimension into registers, two slices ahead,
+// and staged in LDS as BF16 (two buffers, one barrier per slice).  The sizes of
+// this network leave every product bound by latency: few tiles, each a chain
+// of slices.  So T = 32 unless 64 x 64 tiles already fill the chip twice
+// (kGemmWide), and all weight gradients of a step are one launch.  The
+// contraction runs in ascending steps of 32 in every form and tile, so the
+// tile does not change a bit of the result.
+// Measured (batch 1,024, layers 68-256-256-256-360): 73 us per product with
+// 64 x 64 tiles, strided scalar loads and no prefetch, 11 products a step;
+// the training step went from 1,785 to 87 us (7 to 12 us per product, 21 for the
+// weight gradients with their Adam update).
+enum { GEMM_FWD = 0, GEMM_FWD_MSE = 1, GEMM_DACT = 2, GEMM_DW = 3, GEMM_DW_ADAM = 4 };
+
+struct AdamArgs {
+  float lr, b1, b2, eps, c1, c2;
+};
+
 struct GemmArgs {
-  const float* A;  // element (i, k) at A[i * sai + k * sak]
-  long sai, sak;
-  const float* B;  // element (k, j) at B[k * sbk + j * sbj]
-  long sbk, sbj;
-  float* C;        // C[i * ldc + j]
-  long ldc;
-  const float* bias;  // per column j, or NULL
+  const float* A;
+  const float* B;
+  const int* rows;     // FWD: row i of A is rows[i] (NULL: itself), and
+  float* gathered;     // these rows are written here (M x K)
+  float* C;
+  const float* bias;   // FWD: per column j
+  const float* act;    // DACT: activations that mask C (same shape)
+  const float* y;      // FWD_MSE: targets, row i at yrows[i]
+  const int* yrows;
+  double* loss;        // FWD_MSE: squared error of each tile
+  float scale;         // FWD_MSE: 2 / (M N)
+  float *p, *m, *v;    // DW_ADAM: parameters and moments, C's layout
+  int lda, ldb;        // elements between rows of A and B as stored
   int M, N, K;
   int relu;
 };
 
-// 64 x 64 output tile per workgroup, 4 waves in 2 x 2, each a 32 x 32
-// sub-tile of 2 x 2 matrix ops; K in slices of 32 staged in LDS as BF16.
-__global__ __launch_bounds__(256) void k_gemm_bf16(GemmArgs g) {
-  constexpr int TS = 40;  // LDS row stride (elements): 80 B, conflict-free 16 B reads
-  __shared__ __attribute__((aligned(16))) __bf16 sA[64 * TS];
-  __shared__ __attribute__((aligned(16))) __bf16 sB[64 * TS];  // transposed: [j][k]
+constexpr int kGemmWide = 512;  // 64 x 64 tiles from this many workgroups (two per compute unit)
+constexpr int kKS = 64;         // k per slice
+constexpr int kTS = kKS + 8;    // LDS row stride: 144 B, 16-byte aligned operand reads
+
+// Adam's update from the gradient gi; the order of the fused operations is
+// written out so that every caller rounds alike.
+__device__ inline void adam_update(float gi, float& p, float& m, float& v, const AdamArgs& a) {
+  m = fmaf(1.f - a.b1, gi, a.b1 * m);
+  v = fmaf(gi, (1.f - a.b2) * gi, a.b2 * v);
+  p -= a.lr * (m / a.c1) / (sqrtf(v / a.c2) + a.eps);
+}
+
+// One slice of an operand, T rows (i or j) x 64 k, into registers.  KC: the
+// stored rows are this operand's rows, contiguous in k (row r at rows[r] if
+// given); otherwise the stored rows are k, contiguous in the operand's rows.
+template <int T, bool KC>
+__device__ inline void gemm_load(const float* __restrict__ src, const int* __restrict__ rows, int ld, int r0, int R,
+                                 int k0, int K, int tid, float (&v)[T * kKS / 256]) {
+#pragma unroll
+  for (int u = 0; u < T * kKS / 256; ++u) {
+    const int e = tid + 256 * u;
+    const int r = r0 + (KC ? e / kKS : e % T), k = k0 + (KC ? e % kKS : e / T);
+    v[u] = 0.f;
+    if (r < R && k < K) {
+      const int s = KC ? r : k, c = KC ? k : r;
+      v[u] = src[(size_t)(rows ? rows[s] : s) * ld + c];
+    }
+  }
+}
+
+template <int T, bool KC>
+__device__ inline void gemm_stage(__bf16* dst, int tid, const float (&v)[T * kKS / 256]) {
+#pragma unroll
+  for (int u = 0; u < T * kKS / 256; ++u) {
+    const int e = tid + 256 * u;
+    dst[(KC ? e / kKS : e % T) * kTS + (KC ? e % kKS : e / T)] = (__bf16)v[u];
+  }
+}
+
+template <int T, int FORM>
+__device__ inline void gemm_tile(const GemmArgs& g, int bi, int bj, const AdamArgs& ad) {
+  constexpr bool AK = FORM <= GEMM_DACT, BK = FORM <= GEMM_FWD_MSE;
+  constexpr int NL = T * kKS / 256;
+  constexpr int S = T / 32;  // 16-wide sub-tiles per wavefront and side
+  __shared__ __attribute__((aligned(16))) __bf16 sA[2][T * kTS];
+  __shared__ __attribute__((aligned(16))) __bf16 sB[2][T * kTS];
+  __shared__ double sL[4];
   const int tid = threadIdx.x;
   const int wave = tid >> 6, lane = tid & 63, q = lane >> 4, n = lane & 15;
-  const int i0 = blockIdx.y * 64, j0 = blockIdx.x * 64;
-  const int wr = (wave >> 1) * 32, wc = (wave & 1) * 32;
-  f4v acc[2][2];
+  const int i0 = bi * T, j0 = bj * T;
+  const int wr = (wave >> 1) * (T / 2), wc = (wave & 1) * (T / 2);
+  const int* arows = FORM <= GEMM_FWD_MSE ? g.rows : nullptr;
+  f4v acc[S][S];
 #pragma unroll
-  for (int a = 0; a < 2; ++a)
+  for (int a = 0; a < S; ++a)
 #pragma unroll
-    for (int b = 0; b < 2; ++b) acc[a][b] = f4v{0.f, 0.f, 0.f, 0.f};
-
-  for (int k0 = 0; k0 < g.K; k0 += 32) {
-    // stage: thread t covers row t / 4, k-offset (t % 4) * 8 .. +7
-    {
-      const int r = tid >> 2, kk = (tid & 3) * 8;
+    for (int b = 0; b < S; ++b) acc[a][b] = f4v{0.f, 0.f, 0.f, 0.f};
+  float ra[2][NL], rb[2][NL];
+  auto load = [&](int s, float (&va)[NL], float (&vb)[NL]) {
+    gemm_load<T, AK>(g.A, arows, g.lda, i0, g.M, s * kKS, g.K, tid, va);
+    gemm_load<T, BK>(g.B, nullptr, g.ldb, j0, g.N, s * kKS, g.K, tid, vb);
+  };
+  const int ns = (g.K + kKS - 1) / kKS;
+  auto step = [&](int s, __bf16* cA, __bf16* cB, float (&va)[NL], float (&vb)[NL]) {
+    gemm_stage<T, AK>(cA, tid, va);
+    gemm_stage<T, BK>(cB, tid, vb);
+    if constexpr (FORM <= GEMM_FWD_MSE) {
+      // the gathered rows, for the weight gradient (whose contraction over
+      // them would otherwise wait for each slice's row indices)
+      if (g.rows && bj == 0) {
 #pragma unroll
-      for (int e = 0; e < 8; ++e) {
-        const int i = i0 + r, k = k0 + kk + e, j = j0 + r;
-        const float av = (i < g.M && k < g.K) ? g.A[(long)i * g.sai + (long)k * g.sak] : 0.f;
-        const float bv = (j < g.N && k < g.K) ? g.B[(long)k * g.sbk + (long)j * g.sbj] : 0.f;
-        sA[r * TS + kk + e] = (__bf16)av;
-        sB[r * TS + kk + e] = (__bf16)bv;
-      }
-    }
-    __syncthreads();
-    bf8v af[2], bfr[2];
-#pragma unroll
-    for (int a = 0; a < 2; ++a) {
-      af[a] = *reinterpret_cast<const bf8v*>(&sA[(wr + 16 * a + n) * TS + 8 * q]);
-      bfr[a] = *reinterpret_cast<const bf8v*>(&sB[(wc + 16 * a + n) * TS + 8 * q]);
-    }
-#pragma unroll
-    for (int a = 0; a < 2; ++a)
-#pragma unroll
-      for (int b = 0; b < 2; ++b)
-        acc[a][b] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(af[a], bfr[b], acc[a][b], 0, 0, 0);
-    __syncthreads();
-  }
-#pragma unroll
-  for (int a = 0; a < 2; ++a)
-#pragma unroll
-    for (int b = 0; b < 2; ++b)
-#pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        const int i = i0 + wr + 16 * a + 4 * q + r, j = j0 + wc + 16 * b + n;
-        if (i < g.M && j < g.N) {
-          float v = acc[a][b][r];
-          if (g.bias) v += g.bias[j];
-          if (g.relu) v = fmaxf(v, 0.f);
-          g.C[(long)i * g.ldc + j] = v;
+        for (int u = 0; u < NL; ++u) {
+          const int e = tid + 256 * u;
+          const int i = i0 + e / kKS, k = s * kKS + e % kKS;
+          if (i < g.M && k < g.K) g.gathered[(size_t)i * g.K + k] = va[u];
         }
       }
-}
-
-// dL/dout for L = mean((out - y)^2) over B x N entries, and the per-row
-// partial sums of the squared error (summed in fixed order afterwards).
-__global__ void k_mse(const float* __restrict__ out, const float* __restrict__ y, int B, int N,
-                      float* __restrict__ g, double* __restrict__ row_loss) {
-  const int i = blockIdx.x;
-  __shared__ double red[256];
-  double s = 0.0;
-  const float scale = 2.f / ((float)B * (float)N);
-  for (int j = threadIdx.x; j < N; j += blockDim.x) {
-    const float d = out[(size_t)i * N + j] - y[(size_t)i * N + j];
-    g[(size_t)i * N + j] = scale * d;
-    s += (double)d * (double)d;
-  }
-  red[threadIdx.x] = s;
-  __syncthreads();
-  for (int o = blockDim.x / 2; o > 0; o >>= 1) {
-    if ((int)threadIdx.x < o) red[threadIdx.x] += red[threadIdx.x + o];
+    }
+    if (s + 2 < ns) load(s + 2, va, vb);
     __syncthreads();
+#pragma unroll
+    for (int h = 0; h < kKS / 32; ++h) {
+      if (s * kKS + 32 * h >= g.K) break;
+      bf8v af[S], bfr[S];
+#pragma unroll
+      for (int a = 0; a < S; ++a) {
+        af[a] = *reinterpret_cast<const bf8v*>(&cA[(wr + 16 * a + n) * kTS + 32 * h + 8 * q]);
+        bfr[a] = *reinterpret_cast<const bf8v*>(&cB[(wc + 16 * a + n) * kTS + 32 * h + 8 * q]);
+      }
+#pragma unroll
+      for (int a = 0; a < S; ++a)
+#pragma unroll
+        for (int b = 0; b < S; ++b)
+          acc[a][b] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(af[a], bfr[b], acc[a][b], 0, 0, 0);
+    }
+  };
+  load(0, ra[0], rb[0]);
+  if (ns > 1) load(1, ra[1], rb[1]);
+  for (int s = 0; s < ns; s += 2) {
+    step(s, sA[0], sB[0], ra[0], rb[0]);
+    if (s + 1 < ns) step(s + 1, sA[1], sB[1], ra[1], rb[1]);
   }
-  if (threadIdx.x == 0) row_loss[i] = red[0];
-}
-
-__global__ void k_sum_loss(const double* __restrict__ row_loss, int B, int N, double* __restrict__ out) {
-  __shared__ double red[256];
-  double s = 0.0;
-  for (int i = threadIdx.x; i < B; i += blockDim.x) s += row_loss[i];
-  red[threadIdx.x] = s;
-  __syncthreads();
-  for (int o = blockDim.x / 2; o > 0; o >>= 1) {
-    if ((int)threadIdx.x < o) red[threadIdx.x] += red[threadIdx.x + o];
+  double sq = 0.0;
+  // element e = (a, b, r) of the tile: row and column of accumulator register r
+  auto row = [&](int e) { return i0 + wr + 16 * (e / (4 * S)) + 4 * q + e % 4; };
+  auto col = [&](int e) { return j0 + wc + 16 * (e / 4 % S) + n; };
+  constexpr int NE = 4 * S * S;
+  float e0[NE], e1[NE], e2[NE];  // what the epilogue reads, all loads in flight together
+#pragma unroll
+  for (int e = 0; e < NE; ++e) {
+    const int i = row(e), j = col(e);
+    if (i >= g.M || j >= g.N) continue;
+    const size_t at = (size_t)i * g.N + j;
+    if constexpr (FORM <= GEMM_FWD_MSE) e0[e] = g.bias[j];
+    if constexpr (FORM == GEMM_FWD_MSE) e1[e] = g.y[(size_t)(g.yrows ? g.yrows[i] : i) * g.N + j];
+    if constexpr (FORM == GEMM_DACT) e0[e] = g.act[at];
+    if constexpr (FORM == GEMM_DW_ADAM) {
+      e0[e] = g.p[at];
+      e1[e] = g.m[at];
+      e2[e] = g.v[at];
+    }
+  }
+#pragma unroll
+  for (int e = 0; e < NE; ++e) {
+    const int i = row(e), j = col(e);
+    if (i >= g.M || j >= g.N) continue;
+    const size_t at = (size_t)i * g.N + j;
+    float v = acc[e / (4 * S)][e / 4 % S][e % 4];
+    if constexpr (FORM <= GEMM_FWD_MSE) v += e0[e];
+    if constexpr (FORM == GEMM_FWD) {
+      if (g.relu) v = fmaxf(v, 0.f);
+    }
+    if constexpr (FORM == GEMM_FWD_MSE) {
+      // dL/dout for L = mean((out - y)^2)
+      const float d = v - e1[e];
+      sq += (double)d * (double)d;
+      v = g.scale * d;
+    }
+    if constexpr (FORM == GEMM_DACT) {
+      if (!(e0[e] > 0.f)) v = 0.f;
+    }
+    if constexpr (FORM == GEMM_DW_ADAM) {
+      adam_update(v, e0[e], e1[e], e2[e], ad);
+      g.p[at] = e0[e];
+      g.m[at] = e1[e];
+      g.v[at] = e2[e];
+    } else {
+      g.C[at] = v;
+    }
+  }
+  if constexpr (FORM == GEMM_FWD_MSE) {
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1) sq += __shfl_xor(sq, o);
+    if (lane == 0) sL[wave] = sq;
     __syncthreads();
+    if (tid == 0) g.loss[(size_t)bi * gridDim.y + bj] = (sL[0] + sL[1]) + (sL[2] + sL[3]);
   }
-  if (threadIdx.x == 0) *out = red[0] / ((double)B * (double)N);
 }
 
-__global__ void k_relu_back(float* __restrict__ g, const float* __restrict__ act, size_t n) {
-  for (size_t i = blockIdx.x * (size_t)blockDim.x + threadIdx.x; i < n; i += (size_t)gridDim.x * blockDim.x)
-    if (!(act[i] > 0.f)) g[i] = 0.f;
+template <int T, int FORM>
+__global__ __launch_bounds__(256, 2) void k_gemm(GemmArgs g) {
+  gemm_tile<T, FORM>(g, blockIdx.x, blockIdx.y, AdamArgs{});
 }
 
-// db[j] = sum_i g[i][j], fixed order over rows
-__global__ void k_colsum(const float* __restrict__ g, int B, int N, float* __restrict__ db) {
-  const int j = blockIdx.x * blockDim.x + threadIdx.x;
-  if (j >= N) return;
+// Bias gradient db[j] = sum_i g[i][j] of 64 columns, in row order: chunks of
+// 128 rows through registers (the next chunk in flight) into LDS, added by one
+// wavefront.
+__device__ inline float bias_sum(const float* __restrict__ G, int B, int N, int j0) {
+  constexpr int R = 32;
+  __shared__ float sG[4 * R][64];
+  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+  const int j = min(j0 + lane, N - 1);
+  float v[R];
+  auto load = [&](int b) {
+#pragma unroll
+    for (int u = 0; u < R; ++u) {
+      const int i = b + wave * R + u;
+      v[u] = i < B ? G[(size_t)i * N + j] : 0.f;
+    }
+  };
+  load(0);
   float s = 0.f;
-  for (int i = 0; i < B; ++i) s += g[(size_t)i * N + j];
-  db[j] = s;
+  for (int b = 0; b < B; b += 4 * R) {
+#pragma unroll
+    for (int u = 0; u < R; ++u) sG[wave * R + u][lane] = v[u];
+    __syncthreads();
+    if (b + 4 * R < B) load(b + 4 * R);
+    if (wave == 0) {
+      const int n = min(4 * R, B - b);
+#pragma unroll 16
+      for (int i = 0; i < n; ++i) s += sG[i][lane];
+    }
+    __syncthreads();
+  }
+  return s;
 }
 
-__global__ void k_adam(float* __restrict__ p, const float* __restrict__ g, float* __restrict__ m,
-                       float* __restrict__ v, size_t n, float lr, float b1, float b2, float eps,
-                       float c1, float c2) {
-  for (size_t i = blockIdx.x * (size_t)blockDim.x + threadIdx.x; i < n; i += (size_t)gridDim.x * blockDim.x) {
-    const float gi = g[i];
-    const float mi = b1 * m[i] + (1.f - b1) * gi;
-    const float vi = b2 * v[i] + (1.f - b2) * gi * gi;
-    m[i] = mi;
-    v[i] = vi;
-    p[i] -= lr * (mi / c1) / (sqrtf(vi / c2) + eps);
+// Weight and bias gradients of up to kDwLayers layers in one launch: layer l's
+// tiles are workgroups first[l] .. first[l + 1] - 1, its bias columns the last
+// ceil(out / 64) of them.  ADAM: the parameters are updated in place of
+// storing the gradient (nothing later in the step reads them).
+constexpr int kDwLayers = 6;
+struct DwArgs {
+  GemmArgs g[kDwLayers];
+  float* db[kDwLayers];  // bias gradient; ADAM: bias parameters, with their moments
+  float* dbm[kDwLayers];
+  float* dbv[kDwLayers];
+  int first[kDwLayers + 1];
+  int n;
+  AdamArgs ad;
+};
+
+template <int T, bool ADAM>
+__global__ __launch_bounds__(256, 2) void k_dw(DwArgs a) {
+  int l = 0;
+  while (l + 1 < a.n && (int)blockIdx.x >= a.first[l + 1]) ++l;
+  const GemmArgs& g = a.g[l];
+  const int t = blockIdx.x - a.first[l];
+  const int tj = (g.N + T - 1) / T, tiles = tj * ((g.M + T - 1) / T);
+  if (t < tiles) {
+    gemm_tile<T, ADAM ? GEMM_DW_ADAM : GEMM_DW>(g, t / tj, t % tj, a.ad);
+  } else {
+    const int j0 = (t - tiles) * 64;
+    const float s = bias_sum(g.A, g.K, g.M, j0);
+    const int j = j0 + (int)threadIdx.x;
+    if (threadIdx.x < 64 && j < g.M) {
+      if constexpr (ADAM) adam_update(s, a.db[l][j], a.dbm[l][j], a.dbv[l][j], a.ad);
+      else a.db[l][j] = s;
+    }
   }
 }
 
-__global__ void k_gather_rows(const float* __restrict__ src, const int* __restrict__ idx, int B, int N,
-                              float* __restrict__ dst) {
-  const int i = blockIdx.x;
-  if (i >= B) return;
-  const size_t s = (size_t)idx[i];
-  for (int j = threadIdx.x; j < N; j += blockDim.x) dst[(size_t)i * N + j] = src[s * N + j];
+// Mean squared error of step blockIdx.x from its tiles' sums, in a fixed order.
+__global__ __launch_bounds__(256) void k_sum_loss(const double* __restrict__ tile_loss, int n, double count,
+                                                  double* __restrict__ out) {
+  __shared__ double red[256];
+  const double* src = tile_loss + (size_t)blockIdx.x * n;
+  double s = 0.0;
+  for (int i = threadIdx.x; i < n; i += blockDim.x) s += src[i];
+  red[threadIdx.x] = s;
+  __syncthreads();
+  for (int o = blockDim.x / 2; o > 0; o >>= 1) {
+    if ((int)threadIdx.x < o) red[threadIdx.x] += red[threadIdx.x + o];
+    __syncthreads();
+  }
+  if (threadIdx.x == 0) out[blockIdx.x] = red[0] / count;
 }
 
 // Case features: for dwell l and structure j the distance to the nearest
@@ -213,10 +361,10 @@ struct gmco_mlp {
   std::vector<float*> act;   // act[0] = input, act[k+1] = output of layer k
   std::vector<float*> dact;  // gradient buffers, same shapes
   float* y = nullptr;        // targets of the batch
-  double* row_loss = nullptr;
   double* loss = nullptr;
-  int* idx = nullptr;
   float *dataX = nullptr, *dataY = nullptr;
+  void* steps = nullptr;     // order, tile losses and losses of a training call
+  size_t steps_bytes = 0;
   int n_data = 0;
   int adam_step = 0;
   std::vector<void*> owned;
@@ -236,56 +384,136 @@ int mfail(gmco_mlp* m, int code, const std::string& msg) {
     if (e_ != hipSuccess) return mfail((mm), GMCO_EHIP, std::string(#call) + ": " + hipGetErrorString(e_)); \
   } while (0)
 
-hipError_t gemm(hipStream_t st, const float* A, long sai, long sak, const float* B, long sbk, long sbj,
-                float* C, long ldc, const float* bias, int M, int N, int K, int relu) {
-  GemmArgs a{A, sai, sak, B, sbk, sbj, C, ldc, bias, M, N, K, relu};
-  hipLaunchKernelGGL(k_gemm_bf16, dim3((N + 63) / 64, (M + 63) / 64), dim3(256), 0, st, a);
+int layers(const gmco_mlp* m) { return (int)m->sizes.size() - 1; }
+
+int tiles_of(int rows, int cols, int T) { return ((rows + T - 1) / T) * ((cols + T - 1) / T); }
+
+template <int FORM>
+hipError_t gemm(hipStream_t st, const GemmArgs& a) {
+  if constexpr (FORM != GEMM_FWD_MSE) {  // (whose tile losses are laid out for 32 x 32 tiles)
+    if (tiles_of(a.M, a.N, 64) >= kGemmWide) {
+      hipLaunchKernelGGL((k_gemm<64, FORM>), dim3((a.M + 63) / 64, (a.N + 63) / 64), dim3(256), 0, st, a);
+      return hipGetLastError();
+    }
+  }
+  hipLaunchKernelGGL((k_gemm<32, FORM>), dim3((a.M + 31) / 32, (a.N + 31) / 32), dim3(256), 0, st, a);
   return hipGetLastError();
 }
 
-int layers(const gmco_mlp* m) { return (int)m->sizes.size() - 1; }
+GemmArgs forward_args(const gmco_mlp* m, int B, int k, const float* in, const int* rows) {
+  GemmArgs a{};
+  a.A = k == 0 ? in : m->act[k];
+  a.rows = k == 0 ? rows : nullptr;
+  a.gathered = m->act[0];
+  a.B = m->p + m->woff[k];
+  a.C = m->act[k + 1];
+  a.bias = m->p + m->boff[k];
+  a.lda = a.ldb = m->sizes[k];
+  a.M = B;
+  a.N = m->sizes[k + 1];
+  a.K = m->sizes[k];
+  a.relu = k < layers(m) - 1;
+  return a;
+}
 
-// forward over act[0] (B rows): act[k+1] = relu?(act[k] W_k^T + b_k), on
-// stream st (the network's own unless a caller's)
-hipError_t forward(gmco_mlp* m, int B, hipStream_t st) {
-  const int L = layers(m);
-  for (int k = 0; k < L; ++k) {
-    const int in = m->sizes[k], out = m->sizes[k + 1];
-    hipError_t e = gemm(st, m->act[k], in, 1, m->p + m->woff[k], 1, in, m->act[k + 1], out,
-                        m->p + m->boff[k], B, out, in, k < L - 1);
+// forward over B rows of `in` (row i at rows[i] if given): act[k+1] =
+// relu?(act[k] W_k^T + b_k), on stream st (the network's own unless a
+// caller's); layers 0 .. n - 1
+hipError_t forward(gmco_mlp* m, int B, const float* in, const int* rows, int n, hipStream_t st) {
+  for (int k = 0; k < n; ++k) {
+    const hipError_t e = gemm<GEMM_FWD>(st, forward_args(m, B, k, in, rows));
     if (e != hipSuccess) return e;
   }
   return hipSuccess;
 }
-hipError_t forward(gmco_mlp* m, int B) { return forward(m, B, m->stream); }
 
-// backward from the targets in m->y; gradients into m->g, loss into *m->loss
-hipError_t backward(gmco_mlp* m, int B) {
+// One training step's products on B rows of `in` and `y` (at rows[i] if
+// given): forward with the squared error's derivative and tile sums (into
+// tile_loss), the activations' gradients, then every layer's weight and bias
+// gradients into m->g, or, with ad, their Adam update of m->p.
+hipError_t step_products(gmco_mlp* m, int B, const float* in, const float* y, const int* rows, double* tile_loss,
+                         const AdamArgs* ad) {
   const int L = layers(m);
-  const int nout = m->sizes[L];
-  hipLaunchKernelGGL(k_mse, dim3(B), dim3(256), 0, m->stream, m->act[L], m->y, B, nout, m->dact[L],
-                     m->row_loss);
-  hipLaunchKernelGGL(k_sum_loss, dim3(1), dim3(256), 0, m->stream, m->row_loss, B, nout, m->loss);
-  for (int k = L - 1; k >= 0; --k) {
-    const int in = m->sizes[k], out = m->sizes[k + 1];
-    float* G = m->dact[k + 1];
-    if (k < L - 1) {
-      hipLaunchKernelGGL(k_relu_back, dim3(256), dim3(256), 0, m->stream, G, m->act[k + 1],
-                         (size_t)B * out);
-    }
-    // dW_k = G^T act[k]   (out x in), contraction over the batch
-    hipError_t e = gemm(m->stream, G, 1, out, m->act[k], in, 1, m->g + m->woff[k], in, nullptr, out, in,
-                        B, 0);
+  hipError_t e = forward(m, B, in, rows, L - 1, m->stream);
+  if (e != hipSuccess) return e;
+  GemmArgs f = forward_args(m, B, L - 1, in, rows);
+  f.C = m->dact[L];
+  f.y = y;
+  f.yrows = rows;
+  f.loss = tile_loss;
+  f.scale = 2.f / ((float)B * (float)m->sizes[L]);
+  e = gemm<GEMM_FWD_MSE>(m->stream, f);
+  if (e != hipSuccess) return e;
+  for (int k = L - 1; k > 0; --k) {  // d act[k] = (G W_k) where act[k] > 0   (B x in)
+    GemmArgs a{};
+    a.A = m->dact[k + 1];
+    a.B = m->p + m->woff[k];
+    a.C = m->dact[k];
+    a.act = m->act[k];
+    a.lda = m->sizes[k + 1];
+    a.ldb = m->sizes[k];
+    a.M = B;
+    a.N = m->sizes[k];
+    a.K = m->sizes[k + 1];
+    e = gemm<GEMM_DACT>(m->stream, a);
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(k_colsum, dim3((out + 255) / 256), dim3(256), 0, m->stream, G, B, out,
-                       m->g + m->boff[k]);
-    if (k > 0) {
-      // d act[k] = G W_k   (B x in)
-      e = gemm(m->stream, G, out, 1, m->p + m->woff[k], in, 1, m->dact[k], in, nullptr, B, in, out, 0);
-      if (e != hipSuccess) return e;
-    }
   }
-  return hipGetLastError();
+  for (int k0 = 0; k0 < L; k0 += kDwLayers) {
+    DwArgs d{};
+    d.n = std::min(kDwLayers, L - k0);
+    int wide = 0;
+    for (int l = 0; l < d.n; ++l) wide += tiles_of(m->sizes[k0 + l + 1], m->sizes[k0 + l], 64);
+    const int T = wide >= kGemmWide ? 64 : 32;
+    for (int l = 0; l < d.n; ++l) {  // dW_k = G^T act[k]   (out x in), contraction over the batch
+      const int k = k0 + l, out = m->sizes[k + 1], nin = m->sizes[k];
+      GemmArgs& a = d.g[l];
+      a.A = m->dact[k + 1];
+      a.lda = out;
+      a.B = k == 0 && !rows ? in : m->act[k];  // (gathered rows: written by the forward product)
+      a.ldb = nin;
+      a.M = out;
+      a.N = nin;
+      a.K = B;
+      a.C = m->g + m->woff[k];
+      a.p = m->p + m->woff[k];
+      a.m = m->m + m->woff[k];
+      a.v = m->v + m->woff[k];
+      d.db[l] = (ad ? m->p : m->g) + m->boff[k];
+      d.dbm[l] = m->m + m->boff[k];
+      d.dbv[l] = m->v + m->boff[k];
+      d.first[l + 1] = d.first[l] + tiles_of(out, nin, T) + (out + 63) / 64;
+    }
+    if (ad) d.ad = *ad;
+    const dim3 grid(d.first[d.n]);
+    if (ad && T == 64) hipLaunchKernelGGL((k_dw<64, true>), grid, dim3(256), 0, m->stream, d);
+    else if (ad) hipLaunchKernelGGL((k_dw<32, true>), grid, dim3(256), 0, m->stream, d);
+    else if (T == 64) hipLaunchKernelGGL((k_dw<64, false>), grid, dim3(256), 0, m->stream, d);
+    else hipLaunchKernelGGL((k_dw<32, false>), grid, dim3(256), 0, m->stream, d);
+    e = hipGetLastError();
+    if (e != hipSuccess) return e;
+  }
+  return hipSuccess;
+}
+
+int loss_tiles(const gmco_mlp* m, int B) { return tiles_of(B, m->sizes.back(), 32); }
+
+// Device memory of a training call, kept for the next one and grown when a
+// call needs more (its last work has ended: every call synchronises).
+hipError_t reserve_steps(gmco_mlp* m, size_t bytes) {
+  if (m->steps_bytes >= bytes) return hipSuccess;
+  if (m->steps) {
+    m->owned.erase(std::find(m->owned.begin(), m->owned.end(), m->steps));
+    (void)hipFree(m->steps);
+    m->steps = nullptr;
+    m->steps_bytes = 0;
+  }
+  void* p = nullptr;
+  const hipError_t e = hipMalloc(&p, bytes);
+  if (e != hipSuccess) return e;
+  m->owned.push_back(p);
+  m->steps = p;
+  m->steps_bytes = bytes;
+  return hipSuccess;
 }
 
 }  // namespace
@@ -330,9 +558,7 @@ int gmco_mlp_create(gmco_mlp** out, int device, const int* sizes, int n_sizes, i
     m->dact.push_back((float*)alloc((size_t)max_batch * sizes[k] * 4));
   }
   m->y = (float*)alloc((size_t)max_batch * sizes[n_sizes - 1] * 4);
-  m->row_loss = (double*)alloc((size_t)max_batch * 8);
-  m->loss = (double*)alloc(8);
-  m->idx = (int*)alloc((size_t)max_batch * 4);
+  m->loss = (double*)alloc((size_t)(1 + loss_tiles(m, max_batch)) * 8);  // the loss, then its tiles
   for (void* ptr : m->owned) ok = ok && ptr;
   if (!ok || hipMemset(m->p, 0, off * 4) != hipSuccess || hipMemset(m->m, 0, off * 4) != hipSuccess ||
       hipMemset(m->v, 0, off * 4) != hipSuccess) {
@@ -391,8 +617,10 @@ int gmco_mlp_loss_grad(gmco_mlp* m, int B, const float* X, const float* Y, doubl
   const int L = layers(m);
   MLP_HIP(m, hipMemcpyAsync(m->act[0], X, (size_t)B * m->sizes[0] * 4, hipMemcpyHostToDevice, m->stream));
   MLP_HIP(m, hipMemcpyAsync(m->y, Y, (size_t)B * m->sizes[L] * 4, hipMemcpyHostToDevice, m->stream));
-  MLP_HIP(m, forward(m, B));
-  MLP_HIP(m, backward(m, B));
+  MLP_HIP(m, step_products(m, B, m->act[0], m->y, nullptr, m->loss + 1, nullptr));
+  hipLaunchKernelGGL(k_sum_loss, dim3(1), dim3(256), 0, m->stream, m->loss + 1, loss_tiles(m, B),
+                     (double)B * (double)m->sizes[L], m->loss);
+  MLP_HIP(m, hipGetLastError());
   if (loss) MLP_HIP(m, hipMemcpyAsync(loss, m->loss, 8, hipMemcpyDeviceToHost, m->stream));
   if (grad) MLP_HIP(m, hipMemcpyAsync(grad, m->g, m->n_params * 4, hipMemcpyDeviceToHost, m->stream));
   MLP_HIP(m, hipStreamSynchronize(m->stream));
@@ -432,36 +660,28 @@ int gmco_mlp_train(gmco_mlp* m, int n_steps, int B, const int32_t* order, float 
     if (order[i] < 0 || order[i] >= m->n_data) return mfail(m, GMCO_EINVAL, "sample index out of range");
   MLP_HIP(m, hipSetDevice(m->device));
   const int L = layers(m);
-  int* dorder = nullptr;
-  double* losses = nullptr;
-  MLP_HIP(m, hipMalloc(&dorder, (size_t)n_steps * B * 4));
-  if (hipMalloc(&losses, (size_t)n_steps * 8) != hipSuccess) {
-    hipFree(dorder);
-    return mfail(m, GMCO_ENOMEM, "loss buffer");
-  }
-  struct Free {
-    void* a;
-    void* b;
-    ~Free() {
-      hipFree(a);
-      hipFree(b);
-    }
-  } guard{dorder, losses};
+  const int nt = loss_tiles(m, B);
+  const size_t order_bytes = ((size_t)n_steps * B * 4 + 255) / 256 * 256;
+  // tile losses of up to kLossSteps steps, reduced together
+  constexpr int kLossSteps = 64;
+  if (reserve_steps(m, order_bytes + ((size_t)n_steps + (size_t)std::min(n_steps, kLossSteps) * nt) * 8) != hipSuccess)
+    return mfail(m, GMCO_ENOMEM, "training buffers");
+  int* dorder = (int*)m->steps;
+  double* losses = (double*)((char*)m->steps + order_bytes);
+  double* tile_loss = losses + n_steps;
   MLP_HIP(m, hipMemcpyAsync(dorder, order, (size_t)n_steps * B * 4, hipMemcpyHostToDevice, m->stream));
   const float b1 = 0.9f, b2 = 0.999f, eps = 1e-8f;
   for (int s = 0; s < n_steps; ++s) {
-    hipLaunchKernelGGL(k_gather_rows, dim3(B), dim3(128), 0, m->stream, m->dataX, dorder + (size_t)s * B, B,
-                       m->sizes[0], m->act[0]);
-    hipLaunchKernelGGL(k_gather_rows, dim3(B), dim3(128), 0, m->stream, m->dataY, dorder + (size_t)s * B, B,
-                       m->sizes[L], m->y);
-    MLP_HIP(m, forward(m, B));
-    MLP_HIP(m, backward(m, B));
-    MLP_HIP(m, hipMemcpyAsync(losses + s, m->loss, 8, hipMemcpyDeviceToDevice, m->stream));
     m->adam_step += 1;
-    const float c1 = 1.f - powf(b1, (float)m->adam_step), c2 = 1.f - powf(b2, (float)m->adam_step);
-    hipLaunchKernelGGL(k_adam, dim3(256), dim3(256), 0, m->stream, m->p, m->g, m->m, m->v, m->n_params, lr, b1,
-                       b2, eps, c1, c2);
-    MLP_HIP(m, hipGetLastError());
+    const AdamArgs ad{lr, b1, b2, eps, 1.f - powf(b1, (float)m->adam_step), 1.f - powf(b2, (float)m->adam_step)};
+    MLP_HIP(m, step_products(m, B, m->dataX, m->dataY, dorder + (size_t)s * B,
+                             tile_loss + (size_t)(s % kLossSteps) * nt, &ad));
+    if (s + 1 == n_steps || (s + 1) % kLossSteps == 0) {
+      const int first = s / kLossSteps * kLossSteps;
+      hipLaunchKernelGGL(k_sum_loss, dim3(s + 1 - first), dim3(256), 0, m->stream, tile_loss, nt,
+                         (double)B * (double)m->sizes[L], losses + first);
+      MLP_HIP(m, hipGetLastError());
+    }
   }
   std::vector<double> h(n_steps);
   MLP_HIP(m, hipMemcpyAsync(h.data(), losses, (size_t)n_steps * 8, hipMemcpyDeviceToHost, m->stream));
@@ -482,7 +702,7 @@ int gmco_mlp_predict(gmco_mlp* m, int B, const float* X, float* Y) {
     const int nb = std::min(m->max_batch, B - b0);
     MLP_HIP(m, hipMemcpyAsync(m->act[0], X + (size_t)b0 * m->sizes[0], (size_t)nb * m->sizes[0] * 4,
                               hipMemcpyHostToDevice, m->stream));
-    MLP_HIP(m, forward(m, nb));
+    MLP_HIP(m, forward(m, nb, m->act[0], nullptr, L, m->stream));
     MLP_HIP(m, hipMemcpyAsync(Y + (size_t)b0 * m->sizes[L], m->act[L], (size_t)nb * m->sizes[L] * 4,
                               hipMemcpyDeviceToHost, m->stream));
   }
@@ -504,10 +724,7 @@ hipError_t mlp_forward_device(gmco_mlp* m, int B, const float* X, float* Y, hipS
   const int L = layers(m);
   for (int b0 = 0; b0 < B; b0 += m->max_batch) {
     const int nb = std::min(m->max_batch, B - b0);
-    hipError_t e = hipMemcpyAsync(m->act[0], X + (size_t)b0 * m->sizes[0], (size_t)nb * m->sizes[0] * 4,
-                                  hipMemcpyDeviceToDevice, st);
-    if (e != hipSuccess) return e;
-    e = forward(m, nb, st);
+    hipError_t e = forward(m, nb, X + (size_t)b0 * m->sizes[0], nullptr, L, st);
     if (e != hipSuccess) return e;
     e = hipMemcpyAsync(Y + (size_t)b0 * m->sizes[L], m->act[L], (size_t)nb * m->sizes[L] * 4,
                        hipMemcpyDeviceToDevice, st);

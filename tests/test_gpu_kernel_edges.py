@@ -99,3 +99,59 @@ def test_dose_setup_edges(n_cath, n_dw, M, dtype):
     _, gr = O.objective_and_gradient_x(D, x, c.group, PARAMS, W)
     tol = {"f32": 2e-4, "bf16": 5e-2, "fp8": 0.25}[dtype]
     assert np.abs(g - gr).max() <= tol * np.abs(gr).max()
+
+
+# The network's products at the edges of their tiles (32 x 32, slices of 64)
+# and past six layers (the weight gradients of one launch).  BF16 operands in
+# every product: the tolerances of the network's own parity test.
+@pytest.mark.parametrize("sizes,B", [([1, 1], 1), ([33, 65, 31], 33), ([64, 32, 64], 128), ([68, 40, 277], 129),
+                                     ([9, 8, 8, 8, 8, 8, 8, 8, 5], 70)])
+def test_network_products_at_tile_edges(sizes, B):
+    from oracle import mlp_oracle as MO
+    from paper_1904_01567_amd import Network
+    announce(f"network {sizes} B={B}")
+    rng = np.random.default_rng(B)
+    p = cases.mlp_init(sizes, seed=1).astype(np.float32)
+    X = rng.uniform(0, 1, size=(B + 7, sizes[0])).astype(np.float32)
+    Y = rng.uniform(0, 2, size=(B + 7, sizes[-1])).astype(np.float32)
+    order = rng.permutation(B + 7)[:B].astype(np.int32)
+    net = Network(sizes, max_batch=B)
+    net.set_params(p)
+    L, g = net.loss_grad(X[order], Y[order])
+    Lr, gr = MO.loss_and_grad(p.astype(np.float64), sizes, X[order].astype(np.float64), Y[order].astype(np.float64))
+    assert L == pytest.approx(Lr, rel=2e-2)
+    assert np.abs(g - gr).max() <= 5e-2 * np.abs(gr).max()
+    # rows gathered by index, and the same rows laid out in order: the same step
+    got = []
+    for Xd, Yd, o in ((X, Y, order), (X[order], Y[order], np.arange(B, dtype=np.int32))):
+        net.set_params(p)
+        net.set_data(Xd, Yd)
+        loss = net.train(np.concatenate([o, o]), B, 1e-3)
+        got.append((loss, net.params()))
+    assert got[0][0] == got[1][0]
+    np.testing.assert_array_equal(got[0][1], got[1][1])
+    assert np.abs(got[0][1] - p).max() > 1e-4
+
+
+def test_network_tile_sizes_agree_bitwise():
+    # 64 x 64 tiles from 512 of them (2,048 rows x 1,100 columns), 32 x 32 below
+    from paper_1904_01567_amd import Network
+    announce("network tile sizes")
+    sizes = [70, 1100, 1030]
+    rng = np.random.default_rng(3)
+    p = cases.mlp_init(sizes, seed=2).astype(np.float32)
+    X = rng.uniform(0, 1, size=(2048, 70)).astype(np.float32)
+    out = []
+    for mb in (2048, 100):
+        net = Network(sizes, max_batch=mb)
+        net.set_params(p)
+        out.append(net.predict(X))
+    np.testing.assert_array_equal(out[0], out[1])
+    Y = rng.uniform(0, 2, size=(2048, 1030)).astype(np.float32)
+    net = Network(sizes, max_batch=2048)
+    net.set_params(p)
+    L, g = net.loss_grad(X, Y)
+    from oracle import mlp_oracle as MO
+    Lr, gr = MO.loss_and_grad(p.astype(np.float64), sizes, X.astype(np.float64), Y.astype(np.float64))
+    assert L == pytest.approx(Lr, rel=2e-2)
+    assert np.abs(g - gr).max() <= 5e-2 * np.abs(gr).max()
