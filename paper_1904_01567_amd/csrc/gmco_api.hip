@@ -26,7 +26,7 @@ struct Layout {
   size_t Wst, t0st, xst, Fst, gst;
   size_t wn, W64, x, g, dir, xt, xe, Sh, Yh, rho, ps, Gpart, Fpart, active, work, flag, slot, rt,
       split_tab;
-  size_t t64, d64, metrics, hist, feat, sel;
+  size_t d64, metrics, hist, feat, sel;
   size_t mlpX, mlpY, Fu, usewarm, nwarm;
   size_t total;
 };
@@ -244,7 +244,6 @@ Layout make_layout(const Dims& d, int G, int m, int dtype, int Pmax) {
   L.split_tab = take((size_t)2 * (d.ntiles + 1) * 4);
   L.active = take(2 * sizeof(int));
   L.work = take(2 * sizeof(unsigned long long));
-  L.t64 = take(PK * 8);
   // final doses (Pp x Mp, then Pp x Mdp for the DVH points); an FP8 context
   // also widens its matrix (Mp x Kp) here
   L.d64 = take(std::max((size_t)d.Pp * std::max(d.Mp, d.Mdp),
@@ -1410,8 +1409,8 @@ int compute_metrics(gmco_ctx* c) {
   m.volume_cc = c->at<double>(L.volume);
   m.rx = c->rx;
   m.out = c->at<gmco_plan_metrics>(L.metrics);
-  GMCO_HIP(c, launch_export_t(c->at<float>(L.x), d.Pp, d.K, d.Kp, c->at<double>(L.t64), d.Kp, c->stream));
-  GMCO_HIP(c, launch_dose64(c->at<double>(L.D64), c->at<double>(L.t64), d.Mp, d.Kp, d.Pp, c->at<double>(L.d64), c->stream));
+  const float* x = c->at<float>(L.x);
+  GMCO_HIP(c, launch_dose64(c->at<double>(L.D64), x, d.Mp, d.K, d.Kp, c->P, c->at<double>(L.d64), c->stream));
   m.d64 = c->at<double>(L.d64);
   m.ld = d.Mp;
   m.off = c->at<int>(L.goff);
@@ -1420,8 +1419,8 @@ int compute_metrics(gmco_ctx* c) {
   m.dvh = dvh ? 0 : 1;
   GMCO_HIP(c, launch_metrics(m, c->stream));
   if (dvh) {
-    GMCO_HIP(c, launch_dose64(c->at<double>(L.D64d), c->at<double>(L.t64), d.Mdp, d.Kp, d.Pp,
-                              c->at<double>(L.d64), c->stream));
+    GMCO_HIP(c, launch_dose64(c->at<double>(L.D64d), x, d.Mdp, d.K, d.Kp, c->P, c->at<double>(L.d64),
+                              c->stream));
     m.ld = d.Mdp;
     m.off = c->at<int>(L.doff);
     m.cnt = c->at<int>(L.dcnt);

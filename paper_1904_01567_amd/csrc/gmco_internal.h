@@ -193,8 +193,9 @@ hipError_t launch_export_t(const float* x, int P, int K, int Kp, double* t64, in
                            hipStream_t st);
 hipError_t launch_x_to_device(const double* x_host_dev, int P, int Pp, int K, int Kp, float* xe,
                               hipStream_t st);
-hipError_t launch_dose64(const double* D64, const double* t64, int Mp, int Kp, int Pp,
-                         double* d64, hipStream_t st);
+// FP64 doses d64 (P rows of stride Mp) of the first P plans at t = x^2
+hipError_t launch_dose64(const double* D64, const float* x, int Mp, int K, int Kp, int P, double* d64,
+                         hipStream_t st);
 // One pass of the per-organ metrics over the doses d64 (P rows of stride ld)
 // of a point set whose organ o is the range off[o] .. off[o] + cnt[o]:
 // objective != 0 adds the individual objectives (eq. 1 with each point's

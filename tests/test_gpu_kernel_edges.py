@@ -155,3 +155,58 @@ def test_network_tile_sizes_agree_bitwise():
     Lr, gr = MO.loss_and_grad(p.astype(np.float64), sizes, X.astype(np.float64), Y.astype(np.float64))
     assert L == pytest.approx(Lr, rel=2e-2)
     assert np.abs(g - gr).max() <= 5e-2 * np.abs(gr).max()
+
+
+def _check_metrics(pl, D, t, c, W, params=PARAMS):
+    m = pl.metrics()
+    mref = O.plan_metrics(D, t, c.group, params, W, c.volume_cc, 15.0)
+    for p, q in enumerate(mref):
+        assert m["F64"][p] == pytest.approx(q["F"], rel=1e-12, abs=1e-300)
+        np.testing.assert_allclose(m["f_organ"][p], q["f_organ"], rtol=1e-12, atol=1e-300)
+        np.testing.assert_array_equal(m["V100_pct"][p], q["V100_pct"])
+        np.testing.assert_array_equal(m["V75_cc"][p], q["V75_cc"])
+        np.testing.assert_allclose(m["D10_pct"][p], q["D10_pct"], rtol=1e-13)
+        np.testing.assert_allclose(m["D90_pct"][p], q["D90_pct"], rtol=1e-13)
+    best, cls, nd, frac = pl.select_plan()
+    np.testing.assert_array_equal(cls, [O.plan_class(q) for q in mref])
+    np.testing.assert_array_equal(nd, O.nondominated(np.array([q["f_organ"] for q in mref])))
+    assert best == O.select_plan(mref)
+    assert frac == pytest.approx(nd.mean())
+
+
+# FP64 doses in tiles of 16, 32 and 64 plans and steps of 16 dwells; the
+# tolerances of the metrics' parity test (FP64 sums in another order).
+@pytest.mark.parametrize("P", [1, 16, 17, 32, 33, 64, 65])
+@pytest.mark.parametrize("n_cath,n_dw,M", [(1, 5, 40), (3, 16, 129), (5, 7, 1007)])
+def test_metrics_tile_edges(P, n_cath, n_dw, M):
+    announce(f"metrics P={P} K={n_cath * n_dw} M={M}")
+    c = _case(n_cath, n_dw, M)
+    D = O.dose_rate_matrix(c.dwell_xyz, c.pt_xyz)
+    W = cases.hidden_weights(P, seed=P)
+    t0 = O.uniform_start_time(D, c.group, 15.0) * (0.1 + 1.9 * cases.uniform_draws((P, c.K), seed=303))
+    pl = planner(c, W, t0=t0)
+    x = np.sqrt(t0).astype(np.float32).astype(np.float64)
+    _check_metrics(pl, D, x * x, c, W)
+
+
+# D10 / D90 by histogram and ranking; bins of more than 1,024 doses by the
+# radix select: an organ of equal doses, one of two values around the rank, and
+# doses far outside the histogram's 2^-4 .. 2^12 Gy, where its end bins hold all.
+@pytest.mark.parametrize("scale", [1.0, 1e-6, 1e6])
+def test_metrics_of_equal_and_extreme_doses(scale):
+    announce(f"metrics of equal doses x {scale}")
+    from paper_1904_01567_amd import Planner
+    c = _case(3, 5, 10000)
+    rng = np.random.default_rng(8)
+    D = np.empty((c.M, c.K))
+    D[c.group == 0] = 1.0                                            # one dose
+    two = rng.uniform(size=(c.group == 1).sum()) < 0.1               # two doses
+    D[c.group == 1] = np.where(two, 2.0, 1.0)[:, None]
+    D[c.group >= 2] = rng.uniform(0.5, 2.0, size=((c.group >= 2).sum(), 1))
+    D *= scale
+    W = cases.hidden_weights(3, seed=2)
+    t0 = np.full((3, c.K), 1.0) * np.array([[1.0], [4.0], [0.25]])   # exact square roots
+    pl = Planner(max_plans=3)
+    pl.load_case(c.dwell_xyz, None, c.group, PARAMS, c.volume_cc, 15.0, 0, dose_rate=D)
+    pl.set_weights(W, t0)
+    _check_metrics(pl, D, t0, c, W)
