@@ -112,7 +112,6 @@ struct gmco_ctx {
   hipEvent_t ev0 = nullptr, ev1 = nullptr;
   hipStream_t gstream = nullptr;  // library-owned stream for graph capture
   hipEvent_t gev = nullptr;
-  GroupTable gt{};
 
   template <class T>
   T* at(size_t off) const {
@@ -284,6 +283,7 @@ EvalArgs eval_args(const gmco_ctx* c, const float* x, bool compacted, int dtype)
   a.grp = c->at<int>(c->lay.grp);
   a.x = x;
   a.wn = c->at<float>(c->lay.wn);
+  a.P = c->P;
   const Dims& d = c->dim;
   const bool lp = is_low_precision(dtype);
   const int units = eval_units(d, dtype);
@@ -293,7 +293,6 @@ EvalArgs eval_args(const gmco_ctx* c, const float* x, bool compacted, int dtype)
     a.slot = c->at<int>(c->lay.slot);
     a.rt = c->at<RoundTable>(c->lay.rt);
     a.work = c->at<unsigned long long>(c->lay.work);
-    a.P = c->P;
     a.s_tuned = lp ? d.S_tuned_lp : d.S_tuned;
   }
   a.Gpart = c->at<float>(c->lay.Gpart);
@@ -310,7 +309,7 @@ EvalArgs eval_args(const gmco_ctx* c, const float* x, bool compacted, int dtype)
   a.lp_shape = eval_shape(d, dtype);
   a.xcd_map = lp ? d.xcd_lp : d.xcd32;
   a.last16 = d.K > d.Kp - 16 ? 1 : 0;
-  a.gt = c->gt;
+  a.gparams = c->at<double>(c->lay.gparams);
   return a;
 }
 
@@ -603,12 +602,6 @@ int gmco_load_case(gmco_ctx* c, const gmco_case* cs) {
   std::vector<int> split_tab(d.split16);
   split_tab.insert(split_tab.end(), d.split32.begin(), d.split32.end());
   if ((rc = copy_h2d(c, c->at<void>(L.split_tab), split_tab.data(), split_tab.size() * 4))) return rc;
-  for (int j = 0; j <= kGmax; ++j) {
-    for (int k = 0; k < 4; ++k) c->gt.prm64[j][k] = j < G ? gp[4 * j + k] : 0.0;
-    c->gt.prm[j] = make_float4((float)c->gt.prm64[j][0], (float)c->gt.prm64[j][1],
-                               (float)c->gt.prm64[j][2], (float)c->gt.prm64[j][3]);
-  }
-
   // (the doses' array is free until the metrics: scratch of the row sums and column maxima)
   const int r0 = c->offsets[cs->target_group];
   GMCO_HIP(c, launch_dose_setup(st_dw, cs->point_xyz ? st_pt : nullptr, cs->dose_rate ? st_D : nullptr,

@@ -70,13 +70,6 @@ struct PlanState {
 };
 static_assert(sizeof(PlanState) == 64, "PlanState layout");
 
-// Eq. 1 parameters per structure: (w_min, D_min, D_max, w_max); entry kGmax
-// is the all-zero row used by padding points.
-struct GroupTable {
-  float4 prm[kGmax + 1];
-  double prm64[kGmax + 1][4];
-};
-
 // Per-round shape of the compacted evaluation, written by the evaluation
 // kernel: the running plans occupy compact columns 0..nact-1, which form
 // ntiles tiles of kPT; every tile is split S ways over the points.
@@ -125,7 +118,7 @@ struct EvalArgs {
   int xcd_map;            // 1: tiles of one point range on one XCD when the grid allows
   int last16;             // 0: dwells Kp - 16 .. Kp - 1 are all padding (FP32-operand
                           // kernels skip that 16-dwell slice: its products are zero)
-  GroupTable gt;
+  const double* gparams;  // [kGmax][4] eq. 1 row per structure: (w_min, D_min, D_max, w_max)
 };
 
 struct UpdateArgs {

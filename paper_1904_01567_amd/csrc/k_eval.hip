@@ -65,38 +65,68 @@ __device__ inline void split_tile(int bid, int S, int ntiles, int xcd_map, int& 
   }
 }
 
-// Resolves the evaluation's shape (split count S, tile count, row stride of
-// the partial buffers), workgroup bid's (split, first compact column j0) and
-// the plan behind each of its TPW * kPT columns (-1: empty), and stages the
-// columns' structure weights.  In a compacted round every workgroup ranks
-// the running plans itself (a block-wide scan of the flags), so no separate
-// launch is needed.  Returns false, for the whole workgroup, when the grid
-// is larger than this round's S * (units of NCOL columns).  A workgroup
-// covers NCOL consecutive columns: TPW whole plan tiles (NCOL = TPW kPT) or
-// half a tile (NCOL = kPT / 2).  Columns at or past `stride` (the second tile
-// of the last workgroup when ntiles is odd) are empty and have no partials.
+// The eq. 1 rows (w_min, D_min, D_max, w_max) of the groups, and the all-zero
+// row of the padding points, in LDS.
+template <int NT, class T>
+__device__ inline void stage_params(const EvalArgs& a, T* sP) {
+  for (int i = threadIdx.x; i < 4 * (kGmax + 1); i += NT) sP[i] = i < 4 * kGmax ? (T)a.gparams[i] : (T)0;
+}
+
+// A workgroup's place in the evaluation: split s of S, row stride of the
+// partial buffers, first compact column j0 and its columns that hold a plan
+// (the first nval; the rest are empty and have no partials).
+struct Tile {
+  int s, S, stride, j0, nval;
+};
+
+// Resolves workgroup bid's Tile and the plan behind each of its NCOL columns
+// (-1: empty).  In a compacted round every workgroup ranks the running plans
+// itself (a block-wide scan of the flags), so no separate launch is needed.
+// Returns false, for the whole workgroup, when the grid is larger than this
+// round's S * (units of NCOL columns); ends with a barrier otherwise.  A
+// workgroup covers NCOL consecutive columns: whole plan tiles (a multiple of
+// kPT) or half a tile (NCOL = kPT / 2).
+// A short launch waits mostly for chains of dependent loads, so the flags (a
+// thread's plans at once, kept as bits for the ranking) and the split table are
+// loaded together.
 template <int NT, int NCOL = kPT>
-__device__ inline bool tile_setup(const EvalArgs& a, int bid, int* sPlan, int* sScan, float* sW, int& s,
-                                  int& S, int& stride, int& j0) {
+__device__ inline bool tile_setup(const EvalArgs& a, int bid, int* sPlan, int* sScan, Tile& t) {
   static_assert(NCOL % 16 == 0 && (NCOL % kPT == 0 || kPT % NCOL == 0), "whole 16-plan groups");
+  constexpr int kTab = 64;  // split counts kept in LDS (4,032 plans; past it they are read when known)
+  __shared__ int sTab[kTab];
   const int tid = threadIdx.x;
   const int lane = tid & 63, wave = tid >> 6;
   int unit;
   if (a.flag == nullptr) {
-    S = a.S;
-    stride = a.Pp;
+    t.S = a.S;
+    t.stride = a.Pp;
     const int units = (a.ntiles * kPT + NCOL - 1) / NCOL;
-    if (bid >= S * units) return false;
-    split_tile(bid, S, units, a.xcd_map, s, unit);
-    j0 = unit * NCOL;
-    for (int i = tid; i < NCOL; i += NT) sPlan[i] = j0 + i < a.Pp ? j0 + i : -1;
+    if (bid >= t.S * units) return false;
+    split_tile(bid, t.S, units, a.xcd_map, t.s, unit);
+    t.j0 = unit * NCOL;
+    t.nval = min(a.P - t.j0, NCOL);
+    if (t.nval <= 0) return false;  // (capacity past the batch)
+    for (int i = tid; i < NCOL; i += NT) sPlan[i] = i < t.nval ? t.j0 + i : -1;
   } else {
-    for (int i = tid; i < NCOL; i += NT) sPlan[i] = -1;
+    constexpr int kBits = 64;  // plans per thread whose flags stay in registers
     const int per = (a.P + NT - 1) / NT;
     const int b = tid * per;
     const int e = min(b + per, a.P);
+    if (tid < kTab && tid <= a.ntiles) sTab[tid] = a.split_tab[tid];
+    unsigned long long bits = 0;
     int cnt = 0;
-    for (int p = b; p < e; ++p) cnt += a.flag[p];
+    if (per <= kBits) {
+      for (int i = 0; i < per; i += 8) {
+        int f[8];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) f[u] = (i + u < per && b + i + u < e) ? a.flag[b + i + u] : 0;
+#pragma unroll
+        for (int u = 0; u < 8; ++u) bits |= (unsigned long long)(f[u] != 0) << (i + u);
+      }
+      cnt = __popcll(bits);
+    } else {
+      for (int p = b; p < e; ++p) cnt += a.flag[p];
+    }
     int v = cnt;  // inclusive scan over the wavefront, then over the waves
 #pragma unroll
     for (int o = 1; o < 64; o <<= 1) {
@@ -104,48 +134,61 @@ __device__ inline bool tile_setup(const EvalArgs& a, int bid, int* sPlan, int* s
       if (lane >= o) v += u;
     }
     if (lane == 63) sScan[wave] = v;
+    for (int i = tid; i < NCOL; i += NT) sPlan[i] = -1;
     __syncthreads();
     int base = 0, nact = 0;
 #pragma unroll
     for (int w = 0; w < NT / 64; ++w) {
-      const int t = sScan[w];
-      base += w < wave ? t : 0;
-      nact += t;
+      const int c = sScan[w];
+      base += w < wave ? c : 0;
+      nact += c;
     }
     const int ntiles = (nact + kPT - 1) / kPT;
-    S = (a.s_tuned > 0 && ntiles == a.ntiles) ? a.s_tuned : a.split_tab[ntiles];
-    stride = ntiles * kPT;
+    t.S = (a.s_tuned > 0 && ntiles == a.ntiles) ? a.s_tuned : (ntiles < kTab ? sTab[ntiles] : a.split_tab[ntiles]);
+    t.stride = ntiles * kPT;
     if (bid == 0 && tid == 0) {
       RoundTable r;
       r.nact = nact;
       r.ntiles = ntiles;
-      r.S = S;
+      r.S = t.S;
       r.pad = 0;
       *a.rt = r;
       if (a.work != nullptr) *a.work += (unsigned long long)nact;
       if (a.work2 != nullptr) *a.work2 += (unsigned long long)nact;
     }
     const int units = (ntiles * kPT + NCOL - 1) / NCOL;
-    if (bid >= S * units) return false;
-    split_tile(bid, S, units, a.xcd_map, s, unit);
-    j0 = unit * NCOL;
+    if (bid >= t.S * units) return false;
+    split_tile(bid, t.S, units, a.xcd_map, t.s, unit);
+    t.j0 = unit * NCOL;
+    t.nval = min(nact - t.j0, NCOL);
+    if (t.nval <= 0) return false;  // (the empty half of the last tile)
     int r = base + v - cnt;
-    for (int p = b; p < e; ++p) {
-      if (a.flag[p]) {
-        if (r >= j0 && r < j0 + NCOL) {
-          sPlan[r - j0] = p;
-          if (s == 0) a.slot[p] = r;
-        }
-        ++r;
+    auto place = [&](int p) {
+      if (r >= t.j0 && r < t.j0 + NCOL) {
+        sPlan[r - t.j0] = p;
+        if (t.s == 0) a.slot[p] = r;
       }
+      ++r;
+    };
+    if (per <= kBits) {
+      for (; bits; bits &= bits - 1) place(b + __ffsll(bits) - 1);
+    } else {
+      for (int p = b; p < e; ++p)
+        if (a.flag[p]) place(p);
     }
   }
   __syncthreads();
-  for (int i = tid; i < NCOL * kGmax; i += NT) {
+  return true;
+}
+
+// Structure weights of the workgroup's columns (zero for empty ones), staged
+// after the loads of D and x have been issued.
+template <int NT, int NCOL = kPT>
+__device__ inline void stage_weights(const EvalArgs& a, const int* sPlan, float* sW) {
+  for (int i = threadIdx.x; i < NCOL * kGmax; i += NT) {
     const int pl = sPlan[i / kGmax];
     sW[i] = pl >= 0 ? a.wn[(size_t)pl * kGmax + (i % kGmax)] : 0.f;
   }
-  return true;
 }
 
 // float4-chunk swizzle of row `row` of the FP64-accumulating kernel's LDS tile
@@ -183,15 +226,12 @@ __device__ inline void eval_f32(const EvalArgs& a, int bid) {
   const int q = lane >> 4;
   const int n = lane & 15;
 
-  int s, S, stride, j0;
-  if (!tile_setup<256>(a, bid, sPlan, sScan, sW, s, S, stride, j0)) return;
-#pragma unroll
-  for (int j = 0; j <= kGmax; ++j)
-    if (tid == j) {
-      sP[j] = a.gt.prm[j];
-#pragma unroll
-      for (int c = 0; c < 4; ++c) sP64[j][c] = a.gt.prm64[j][c];
-    }
+  Tile t;
+  if (!tile_setup<256>(a, bid, sPlan, sScan, t)) return;
+  const int s = t.s, S = t.S, stride = t.stride, j0 = t.j0;
+  stage_weights<256>(a, sPlan, sW);
+  if constexpr (MODE == MODE_CHUNK64) stage_params<256>(a, &sP64[0][0]);
+  else stage_params<256>(a, &sP[0].x);
 
   const int col = wave * 16 + n;
   const int plan = sPlan[col];
@@ -335,15 +375,16 @@ __device__ inline void eval_f32(const EvalArgs& a, int bid) {
 #undef GMCO_PREFETCH
 #undef GMCO_STAGE
 
-  // ---- write split partials ----
+  // ---- write split partials (an empty column has none) ----
+  facc += __shfl_xor(facc, 16);
+  facc += __shfl_xor(facc, 32);
+  if (!pv) return;
   float* __restrict__ gout = a.Gpart + ((size_t)s * stride + j0 + col) * KP;
 #pragma unroll
   for (int k = 0; k < NK16; ++k) {
     *reinterpret_cast<float4*>(gout + 16 * k + 4 * q) =
         make_float4(gacc[k][0], gacc[k][1], gacc[k][2], gacc[k][3]);
   }
-  facc += __shfl_xor(facc, 16);
-  facc += __shfl_xor(facc, 32);
   if (q == 0) a.Fpart[(size_t)s * stride + j0 + col] = facc;
 }
 
@@ -383,11 +424,9 @@ __device__ inline void eval_f32_ws(const EvalArgs& a, int bid) {
   const int grp = wave & 3;
   const int nk_used = a.last16 ? NK16 : NK16 - 1;  // the all-padding slice adds zero products
 
-  int s, S, stride, j0;
-  if (!tile_setup<NT, kPT>(a, bid, sPlan, sScan, sW, s, S, stride, j0)) return;
-#pragma unroll
-  for (int j = 0; j <= kGmax; ++j)
-    if (tid == j) sP[j] = a.gt.prm[j];
+  Tile t;
+  if (!tile_setup<NT, kPT>(a, bid, sPlan, sScan, t)) return;
+  const int s = t.s, S = t.S, stride = t.stride, j0 = t.j0;
   const int col = grp * 16 + n;
   const int b_begin = (int)(((long long)s * a.nblocks) / S);
   const int b_end = (int)(((long long)(s + 1) * a.nblocks) / S);
@@ -411,6 +450,8 @@ __device__ inline void eval_f32_ws(const EvalArgs& a, int bid) {
       tf[4 * k + 3] = pv ? xv.w * xv.w : 0.f;
     }
     double facc = 0.0;
+    stage_weights<NTS>(a, sPlan, sW);
+    stage_params<NTS>(a, &sP[0].x);
     __syncthreads();
     for (int i = 0; i <= nblk; ++i) {
       if (i < nblk) {
@@ -443,7 +484,7 @@ __device__ inline void eval_f32_ws(const EvalArgs& a, int bid) {
     }
     facc += __shfl_xor(facc, 16);
     facc += __shfl_xor(facc, 32);
-    if (q == 0) a.Fpart[(size_t)s * stride + j0 + col] = facc;
+    if (q == 0 && pv) a.Fpart[(size_t)s * stride + j0 + col] = facc;
   } else {
     const int st = tid - NTS;
     const f4v* __restrict__ Dg = reinterpret_cast<const f4v*>(a.D);
@@ -498,6 +539,7 @@ __device__ inline void eval_f32_ws(const EvalArgs& a, int bid) {
       }
       __syncthreads();
     }
+    if (sPlan[col] < 0) return;  // an empty column has no partials
     float* __restrict__ gout = a.Gpart + ((size_t)s * stride + j0 + col) * KP;
 #pragma unroll
     for (int k = 0; k < NK16; ++k)
@@ -567,14 +609,24 @@ __device__ inline void eval_acc64(const EvalArgs& a, int bid) {
   // Kp - K >= 16: its products are zero, so the wave skips it (a scalar branch)
   const bool skip_last = __builtin_amdgcn_readfirstlane(half) == NH - 1 && !a.last16;
 
-  int s, S, stride, j0;
-  if (!tile_setup<NT, NCOL>(a, bid, sPlan, sScan, sW, s, S, stride, j0)) return;
-#pragma unroll
-  for (int j = 0; j <= kGmax; ++j)
-    if (tid == j) {
-#pragma unroll
-      for (int c = 0; c < 4; ++c) sP64[j][c] = a.gt.prm64[j][c];
-    }
+  Tile t;
+  if (!tile_setup<NT, NCOL>(a, bid, sPlan, sScan, t)) return;
+  const int s = t.s, S = t.S, stride = t.stride, j0 = t.j0;
+  const int b_begin = (int)(((long long)s * a.nblocks) / S);
+  const int b_end = (int)(((long long)(s + 1) * a.nblocks) / S);
+  const f4v* __restrict__ Dg = reinterpret_cast<const f4v*>(a.D);
+  f4v pf[NPF];
+  int gpre = 0;
+#define GMCO_PF64(blk)                                                      \
+  {                                                                         \
+    const f4v* src_ = Dg + (size_t)(blk) * NF4;                             \
+    _Pragma("unroll") for (int i_ = 0; i_ < NPF; ++i_) {                    \
+      const int idx = tid + NT * i_;                                        \
+      if (NF4 % NT == 0 || idx < NF4) pf[i_] = src_[idx];                   \
+    }                                                                       \
+    if (tid < kBM) gpre = a.grp[(blk) * kBM + tid];                         \
+  }
+  if (b_begin < b_end) GMCO_PF64(b_begin);
 
   const int col = grp * 16 + n;
   const int plan = sPlan[col];
@@ -595,21 +647,6 @@ __device__ inline void eval_acc64(const EvalArgs& a, int bid) {
   for (int k = 0; k < NKH; ++k) gacc[k] = f4v{0.f, 0.f, 0.f, 0.f};
   double facc = 0.0;
 
-  const int b_begin = (int)(((long long)s * a.nblocks) / S);
-  const int b_end = (int)(((long long)(s + 1) * a.nblocks) / S);
-  const f4v* __restrict__ Dg = reinterpret_cast<const f4v*>(a.D);
-
-  f4v pf[NPF];
-  int gpre = 0;
-#define GMCO_PF64(blk)                                                      \
-  {                                                                         \
-    const f4v* src_ = Dg + (size_t)(blk) * NF4;                             \
-    _Pragma("unroll") for (int i_ = 0; i_ < NPF; ++i_) {                    \
-      const int idx = tid + NT * i_;                                        \
-      if (NF4 % NT == 0 || idx < NF4) pf[i_] = src_[idx];                   \
-    }                                                                       \
-    if (tid < kBM) gpre = a.grp[(blk) * kBM + tid];                         \
-  }
 #define GMCO_ST64(buf)                                                      \
   {                                                                         \
     const int buf_ = (buf);                                                 \
@@ -624,20 +661,31 @@ __device__ inline void eval_acc64(const EvalArgs& a, int bid) {
     if (tid < kBM) sG[buf_][tid] = gpre;                                    \
   }
 
-  for (int i = tid; i < kBM * KS; i += NT) sD[1][i] = 0.f;
+  stage_weights<NT, NCOL>(a, sPlan, sW);
+  stage_params<NT>(a, &sP64[0][0]);
   for (int i = tid; i < NG * 4 * 64; i += NT) (&sPhi[0][0][0])[i] = 0.f;
-  if (b_begin < b_end) GMCO_PF64(b_begin);
+  // back-projection of the block in buffer Dp with phi of its points, skipped
+  // when phi is zero for all 16 points and 16 plans of the wave
+  auto back_project = [&](const float* __restrict__ Dp, const float (&phi)[4]) {
+    if (wave_any_nonzero(phi)) {
+#pragma unroll
+      for (int k = 0; k < NKH; ++k) {
+        if (k == NKH - 1 && skip_last) continue;
+        const int kg = half * NKH + k;
+#pragma unroll
+        for (int r = 0; r < 4; ++r)
+          gacc[k] = mfma_f32(Dp[(q + 4 * r) * KS + 16 * kg + (n ^ (swz_row(q + 4 * r) << 2))], phi[r], gacc[k]);
+      }
+    }
+  };
 #pragma unroll 1
-  for (int b = b_begin; b <= b_end; ++b) {
+  for (int b = b_begin; b < b_end; ++b) {
     const int cur = (b - b_begin) & 1;
     const int prv = cur ^ 1;
-    // As in the 256-thread kernel: the first iteration back-projects
-    // phi_prev = 0 over a zeroed buffer and the last repeats a dose product
-    // whose result is discarded.
-    const bool have_cur = b < b_end;
+    // (the first iteration back-projects phi_prev = 0, i.e. nothing)
     // Buffer `cur` was last read by the previous iteration's matrix loop,
     // which every wave finished before that iteration's second barrier.
-    if (have_cur) GMCO_ST64(cur);
+    GMCO_ST64(cur);
     __syncthreads();
     if (b + 1 < b_end) GMCO_PF64(b + 1);
 
@@ -676,17 +724,7 @@ __device__ inline void eval_acc64(const EvalArgs& a, int bid) {
         acc3 = mfma_f64(av.w, tf[4 * k + 3], acc3);
       }
     }
-    if (wave_any_nonzero(phi_prev)) {
-#pragma unroll
-      for (int k = 0; k < NKH; ++k) {
-        if (k == NKH - 1 && skip_last) continue;
-        const int kg = half * NKH + k;
-#pragma unroll
-        for (int r = 0; r < 4; ++r)
-          gacc[k] = mfma_f32(Dp[(q + 4 * r) * KS + 16 * kg + (n ^ (swz_row(q + 4 * r) << 2))],
-                             phi_prev[r], gacc[k]);
-      }
-    }
+    back_project(Dp, phi_prev);
     // partial dose of points q + 4 r (the FP64 op's rows) for plan n
 #pragma unroll
     for (int r = 0; r < 4; ++r) sX[half][grp][r][lane] = (acc0[r] + acc1[r]) + (acc2[r] + acc3[r]);
@@ -694,33 +732,41 @@ __device__ inline void eval_acc64(const EvalArgs& a, int bid) {
     // eq. 1 on the summed dose: each wave of the group takes 4 / NH of the
     // four rows (points q + 4r) and shares phi through LDS; the next
     // iteration's first barrier orders these writes before their reads
-    if (have_cur) {
 #pragma unroll
-      for (int rr = 0; rr < RPW; ++rr) {
-        const int r = RPW * half + rr;
-        double d = sX[0][grp][r][lane] + sX[1][grp][r][lane];
+    for (int rr = 0; rr < RPW; ++rr) {
+      const int r = RPW * half + rr;
+      double d = sX[0][grp][r][lane] + sX[1][grp][r][lane];
 #pragma unroll
-        for (int h = 2; h < NH; ++h) d += sX[h][grp][r][lane];
-        const int gi = sG[cur][q + 4 * r];
-        const float w = (gi < kGmax) ? sW[col * kGmax + gi] : 0.f;
-        // without branches: at most one of the two deviations is nonzero
-        const double lo = fmin(d - sP64[gi][1], 0.0);
-        const double hi = fmax(d - sP64[gi][2], 0.0);
-        const double kap = sP64[gi][0] * lo + sP64[gi][3] * hi;
-        facc += (double)w * (kap * (lo + hi));
-        sPhi[grp][r][lane] = (float)((double)w * kap);
-      }
+      for (int h = 2; h < NH; ++h) d += sX[h][grp][r][lane];
+      const int gi = sG[cur][q + 4 * r];
+      const float w = (gi < kGmax) ? sW[col * kGmax + gi] : 0.f;
+      // without branches: at most one of the two deviations is nonzero
+      const double lo = fmin(d - sP64[gi][1], 0.0);
+      const double hi = fmax(d - sP64[gi][2], 0.0);
+      const double kap = sP64[gi][0] * lo + sP64[gi][3] * hi;
+      facc += (double)w * (kap * (lo + hi));
+      sPhi[grp][r][lane] = (float)((double)w * kap);
     }
+  }
+  if (b_begin < b_end) {  // the last block's back-projection
+    __syncthreads();
+    float phi_last[4];
+#pragma unroll
+    for (int r = 0; r < 4; ++r) phi_last[r] = sPhi[grp][r][lane];
+    back_project(sD[(b_end - 1 - b_begin) & 1], phi_last);
   }
 #undef GMCO_PF64
 #undef GMCO_ST64
 
-  // ---- split partials: each wave its dwell part; F from one wave per group ----
-  float* __restrict__ gout = a.Gpart + ((size_t)s * stride + j0 + col) * KP + half * (KP / NH);
+  // ---- split partials: each wave its dwell part; F from one wave per group;
+  // an empty column has none ----
+  if (pv) {
+    float* __restrict__ gout = a.Gpart + ((size_t)s * stride + j0 + col) * KP + half * (KP / NH);
 #pragma unroll
-  for (int k = 0; k < NKH; ++k) {
-    *reinterpret_cast<float4*>(gout + 16 * k + 4 * q) =
-        make_float4(gacc[k][0], gacc[k][1], gacc[k][2], gacc[k][3]);
+    for (int k = 0; k < NKH; ++k) {
+      *reinterpret_cast<float4*>(gout + 16 * k + 4 * q) =
+          make_float4(gacc[k][0], gacc[k][1], gacc[k][2], gacc[k][3]);
+    }
   }
   // F partial: the rows of part 0, then those of parts 1.. in order, then over q
   if (half > 0) sF[half - 1][grp][lane] = facc;
@@ -730,7 +776,7 @@ __device__ inline void eval_acc64(const EvalArgs& a, int bid) {
     for (int h = 1; h < NH; ++h) facc += sF[h - 1][grp][lane];
     facc += __shfl_xor(facc, 16);
     facc += __shfl_xor(facc, 32);
-    if (q == 0) a.Fpart[(size_t)s * stride + j0 + col] = facc;
+    if (q == 0 && pv) a.Fpart[(size_t)s * stride + j0 + col] = facc;
   }
 }
 
@@ -775,14 +821,9 @@ __device__ inline void eval_acc64_ws(const EvalArgs& a, int bid) {
   // are zero, so both roles skip it
   const int nk_used = a.last16 ? NK : NK - 1;
 
-  int s, S, stride, j0;
-  if (!tile_setup<NT, NCOL>(a, bid, sPlan, sScan, sW, s, S, stride, j0)) return;
-#pragma unroll
-  for (int j = 0; j <= kGmax; ++j)
-    if (tid == j) {
-#pragma unroll
-      for (int c = 0; c < 4; ++c) sP64[j][c] = a.gt.prm64[j][c];
-    }
+  Tile t;
+  if (!tile_setup<NT, NCOL>(a, bid, sPlan, sScan, t)) return;
+  const int s = t.s, S = t.S, stride = t.stride, j0 = t.j0;
   const int col = grp * 16 + n;
   const int b_begin = (int)(((long long)s * a.nblocks) / S);
   const int b_end = (int)(((long long)(s + 1) * a.nblocks) / S);
@@ -809,6 +850,8 @@ __device__ inline void eval_acc64_ws(const EvalArgs& a, int bid) {
       tf[4 * k + 3] = pv ? xv.w * xv.w : 0.f;
     }
     double facc0 = 0.0, facc1 = 0.0;  // rows 0-1 and 2-3, as the two waves of shape 0
+    stage_weights<NTS, NCOL>(a, sPlan, sW);
+    stage_params<NTS>(a, &sP64[0][0]);
     __syncthreads();
     for (int i = 0; i <= nblk; ++i) {
       if (i < nblk) {
@@ -854,7 +897,7 @@ __device__ inline void eval_acc64_ws(const EvalArgs& a, int bid) {
     double facc = facc0 + facc1;
     facc += __shfl_xor(facc, 16);
     facc += __shfl_xor(facc, 32);
-    if (q == 0) a.Fpart[(size_t)s * stride + j0 + col] = facc;
+    if (q == 0 && pv) a.Fpart[(size_t)s * stride + j0 + col] = facc;
   } else {
     const int st = tid - NTS;
     const f4v* __restrict__ Dg = reinterpret_cast<const f4v*>(a.D);
@@ -912,6 +955,7 @@ __device__ inline void eval_acc64_ws(const EvalArgs& a, int bid) {
       }
       __syncthreads();
     }
+    if (sPlan[col] < 0) return;  // an empty column has no partials
     float* __restrict__ gout = a.Gpart + ((size_t)s * stride + j0 + col) * KP;
 #pragma unroll
     for (int k = 0; k < NK; ++k)
@@ -1142,12 +1186,11 @@ __device__ inline void eval_lp(const EvalArgs& a, int bid) {
   const int lane = tid & 63;
   const int q = lane >> 4;
   const int n = lane & 15;
-  if (tid == 0) {  // constant indices: the table is read straight from the kernel arguments
-#pragma unroll
-    for (int j = 0; j <= kGmax; ++j) sP[j] = a.gt.prm[j];
-  }
-  int s, S, stride, j0;  // (tile_setup ends with a barrier)
-  if (!tile_setup<NT, NCOL>(a, bid, sPlan, sScan, sW, s, S, stride, j0)) return;
+  Tile t;  // (tile_setup ends with a barrier)
+  if (!tile_setup<NT, NCOL>(a, bid, sPlan, sScan, t)) return;
+  const int s = t.s, S = t.S, stride = t.stride, j0 = t.j0;
+  stage_weights<NT, NCOL>(a, sPlan, sW);
+  stage_params<NT>(a, &sP[0].x);
 
   // B operands of the dose product, t = x^2 at dwells 32 k + 8 q + e, for
   // the plans of columns 16 (NH wave + h) + n (an empty column evaluates t = 0
@@ -1295,7 +1338,7 @@ __device__ inline void eval_lp(const EvalArgs& a, int bid) {
     double f = facc[h];
     f += __shfl_xor(f, 16);
     f += __shfl_xor(f, 32);
-    if (j0 + col - n < stride) {  // the same for the whole wavefront
+    if (sPlan[col] >= 0) {  // an empty column has no partials
       float* __restrict__ gout = a.Gpart + ((size_t)s * stride + j0 + col) * KP;
 #pragma unroll
       for (int k = 0; k < NK16; ++k) {
@@ -1353,12 +1396,11 @@ __device__ inline void eval_lp_ws(const EvalArgs& a, int bid) {
   const int lane = tid & 63;
   const int q = lane >> 4;
   const int n = lane & 15;
-  if (tid == 0) {
-#pragma unroll
-    for (int j = 0; j <= kGmax; ++j) sP[j] = a.gt.prm[j];
-  }
-  int s, S, stride, j0;  // (tile_setup ends with a barrier)
-  if (!tile_setup<NT, NCOL>(a, bid, sPlan, sScan, sW, s, S, stride, j0)) return;
+  Tile t;  // (tile_setup ends with a barrier)
+  if (!tile_setup<NT, NCOL>(a, bid, sPlan, sScan, t)) return;
+  const int s = t.s, S = t.S, stride = t.stride, j0 = t.j0;
+  stage_weights<NT, NCOL>(a, sPlan, sW);
+  stage_params<NT>(a, &sP[0].x);
   const int nb = a.Mp / BMP;
   const int b_begin = (int)(((long long)s * nb) / S);
   const int b_end = (int)(((long long)(s + 1) * nb) / S);
@@ -1456,7 +1498,7 @@ __device__ inline void eval_lp_ws(const EvalArgs& a, int bid) {
       double f = facc[h];
       f += __shfl_xor(f, 16);
       f += __shfl_xor(f, 32);
-      if (j0 + col - n < stride && q == 0) a.Fpart[(size_t)s * stride + j0 + col] = f;
+      if (q == 0 && sPlan[col] >= 0) a.Fpart[(size_t)s * stride + j0 + col] = f;
     }
   } else {
     const int st = tid - NTS;
@@ -1508,7 +1550,7 @@ __device__ inline void eval_lp_ws(const EvalArgs& a, int bid) {
 #pragma unroll
     for (int h = 0; h < 2; ++h) {
       const int col = 32 * grp + 16 * h + n;
-      if (j0 + col - n < stride) {  // the same for the whole wavefront
+      if (sPlan[col] >= 0) {  // an empty column has no partials
         float* __restrict__ gout = a.Gpart + ((size_t)s * stride + j0 + col) * KP;
 #pragma unroll
         for (int k = 0; k < NK16; ++k)
@@ -1683,59 +1725,77 @@ hipError_t launch_kp_grouped(const EvalArgs* args, const int* start, int n, int 
 
 }  // namespace
 
-hipError_t launch_eval(const EvalArgs& a, int dtype, hipStream_t st) {
+// The padded dwell counts are compiled in four parts: this file is part 0 and
+// is included by the others with GMCO_EVAL_PART 1 .. 3.
+#ifndef GMCO_EVAL_PART
+#define GMCO_EVAL_PART 0
+#endif
+#if GMCO_EVAL_PART == 0
+#define GMCO_KP_LIST(X) X(32) X(160) X(288) X(416)
+#elif GMCO_EVAL_PART == 1
+#define GMCO_KP_LIST(X) X(64) X(192) X(320) X(448)
+#elif GMCO_EVAL_PART == 2
+#define GMCO_KP_LIST(X) X(96) X(224) X(352) X(480)
+#else
+#define GMCO_KP_LIST(X) X(128) X(256) X(384) X(512)
+#endif
+#define GMCO_PART_NAME2(name, part) name##part
+#define GMCO_PART_NAME1(name, part) GMCO_PART_NAME2(name, part)
+#define GMCO_PART_NAME(name) GMCO_PART_NAME1(name, GMCO_EVAL_PART)
+
+hipError_t GMCO_PART_NAME(launch_eval_part)(const EvalArgs& a, int dtype, hipStream_t st) {
   switch (a.Kp) {
 #define GMCO_KP_CASE(v) \
   case v:               \
     return launch_kp<v>(a, dtype, st);
-    GMCO_KP_CASE(32)
-    GMCO_KP_CASE(64)
-    GMCO_KP_CASE(96)
-    GMCO_KP_CASE(128)
-    GMCO_KP_CASE(160)
-    GMCO_KP_CASE(192)
-    GMCO_KP_CASE(224)
-    GMCO_KP_CASE(256)
-    GMCO_KP_CASE(288)
-    GMCO_KP_CASE(320)
-    GMCO_KP_CASE(352)
-    GMCO_KP_CASE(384)
-    GMCO_KP_CASE(416)
-    GMCO_KP_CASE(448)
-    GMCO_KP_CASE(480)
-    GMCO_KP_CASE(512)
+    GMCO_KP_LIST(GMCO_KP_CASE)
 #undef GMCO_KP_CASE
     default:
       return hipErrorInvalidValue;
   }
 }
 
-hipError_t launch_eval_grouped(const EvalArgs* args, const int* start, int n, int grid, int Kp, int dtype,
-                               int lp_shape, hipStream_t st) {
+hipError_t GMCO_PART_NAME(launch_eval_grouped_part)(const EvalArgs* args, const int* start, int n, int grid, int Kp,
+                                                    int dtype, int lp_shape, hipStream_t st) {
   switch (Kp) {
 #define GMCO_KP_CASE(v) \
   case v:               \
     return launch_kp_grouped<v>(args, start, n, grid, dtype, lp_shape, st);
-    GMCO_KP_CASE(32)
-    GMCO_KP_CASE(64)
-    GMCO_KP_CASE(96)
-    GMCO_KP_CASE(128)
-    GMCO_KP_CASE(160)
-    GMCO_KP_CASE(192)
-    GMCO_KP_CASE(224)
-    GMCO_KP_CASE(256)
-    GMCO_KP_CASE(288)
-    GMCO_KP_CASE(320)
-    GMCO_KP_CASE(352)
-    GMCO_KP_CASE(384)
-    GMCO_KP_CASE(416)
-    GMCO_KP_CASE(448)
-    GMCO_KP_CASE(480)
-    GMCO_KP_CASE(512)
+    GMCO_KP_LIST(GMCO_KP_CASE)
 #undef GMCO_KP_CASE
     default:
       return hipErrorInvalidValue;
   }
 }
+
+#if GMCO_EVAL_PART == 0
+#define GMCO_DECLARE_PART(i)                                                             \
+  hipError_t launch_eval_part##i(const EvalArgs& a, int dtype, hipStream_t st);          \
+  hipError_t launch_eval_grouped_part##i(const EvalArgs* args, const int* start, int n,  \
+                                         int grid, int Kp, int dtype, int lp_shape, hipStream_t st);
+GMCO_DECLARE_PART(1)
+GMCO_DECLARE_PART(2)
+GMCO_DECLARE_PART(3)
+#undef GMCO_DECLARE_PART
+
+hipError_t launch_eval(const EvalArgs& a, int dtype, hipStream_t st) {
+  switch ((a.Kp / kKAlign - 1) % 4) {
+    case 0: return launch_eval_part0(a, dtype, st);
+    case 1: return launch_eval_part1(a, dtype, st);
+    case 2: return launch_eval_part2(a, dtype, st);
+    default: return launch_eval_part3(a, dtype, st);
+  }
+}
+
+hipError_t launch_eval_grouped(const EvalArgs* args, const int* start, int n, int grid, int Kp, int dtype,
+                               int lp_shape, hipStream_t st) {
+  switch ((Kp / kKAlign - 1) % 4) {
+    case 0: return launch_eval_grouped_part0(args, start, n, grid, Kp, dtype, lp_shape, st);
+    case 1: return launch_eval_grouped_part1(args, start, n, grid, Kp, dtype, lp_shape, st);
+    case 2: return launch_eval_grouped_part2(args, start, n, grid, Kp, dtype, lp_shape, st);
+    default: return launch_eval_grouped_part3(args, start, n, grid, Kp, dtype, lp_shape, st);
+  }
+}
+#endif
 
 }  // namespace gmco
