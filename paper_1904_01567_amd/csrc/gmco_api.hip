@@ -8,6 +8,7 @@
 #include <new>
 #include <numeric>
 #include <string>
+#include <thread>
 #include <vector>
 
 #include "gmco_internal.h"
@@ -108,7 +109,8 @@ struct gmco_ctx {
   bool case_loaded = false;
   bool has_points = false;  // point positions were given (features need them)
   int P = 0;              // current batch, 0 = none
-  int* host_count = nullptr;  // pinned copies of the running-plan count, one per block parity
+  int* host_count = nullptr;  // pinned: running-plan counts, one per block parity, then host_word
+  unsigned long long* host_word = nullptr;  // a round's number and running plans, written by its evaluation
   hipEvent_t ev0 = nullptr, ev1 = nullptr;
   hipStream_t gstream = nullptr;  // library-owned stream for graph capture
   hipEvent_t gev = nullptr;
@@ -416,11 +418,12 @@ int gmco_create(gmco_ctx** out, const gmco_opts* o) {
   c->Pmax = o->max_plans;
   c->n_cu = prop.multiProcessorCount;
   if (hipSetDevice(c->device) != hipSuccess ||
-      hipHostMalloc((void**)&c->host_count, 2 * sizeof(int), hipHostMallocDefault) != hipSuccess ||
+      hipHostMalloc((void**)&c->host_count, 16, hipHostMallocDefault) != hipSuccess ||
       hipEventCreate(&c->ev0) != hipSuccess || hipEventCreate(&c->ev1) != hipSuccess) {
     gmco_destroy(c);
     return GMCO_EHIP;
   }
+  c->host_word = reinterpret_cast<unsigned long long*>(c->host_count + 2);
   *out = c;
   return GMCO_OK;
 }
@@ -720,38 +723,28 @@ int gmco_optimize(gmco_ctx* c, const gmco_run* r, gmco_run_info* info) {
   GMCO_HIP(c, hipSetDevice(c->device));
   const Layout& L = c->lay;
   const Dims& d = c->dim;
-  int* active = c->at<int>(L.active);
   unsigned long long* work = c->at<unsigned long long>(L.work);  // [0] all launches, [1] timed ones
-  GMCO_HIP(c, hipMemsetAsync(active, 0, 2 * sizeof(int), c->stream));
-  GMCO_HIP(c, hipMemsetAsync(work, 0, 2 * sizeof(unsigned long long), c->stream));
-  GMCO_HIP(c, launch_resume(c->at<PlanState>(L.ps), c->at<float>(L.x), c->at<float>(L.xt), c->at<int>(L.flag), d.Pp, d.Kp,
-                            r->max_iter, r->resume_stopped, c->stream));
+  GMCO_HIP(c, launch_resume(c->at<PlanState>(L.ps), c->at<float>(L.x), c->at<float>(L.xt), c->at<int>(L.flag),
+                            c->at<int>(L.active), work, d.Pp, d.Kp, r->max_iter, r->resume_stopped, c->stream));
   UpdateArgs u = update_args(c, r);
   EvalArgs a = eval_args(c, c->at<float>(L.xt), true, dtype);
-  EvalArgs a_timed = a;  // the timed launches also count their work apart
-  a_timed.work2 = work + 1;
-  const int check = r->check_every > 0 ? r->check_every : 16;
+  a.host_word = c->host_word;
   const long long max_rounds = 1 + (long long)std::max(r->max_iter, 1) * r->max_ls + 1;
-  // Rounds are issued in blocks of `check`.  After each block the running-plan
-  // count is copied to pinned host memory and an event recorded; the host
-  // then waits for the block before last, so the device always has the next
-  // block queued and never idles at a check.  When a block reports no running
-  // plan, the one queued after it runs as empty rounds (every kernel exits at
-  // once) and is not timed.
+  // The evaluation of every kReportRounds-th round writes its number and the
+  // count of running plans to pinned host memory.  The host issues rounds up to
+  // `ahead` past the last one reported, so the device never idles, and stops at
+  // a report of no running plan; the rounds issued past it run empty (every
+  // kernel exits at once).  (Copying the count back once per 16 rounds and
+  // waiting for the block before last left 17 to 32 empty rounds, and the copy's
+  // own launch: 60 steps of 8 plans 1,531 -> 1,444 us, a run of 1,000 plans to
+  // the clinical stop rule 33.7 -> 33.2 ms.)
   // Optional sampled timing: events around the evaluation and the update of
-  // every time_kernels-th round, 4 per timed round, one set per block parity.
+  // every time_kernels-th round, 4 per timed round, in a ring that outlasts the
+  // rounds in flight.
+  const int ahead = kReportRounds + 4;
   const int every = r->time_kernels;
-  std::vector<hipEvent_t> ev;
-  hipEvent_t bev[2] = {nullptr, nullptr};
-  int timed = 0;
-  ev.resize((every > 0 ? (size_t)8 * check : 0) + 2, nullptr);
-  for (auto& e : ev) {
-    if (hipEventCreate(&e) != hipSuccess) {
-      for (auto& f : ev)
-        if (f) (void)hipEventDestroy(f);
-      return fail(c, GMCO_EHIP, "hipEventCreate failed");
-    }
-  }
+  const int ring = every > 0 ? ahead + 1 : 0;
+  std::vector<hipEvent_t> ev((size_t)4 * ring, nullptr);
   struct EventGuard {
     std::vector<hipEvent_t>& v;
     ~EventGuard() {
@@ -759,74 +752,66 @@ int gmco_optimize(gmco_ctx* c, const gmco_run* r, gmco_run_info* info) {
         if (e) (void)hipEventDestroy(e);
     }
   } guard{ev};
-  bev[0] = ev[ev.size() - 2];
-  bev[1] = ev[ev.size() - 1];
+  for (auto& e : ev)
+    if (hipEventCreate(&e) != hipSuccess) return fail(c, GMCO_EHIP, "hipEventCreate failed");
+  int timed = 0, harvested = 0;
   double eval_ms = 0.0, update_ms = 0.0;
-  int in_block[2] = {0, 0};
-  auto harvest = [&](int set) -> hipError_t {
-    const int n = in_block[set];
-    hipEvent_t* e = ev.data() + (size_t)set * 4 * check;
-    timed += n;
-    for (int i = 0; i < n; ++i) {
-      float a_ms = 0.f, b_ms = 0.f;
-      hipError_t er = hipEventElapsedTime(&a_ms, e[4 * i], e[4 * i + 1]);
-      if (er != hipSuccess) return er;
-      er = hipEventElapsedTime(&b_ms, e[4 * i + 2], e[4 * i + 3]);
-      if (er != hipSuccess) return er;
-      eval_ms += a_ms;
-      update_ms += b_ms;
-    }
-    return hipSuccess;
+  auto harvest = [&]() -> hipError_t {  // the oldest timed round
+    hipEvent_t* e = ev.data() + (size_t)4 * (harvested % ring);
+    float a_ms = 0.f, b_ms = 0.f;
+    hipError_t er = hipEventSynchronize(e[3]);
+    if (er == hipSuccess) er = hipEventElapsedTime(&a_ms, e[0], e[1]);
+    if (er == hipSuccess) er = hipEventElapsedTime(&b_ms, e[2], e[3]);
+    eval_ms += a_ms;
+    update_ms += b_ms;
+    ++harvested;
+    return er;
   };
+  volatile unsigned long long* word = c->host_word;
+  *word = 0;
   GMCO_HIP(c, hipEventRecord(c->ev0, c->stream));
   long long round = 0;
-  long long blk = 0;  // blocks issued
-  bool done_flag = false;
-  while (!done_flag) {
-    const int set = (int)(blk & 1);
-    hipEvent_t* e = every > 0 ? ev.data() + (size_t)set * 4 * check : nullptr;
-    in_block[set] = 0;
-    for (int k = 0; k < check && round < max_rounds; ++k, ++round) {
-      u.round = (int)round;
+  long long seen = 0;  // rounds whose report has arrived
+  while (true) {
+    const unsigned long long w = *word;
+    if (w != 0) {
+      seen = (long long)(w >> 32);
+      if ((w & 0xffffffffull) == 0) break;
+    }
+    if (round >= max_rounds) break;  // every plan has stopped by then
+    if (round - seen < ahead) {
+      u.round = a.round = (int)round;
       const bool tk = every > 0 && round % every == 0;
-      const int i = in_block[set];
-      if (tk) GMCO_HIP(c, hipEventRecord(e[4 * i], c->stream));
-      GMCO_HIP(c, launch_eval(tk ? a_timed : a, dtype, c->stream));
+      hipEvent_t* e = nullptr;
+      a.work2 = nullptr;
       if (tk) {
-        GMCO_HIP(c, hipEventRecord(e[4 * i + 1], c->stream));
-        GMCO_HIP(c, hipEventRecord(e[4 * i + 2], c->stream));
+        if (timed - harvested == ring) GMCO_HIP(c, harvest());
+        e = ev.data() + (size_t)4 * (timed % ring);
+        a.work2 = work + 1;  // the timed launches also count their work apart
+        GMCO_HIP(c, hipEventRecord(e[0], c->stream));
+      }
+      GMCO_HIP(c, launch_eval(a, dtype, c->stream));
+      if (tk) {
+        GMCO_HIP(c, hipEventRecord(e[1], c->stream));
+        GMCO_HIP(c, hipEventRecord(e[2], c->stream));
       }
       GMCO_HIP(c, launch_update(u, c->stream));
       if (tk) {
-        GMCO_HIP(c, hipEventRecord(e[4 * i + 3], c->stream));
-        ++in_block[set];
+        GMCO_HIP(c, hipEventRecord(e[3], c->stream));
+        ++timed;
       }
+      ++round;
+      continue;
     }
-    // running plans after this block's last round (the next update resets the
-    // other counter, so the copy is queued before any later round)
-    GMCO_HIP(c, hipMemcpyAsync(c->host_count + set, active + ((round - 1) & 1), sizeof(int),
-                               hipMemcpyDeviceToHost, c->stream));
-    GMCO_HIP(c, hipEventRecord(bev[set], c->stream));
-    ++blk;
-    if (round >= max_rounds) {  // nothing more to issue: wait for the last block
-      GMCO_HIP(c, hipEventSynchronize(bev[set]));
-      // the block before it is not harvested yet; the last block ran empty
-      // when that one already reported no running plan
-      const bool last_empty = blk >= 2 && c->host_count[set ^ 1] == 0;
-      if (every > 0 && blk >= 2) GMCO_HIP(c, harvest(set ^ 1));
-      if (every > 0 && !last_empty) GMCO_HIP(c, harvest(set));
-      done_flag = true;
-    } else if (blk >= 2) {  // wait for the block before this one
-      const int prev = set ^ 1;
-      GMCO_HIP(c, hipEventSynchronize(bev[prev]));
-      if (every > 0) GMCO_HIP(c, harvest(prev));
-      if (c->host_count[prev] == 0) {
-        // the block just queued runs empty: wait for it, do not time it
-        GMCO_HIP(c, hipEventSynchronize(bev[set]));
-        done_flag = true;
-      }
+    // wait for a report; a stream that has run dry or failed has no more to give
+    for (int spin = 0; spin < 256 && *word == w; ++spin) std::this_thread::yield();
+    if (*word == w) {
+      const hipError_t q = hipStreamQuery(c->stream);
+      if (q == hipSuccess && *word == w) return fail(c, GMCO_EHIP, "the stream ended without a report");
+      if (q != hipSuccess && q != hipErrorNotReady) return hip_fail(c, q, "hipStreamQuery");
     }
   }
+  while (harvested < timed) GMCO_HIP(c, harvest());
   GMCO_HIP(c, hipEventRecord(c->ev1, c->stream));
   GMCO_HIP(c, hipEventSynchronize(c->ev1));
   unsigned long long done[2] = {0, 0};
@@ -869,10 +854,9 @@ int gmco_optimize_many(gmco_ctx* const* ctxs, int n, const gmco_run* r, gmco_run
   for (int i = 0; i < n; ++i) {
     gmco_ctx* c = ctxs[i];
     const Layout& L = c->lay;
-    GMCO_HIP(c, hipMemsetAsync(c->at<int>(L.active), 0, 2 * sizeof(int), st));
-    GMCO_HIP(c, hipMemsetAsync(c->at<unsigned long long>(L.work), 0, sizeof(unsigned long long), st));
-    GMCO_HIP(c, launch_resume(c->at<PlanState>(L.ps), c->at<float>(L.x), c->at<float>(L.xt), c->at<int>(L.flag), c->dim.Pp,
-                              c->dim.Kp, r->max_iter, r->resume_stopped, st));
+    GMCO_HIP(c, launch_resume(c->at<PlanState>(L.ps), c->at<float>(L.x), c->at<float>(L.xt), c->at<int>(L.flag),
+                              c->at<int>(L.active), c->at<unsigned long long>(L.work), c->dim.Pp, c->dim.Kp,
+                              r->max_iter, r->resume_stopped, st));
     us[i] = update_args(c, r);
     as[i] = eval_args(c, c->at<float>(L.xt), true, dtypes[i]);
   }

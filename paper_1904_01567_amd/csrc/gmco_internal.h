@@ -39,6 +39,9 @@ __host__ __device__ constexpr bool acc_quarters_ok(int Kp) { return Kp % 64 == 0
 __host__ __device__ constexpr int lp_tiles(int Kp) { return lp_threads(Kp) / 64 * 16 * lp_halves(Kp) / kPT; }
 constexpr int kKAlign = 32;
 constexpr int kMAlign = 32;  // points: a multiple of every kernel's block
+// Rounds between reports of the running plans to the host: a store to host
+// memory holds its kernel's end for about 2.7 us.
+constexpr int kReportRounds = 8;
 constexpr int kSplitMax = 256;  // largest split-M count the heuristic picks
 
 // Internal plan states; 0..5 match gmco_plan_status.
@@ -103,6 +106,9 @@ struct EvalArgs {
   const int* split_tab;   // [ntiles + 1] split count per active tile count
   int* slot;              // [Pp] compact rank of each running plan
   RoundTable* rt;
+  unsigned long long* host_word;  // pinned host memory, NULL: no report.  Every
+                          // kReportRounds-th round: (round + 1) << 32 | nact
+  int round;
   unsigned long long* work;
   unsigned long long* work2;  // optional second count (the timed launches)
   int P;                  // plans of the batch
@@ -180,8 +186,11 @@ hipError_t launch_update(const UpdateArgs& a, hipStream_t st);
 hipError_t launch_finish_eval(const float* Gpart, const double* Fpart, const float* x, int S,
                               int P, int Pp, int K, int Kp, double* F, double* g,
                               hipStream_t st);
-hipError_t launch_resume(PlanState* ps, const float* x, float* xt, int* flag, int Pp, int Kp,
-                         int max_iter, int resume_stopped, hipStream_t st);
+// Resumes stopped plans, sets every plan's flag and clears the running
+// counts and the work counts of the call.
+hipError_t launch_resume(PlanState* ps, const float* x, float* xt, int* flag, int* active,
+                         unsigned long long* work, int Pp, int Kp, int max_iter, int resume_stopped,
+                         hipStream_t st);
 hipError_t launch_export_t(const float* x, int P, int K, int Kp, double* t64, int Kp_out,
                            hipStream_t st);
 hipError_t launch_x_to_device(const double* x_host_dev, int P, int Pp, int K, int Kp, float* xe,

@@ -611,9 +611,14 @@ __global__ __launch_bounds__(64 * NW) void k_finish_eval(const float* __restrict
 // stopped by the stop rule or a failed line search: the current point is
 // taken as the iterate again (history kept) and a new direction computed.
 __global__ void k_resume(PlanState* ps, const float* __restrict__ x, float* __restrict__ xt,
-                         int* __restrict__ flag, int Pp, int Kp, int max_iter, int resume_stopped) {
+                         int* __restrict__ flag, int* __restrict__ active, unsigned long long* __restrict__ work,
+                         int Pp, int Kp, int max_iter, int resume_stopped) {
   const int p = blockIdx.x;
   if (p >= Pp) return;
+  if (p == 0 && threadIdx.x < 2) {
+    active[threadIdx.x] = 0;
+    work[threadIdx.x] = 0;
+  }
   const int s = ps[p].status;
   const bool resume = (s == ST_MAXITER && ps[p].iter < max_iter) ||
                       (resume_stopped && (s == ST_CONVERGED || s == ST_LSFAIL) &&
@@ -654,9 +659,10 @@ hipError_t launch_finish_eval(const float* Gpart, const double* Fpart, const flo
   return hipGetLastError();
 }
 
-hipError_t launch_resume(PlanState* ps, const float* x, float* xt, int* flag, int Pp, int Kp,
-                         int max_iter, int resume_stopped, hipStream_t st) {
-  hipLaunchKernelGGL(k_resume, dim3(Pp), dim3(128), 0, st, ps, x, xt, flag, Pp, Kp, max_iter,
+hipError_t launch_resume(PlanState* ps, const float* x, float* xt, int* flag, int* active,
+                         unsigned long long* work, int Pp, int Kp, int max_iter, int resume_stopped,
+                         hipStream_t st) {
+  hipLaunchKernelGGL(k_resume, dim3(Pp), dim3(128), 0, st, ps, x, xt, flag, active, work, Pp, Kp, max_iter,
                      resume_stopped);
   return hipGetLastError();
 }
