@@ -97,6 +97,8 @@ class gmco_plan_metrics(C.Structure):
                 ("reserved", C.c_int)]
 
 
+_METRICS_DTYPE = np.dtype(gmco_plan_metrics)  # one record per plan, the C layout
+
 _lib = None
 
 
@@ -353,18 +355,14 @@ class Planner:
         return x
 
     def metrics(self) -> dict:
-        arr = (gmco_plan_metrics * self.P)()
-        self._check(self.lib.gmco_get_metrics(self._ctx, arr), "get_metrics")
-        G = self.O
-        out = {
-            "F_run": np.array([m.F_run for m in arr]),
-            "F64": np.array([m.F64 for m in arr]),
-            "iterations": np.array([m.iterations for m in arr]),
-            "evaluations": np.array([m.evaluations for m in arr]),
-            "status": np.array([m.status for m in arr]),
-        }
+        arr = np.empty(self.P, dtype=_METRICS_DTYPE)
+        self._check(self.lib.gmco_get_metrics(self._ctx, arr.ctypes.data_as(C.POINTER(gmco_plan_metrics))),
+                    "get_metrics")
+        out = {f: arr[f].copy() for f in ("F_run", "F64")}
+        for f in ("iterations", "evaluations", "status"):
+            out[f] = arr[f].astype(np.int64)
         for f in ("f_organ", "V100_pct", "V75_cc", "D10_pct", "D90_pct"):
-            out[f] = np.array([list(getattr(m, f))[:G] for m in arr])
+            out[f] = arr[f][:, :self.O].copy()
         return out
 
     def dose_rate(self, run_dtype: bool = False):

@@ -3,6 +3,7 @@
 #include <algorithm>
 #include <cmath>
 #include <cstdio>
+#include <cstdlib>
 #include <cstring>
 #include <mutex>
 #include <new>
@@ -22,11 +23,12 @@ int round_up(int v, int a) { return (v + a - 1) / a * a; }
 
 // Byte offsets of every device array inside the arena.
 struct Layout {
-  size_t D64, D32, Dlp, DTlp, colscale, grp, perm, stage, gparams, volume, goff, gcnt, counts, t_bar;
-  size_t gorg, D64d, dstage, dperm, doff, dcnt;
+  size_t D64, D32, Dlp, DTlp, colscale, stage, t_bar, D64d;
+  // the case's small arrays, uploaded as one block
+  size_t up, grp, perm, dwell, pts, gparams, volume, goff, gcnt, counts, gorg, dstage, dperm, doff, dcnt, split_tab,
+      up_end;
   size_t Wst, t0st, xst, Fst, gst;
-  size_t wn, W64, x, g, dir, xt, xe, Sh, Yh, rho, ps, Gpart, Fpart, active, work, flag, slot, rt,
-      split_tab;
+  size_t wn, W64, x, g, dir, xt, xe, Sh, Yh, rho, ps, Gpart, Fpart, active, work, flag, slot, rt;
   size_t d64, metrics, hist, feat, sel;
   size_t mlpX, mlpY, Fu, usewarm, nwarm;
   size_t total;
@@ -111,6 +113,7 @@ struct gmco_ctx {
   int P = 0;              // current batch, 0 = none
   int* host_count = nullptr;  // pinned: running-plan counts, one per block parity, then host_word
   unsigned long long* host_word = nullptr;  // a round's number and running plans, written by its evaluation
+  bool pooled = false;  // counted as a user of the staging pool
   hipEvent_t ev0 = nullptr, ev1 = nullptr;
   hipStream_t gstream = nullptr;  // library-owned stream for graph capture
   hipEvent_t gev = nullptr;
@@ -206,20 +209,25 @@ Layout make_layout(const Dims& d, int G, int m, int dtype, int Pmax) {
   L.Dlp = take(MK * lp_bytes(dtype));
   L.DTlp = take(is_low_precision(dtype) ? MK * 2 : 0);  // BF16 for the back-projection
   L.colscale = take((size_t)d.Kp * 4);
+  L.stage = take((size_t)d.M * d.K * 8);  // a caller's dose-rate matrix
+  L.D64d = take((size_t)d.Mdp * d.Kp * 8);
+  L.up = off;
   L.grp = take((size_t)d.Mp * 4);
   L.perm = take((size_t)d.M * 4);
-  L.stage = take((size_t)d.M * d.K * 8 + ((size_t)d.M + d.K) * 3 * 8);
+  L.dwell = take((size_t)d.K * 3 * 8);
+  L.pts = take((size_t)d.M * 3 * 8);
   L.gparams = take(kGmax * 4 * 8);
   L.volume = take(kGmax * 8);
   L.goff = take(kGmax * 4);
   L.gcnt = take(kGmax * 4);
   L.counts = take(kGmax * 4);
   L.gorg = take(kGmax * 4);
-  L.D64d = take((size_t)d.Mdp * d.Kp * 8);
   L.dstage = take((size_t)d.Md * 3 * 8);
   L.dperm = take((size_t)d.Md * 4);
   L.doff = take(kGmax * 4);
   L.dcnt = take(kGmax * 4);
+  L.split_tab = take((size_t)2 * (d.ntiles + 1) * 4);
+  L.up_end = off;
   L.t_bar = take(8);
   L.Wst = take((size_t)Pmax * kGmax * 8);
   L.t0st = take((size_t)Pmax * d.K * 8);
@@ -242,7 +250,6 @@ Layout make_layout(const Dims& d, int G, int m, int dtype, int Pmax) {
   L.flag = take((size_t)d.Pp * 4);
   L.slot = take((size_t)d.Pp * 4);
   L.rt = take(sizeof(RoundTable));
-  L.split_tab = take((size_t)2 * (d.ntiles + 1) * 4);
   L.active = take(2 * sizeof(int));
   L.work = take(2 * sizeof(unsigned long long));
   // final doses (Pp x Mp, then Pp x Mdp for the DVH points); an FP8 context
@@ -263,11 +270,125 @@ Layout make_layout(const Dims& d, int G, int m, int dtype, int Pmax) {
   return L;
 }
 
-bool finite_all(const double* v, size_t n) {
-  for (size_t i = 0; i < n; ++i)
-    if (!std::isfinite(v[i])) return false;
+// True when every value is finite; with y, also their FP32 values.  The test is
+// on the bits, without a branch per value, so that the loop vectorises (an
+// exponent of all ones carries into the sign bit).
+bool finite_all(const double* v, size_t n, float* y = nullptr) {
+  for (size_t i0 = 0; i0 < n; i0 += 2048) {
+    const size_t e = std::min(n, i0 + 2048);
+    uint64_t bad = 0;
+    for (size_t i = i0; i < e; ++i) {
+      uint64_t b;
+      std::memcpy(&b, v + i, 8);
+      bad |= (b & 0x7fffffffffffffffull) + 0x0010000000000000ull;
+    }
+    if (bad >> 63) return false;
+    if (y)
+      for (size_t i = i0; i < e; ++i) y[i] = (float)v[i];
+  }
   return true;
 }
+
+// Pinned host memory that calls borrow to stage their copies: a copy from or to
+// pageable memory goes through the runtime's own staging and takes two to three
+// times as long (2.9 MB: 100 us up and 157 down, against 58).  Blocks
+// outlive a call, since pinning costs far more than a call saves; up to
+// kPinKeep bytes stay while any context exists, all of them go with the last.
+class PinPool {
+ public:
+  void enter() {
+    std::lock_guard<std::mutex> lk(mu_);
+    ++users_;
+  }
+  void leave() {
+    std::lock_guard<std::mutex> lk(mu_);
+    if (--users_ > 0) return;
+    for (int i = 0; i < n_; ++i) (void)hipHostFree(free_[i].p);
+    n_ = 0;
+    kept_ = 0;
+  }
+  // nullptr when no memory can be pinned
+  void* get(size_t bytes, size_t* size) {
+    {
+      std::lock_guard<std::mutex> lk(mu_);
+      int best = -1;
+      for (int i = 0; i < n_; ++i)
+        if (free_[i].size >= bytes && (best < 0 || free_[i].size < free_[best].size)) best = i;
+      if (best >= 0) {
+        const Block b = free_[best];
+        free_[best] = free_[--n_];
+        kept_ -= b.size;
+        *size = b.size;
+        return b.p;
+      }
+    }
+    size_t n = size_t(1) << 20;
+    while (n < bytes) n <<= 1;
+    void* p = nullptr;
+    if (hipHostMalloc(&p, n, hipHostMallocPortable) != hipSuccess) {
+      (void)hipGetLastError();
+      return nullptr;
+    }
+    *size = n;
+    return p;
+  }
+  void put(void* p, size_t size) {
+    {
+      std::lock_guard<std::mutex> lk(mu_);
+      if (users_ > 0 && n_ < kPinBlocks && kept_ + size <= kPinKeep) {
+        free_[n_++] = {p, size};
+        kept_ += size;
+        return;
+      }
+    }
+    (void)hipHostFree(p);
+  }
+
+ private:
+  static constexpr size_t kPinKeep = size_t(64) << 20;
+  static constexpr int kPinBlocks = 16;
+  struct Block {
+    void* p;
+    size_t size;
+  };
+  std::mutex mu_;
+  Block free_[kPinBlocks] = {};
+  int n_ = 0;
+  size_t kept_ = 0;
+  int users_ = 0;
+};
+PinPool g_pin;
+
+// One call's staging memory (pageable when none can be pinned; ok() is false
+// when there is none at all).  Copies from and to it are over once the call has
+// synchronised its stream (settled); a call that returns early waits for them
+// here.
+struct Staging {
+  Staging(size_t bytes, hipStream_t s) : stream(s) {
+    p = g_pin.get(bytes, &size);
+    if (!p) p = plain = std::malloc(bytes);
+  }
+  Staging(const Staging&) = delete;
+  Staging& operator=(const Staging&) = delete;
+  ~Staging() {
+    if (!settled) (void)hipStreamSynchronize(stream);
+    if (plain) std::free(plain);
+    else if (p) g_pin.put(p, size);
+  }
+  bool ok() const { return p != nullptr; }
+  template <class T>
+  T* at(size_t off) {
+    return reinterpret_cast<T*>(static_cast<char*>(p) + off);
+  }
+  hipStream_t stream;
+  void* p = nullptr;
+  void* plain = nullptr;
+  size_t size = 0;
+  bool settled = false;
+};
+
+#define GMCO_STAGED(ctx, st) \
+  if (!(st).ok()) return fail((ctx), GMCO_ENOMEM, "host memory for the call's copies")
 
 int copy_h2d(gmco_ctx* c, void* dst, const void* src, size_t bytes) {
   if (bytes == 0) return GMCO_OK;
@@ -357,12 +478,11 @@ int check_run(gmco_ctx* c, const gmco_run* r, int* dtype) {
 }
 
 int summarize(gmco_ctx* c, long long rounds, float ms, double eval_ms, double update_ms,
-              unsigned long long work, gmco_run_info* info) {
-  std::vector<PlanState> ps(c->P);
-  GMCO_HIP(c, hipMemcpy(ps.data(), c->at<void>(c->lay.ps), (size_t)c->P * sizeof(PlanState), hipMemcpyDeviceToHost));
+              unsigned long long work, const PlanState* ps, gmco_run_info* info) {
   gmco_run_info inf{};
   inf.rounds = (int)rounds;
-  for (const PlanState& s : ps) {
+  for (int p = 0; p < c->P; ++p) {
+    const PlanState& s = ps[p];
     inf.n_converged += s.status == ST_CONVERGED;
     inf.n_maxiter += s.status == ST_MAXITER;
     inf.n_ls_fail += s.status == ST_LSFAIL;
@@ -424,6 +544,8 @@ int gmco_create(gmco_ctx** out, const gmco_opts* o) {
     return GMCO_EHIP;
   }
   c->host_word = reinterpret_cast<unsigned long long*>(c->host_count + 2);
+  c->pooled = true;
+  g_pin.enter();
   *out = c;
   return GMCO_OK;
 }
@@ -440,6 +562,7 @@ int gmco_destroy(gmco_ctx* c) {
   if (c->ev1) (void)hipEventDestroy(c->ev1);
   if (c->gev) (void)hipEventDestroy(c->gev);
   if (c->gstream) (void)hipStreamDestroy(c->gstream);
+  if (c->pooled) g_pin.leave();
   delete c;
   return GMCO_OK;
 }
@@ -576,35 +699,40 @@ int gmco_load_case(gmco_ctx* c, const gmco_case* cs) {
     for (int i = 0; i < Md; ++i) dperm[cur[cs->dvh_organ[i]]++] = i;
   }
 
-  double* stage = c->at<double>(L.stage);
-  double* st_D = stage;                         // M*K
-  double* st_dw = stage + (size_t)M * K;        // K*3
-  double* st_pt = st_dw + (size_t)K * 3;        // M*3
-  int rc;
-  if ((rc = copy_h2d(c, c->at<void>(L.perm), c->perm.data(), (size_t)M * 4))) return rc;
-  if ((rc = copy_h2d(c, c->at<void>(L.grp), grp.data(), (size_t)d.Mp * 4))) return rc;
-  if ((rc = copy_h2d(c, st_dw, cs->dwell_xyz, (size_t)K * 3 * 8))) return rc;
-  if (cs->point_xyz && (rc = copy_h2d(c, st_pt, cs->point_xyz, (size_t)M * 3 * 8))) return rc;
-  if (cs->dose_rate && (rc = copy_h2d(c, st_D, cs->dose_rate, (size_t)M * K * 8))) return rc;
+  // the small arrays as one block, laid out as in the arena
+  Staging st(L.up_end - L.up, c->stream);
+  GMCO_STAGED(c, st);
+  auto put = [&](size_t off, const void* src, size_t bytes) {
+    if (bytes) std::memcpy(st.at<char>(off - L.up), src, bytes);
+  };
+  put(L.perm, c->perm.data(), (size_t)M * 4);
+  put(L.grp, grp.data(), (size_t)d.Mp * 4);
+  put(L.dwell, cs->dwell_xyz, (size_t)K * 3 * 8);
+  if (cs->point_xyz) put(L.pts, cs->point_xyz, (size_t)M * 3 * 8);
   std::vector<double> gp(kGmax * 4, 0.0), vol(kGmax, 0.0);
   std::copy(cs->group_params, cs->group_params + 4 * G, gp.begin());
   if (cs->group_volume_cc) std::copy(cs->group_volume_cc, cs->group_volume_cc + O, vol.begin());
-  if ((rc = copy_h2d(c, c->at<void>(L.gparams), gp.data(), gp.size() * 8))) return rc;
-  if ((rc = copy_h2d(c, c->at<void>(L.volume), vol.data(), vol.size() * 8))) return rc;
-  if ((rc = copy_h2d(c, c->at<void>(L.goff), c->offsets.data(), kGmax * 4))) return rc;
-  if ((rc = copy_h2d(c, c->at<void>(L.gcnt), ocounts.data(), kGmax * 4))) return rc;
-  if ((rc = copy_h2d(c, c->at<void>(L.counts), norm.data(), kGmax * 4))) return rc;
-  if ((rc = copy_h2d(c, c->at<void>(L.gorg), gorg.data(), kGmax * 4))) return rc;
-  if ((rc = copy_h2d(c, c->at<void>(L.doff), doff.data(), kGmax * 4))) return rc;
-  if ((rc = copy_h2d(c, c->at<void>(L.dcnt), dcounts.data(), kGmax * 4))) return rc;
+  put(L.gparams, gp.data(), gp.size() * 8);
+  put(L.volume, vol.data(), vol.size() * 8);
+  put(L.goff, c->offsets.data(), kGmax * 4);
+  put(L.gcnt, ocounts.data(), kGmax * 4);
+  put(L.counts, norm.data(), kGmax * 4);
+  put(L.gorg, gorg.data(), kGmax * 4);
+  put(L.doff, doff.data(), kGmax * 4);
+  put(L.dcnt, dcounts.data(), kGmax * 4);
   if (Md > 0) {
-    if ((rc = copy_h2d(c, c->at<void>(L.dperm), dperm.data(), (size_t)Md * 4))) return rc;
-    if ((rc = copy_h2d(c, c->at<void>(L.dstage), cs->dvh_xyz, (size_t)Md * 3 * 8))) return rc;
+    put(L.dperm, dperm.data(), (size_t)Md * 4);
+    put(L.dstage, cs->dvh_xyz, (size_t)Md * 3 * 8);
   }
-  // (host vectors of this call stay alive until the stream synchronisation below)
-  std::vector<int> split_tab(d.split16);
-  split_tab.insert(split_tab.end(), d.split32.begin(), d.split32.end());
-  if ((rc = copy_h2d(c, c->at<void>(L.split_tab), split_tab.data(), split_tab.size() * 4))) return rc;
+  put(L.split_tab, d.split16.data(), d.split16.size() * 4);
+  put(L.split_tab + d.split16.size() * 4, d.split32.data(), d.split32.size() * 4);
+  int rc;
+  if ((rc = copy_h2d(c, c->at<void>(L.up), st.at<void>(0), L.up_end - L.up))) return rc;
+  double* st_D = c->at<double>(L.stage);
+  const double* st_dw = c->at<double>(L.dwell);
+  const double* st_pt = c->at<double>(L.pts);
+  if (cs->dose_rate && (rc = copy_h2d(c, st_D, cs->dose_rate, (size_t)M * K * 8))) return rc;
+
   // (the doses' array is free until the metrics: scratch of the row sums and column maxima)
   const int r0 = c->offsets[cs->target_group];
   GMCO_HIP(c, launch_dose_setup(st_dw, cs->point_xyz ? st_pt : nullptr, cs->dose_rate ? st_D : nullptr,
@@ -617,6 +745,7 @@ int gmco_load_case(gmco_ctx* c, const gmco_case* cs) {
     GMCO_HIP(c, launch_dose_rate(st_dw, c->at<double>(L.dstage), nullptr, c->at<int>(L.dperm), Md, K,
                                  d.Mdp, d.Kp, c->at<double>(L.D64d), c->stream));
   GMCO_HIP(c, hipStreamSynchronize(c->stream));
+  st.settled = true;
   c->has_points = cs->point_xyz != nullptr;
   c->case_loaded = true;
   return GMCO_OK;
@@ -652,19 +781,27 @@ int gmco_evaluate(gmco_ctx* c, const double* x, double* F, double* g) {
   if (!c || !x || !F || !g) return GMCO_EINVAL;
   if (!c->case_loaded || c->P == 0) return fail(c, GMCO_ESTATE, "gmco_set_weights first");
   const int P = c->P, K = c->dim.K;
-  if (!finite_all(x, (size_t)P * K)) return fail(c, GMCO_EINVAL, "x must be finite");
   GMCO_HIP(c, hipSetDevice(c->device));
   const Layout& L = c->lay;
+  // x crosses in FP32, as the kernels use it, and the gradient in FP32, as they
+  // compute it; F and g come back as one block
+  const size_t n = (size_t)P * K, back = L.gst - L.Fst + n * 4;
+  Staging st(std::max(n * 4, back), c->stream);
+  GMCO_STAGED(c, st);
+  if (!finite_all(x, n, st.at<float>(0))) return fail(c, GMCO_EINVAL, "x must be finite");
   int rc;
-  if ((rc = copy_h2d(c, c->at<void>(L.xst), x, (size_t)P * K * 8))) return rc;
-  GMCO_HIP(c, launch_x_to_device(c->at<double>(L.xst), P, c->dim.Pp, K, c->dim.Kp, c->at<float>(L.xe), c->stream));
+  if ((rc = copy_h2d(c, c->at<void>(L.xst), st.at<void>(0), n * 4))) return rc;
+  GMCO_HIP(c, launch_x32_to_device(c->at<float>(L.xst), P, c->dim.Pp, K, c->dim.Kp, c->at<float>(L.xe), c->stream));
   EvalArgs a = eval_args(c, c->at<float>(L.xe), false, c->dtype);
   GMCO_HIP(c, launch_eval(a, c->dtype, c->stream));
-  GMCO_HIP(c, launch_finish_eval(a.Gpart, a.Fpart, c->at<float>(L.xe), a.S, P, c->dim.Pp, K,
-                                 c->dim.Kp, c->at<double>(L.Fst), c->at<double>(L.gst), c->stream));
-  GMCO_HIP(c, hipMemcpyAsync(F, c->at<void>(L.Fst), (size_t)P * 8, hipMemcpyDeviceToHost, c->stream));
-  GMCO_HIP(c, hipMemcpyAsync(g, c->at<void>(L.gst), (size_t)P * K * 8, hipMemcpyDeviceToHost, c->stream));
+  GMCO_HIP(c, launch_finish_eval_f32(a.Gpart, a.Fpart, c->at<float>(L.xe), a.S, P, c->dim.Pp, K, c->dim.Kp,
+                                     c->at<double>(L.Fst), c->at<float>(L.gst), c->stream));
+  GMCO_HIP(c, hipMemcpyAsync(st.at<void>(0), c->at<void>(L.Fst), back, hipMemcpyDeviceToHost, c->stream));
   GMCO_HIP(c, hipStreamSynchronize(c->stream));
+  st.settled = true;
+  std::memcpy(F, st.at<double>(0), (size_t)P * 8);
+  const float* g32 = st.at<float>(L.gst - L.Fst);
+  for (size_t i = 0; i < n; ++i) g[i] = (double)g32[i];
   return GMCO_OK;
 }
 
@@ -688,8 +825,8 @@ int gmco_set_weights_learned(gmco_ctx* c, gmco_mlp* net, int P, const double* W,
   GMCO_HIP(c, launch_finish_eval(a.Gpart, a.Fpart, a.x, a.S, P, d.Pp, d.K, d.Kp, c->at<double>(L.Fu),
                                  c->at<double>(L.gst), c->stream));
   // network inputs (weights, case features), its prediction, the floored start
-  const double* dw = c->at<double>(L.stage) + (size_t)d.M * d.K;
-  const double* pts = dw + (size_t)d.K * 3;
+  const double* dw = c->at<double>(L.dwell);
+  const double* pts = c->at<double>(L.pts);
   GMCO_HIP(c, launch_features(dw, pts, c->at<int>(L.perm), c->at<int>(L.goff), c->at<int>(L.gcnt), d.K, c->O,
                               c->at<unsigned>(L.hist), c->at<float>(L.feat), c->stream));
   GMCO_HIP(c, launch_learned_inputs(c->at<double>(L.W64), c->at<float>(L.feat), P, c->O, c->at<float>(L.mlpX),
@@ -813,12 +950,17 @@ int gmco_optimize(gmco_ctx* c, const gmco_run* r, gmco_run_info* info) {
   }
   while (harvested < timed) GMCO_HIP(c, harvest());
   GMCO_HIP(c, hipEventRecord(c->ev1, c->stream));
-  GMCO_HIP(c, hipEventSynchronize(c->ev1));
-  unsigned long long done[2] = {0, 0};
-  GMCO_HIP(c, hipMemcpy(done, work, sizeof(done), hipMemcpyDeviceToHost));
+  const size_t ps_bytes = (size_t)c->P * sizeof(PlanState);
+  Staging st(ps_bytes + 16, c->stream);
+  GMCO_STAGED(c, st);
+  GMCO_HIP(c, hipMemcpyAsync(st.at<void>(0), c->at<void>(L.ps), ps_bytes, hipMemcpyDeviceToHost, c->stream));
+  GMCO_HIP(c, hipMemcpyAsync(st.at<void>(ps_bytes), work, 16, hipMemcpyDeviceToHost, c->stream));
+  GMCO_HIP(c, hipStreamSynchronize(c->stream));
+  st.settled = true;
+  const unsigned long long* done = st.at<unsigned long long>(ps_bytes);
   float ms = 0.f;
   GMCO_HIP(c, hipEventElapsedTime(&ms, c->ev0, c->ev1));
-  rc = summarize(c, round, ms, eval_ms, update_ms, done[0], info);
+  rc = summarize(c, round, ms, eval_ms, update_ms, done[0], st.at<PlanState>(0), info);
   if (info) {
     info->timed_launches = timed;
     info->timed_work = (double)done[1] / (double)c->P;
@@ -1044,10 +1186,27 @@ int gmco_optimize_many(gmco_ctx* const* ctxs, int n, const gmco_run* r, gmco_run
   float ms = 0.f;
   GMCO_HIP(c0, hipEventElapsedTime(&ms, c0->ev0, c0->ev1));
   int status = GMCO_OK;
+  size_t bytes = 0;
+  std::vector<size_t> at(n);
   for (int i = 0; i < n; ++i) {
-    unsigned long long done = 0;
-    GMCO_HIP(ctxs[i], hipMemcpy(&done, ctxs[i]->at<void>(ctxs[i]->lay.work), sizeof(done), hipMemcpyDeviceToHost));
-    const int rc = summarize(ctxs[i], round, ms, 0.0, 0.0, done, infos ? &infos[i] : nullptr);
+    at[i] = bytes;
+    bytes += (size_t)ctxs[i]->P * sizeof(PlanState) + 64;  // the plans' states, then the work count
+  }
+  Staging sg(bytes, st);
+  GMCO_STAGED(c0, sg);
+  for (int i = 0; i < n; ++i) {
+    const size_t ps_bytes = (size_t)ctxs[i]->P * sizeof(PlanState);
+    GMCO_HIP(ctxs[i], hipMemcpyAsync(sg.at<void>(at[i]), ctxs[i]->at<void>(ctxs[i]->lay.ps), ps_bytes,
+                                     hipMemcpyDeviceToHost, st));
+    GMCO_HIP(ctxs[i], hipMemcpyAsync(sg.at<void>(at[i] + ps_bytes), ctxs[i]->at<void>(ctxs[i]->lay.work), 8,
+                                     hipMemcpyDeviceToHost, st));
+  }
+  GMCO_HIP(c0, hipStreamSynchronize(st));
+  sg.settled = true;
+  for (int i = 0; i < n; ++i) {
+    const size_t ps_bytes = (size_t)ctxs[i]->P * sizeof(PlanState);
+    const int rc = summarize(ctxs[i], round, ms, 0.0, 0.0, *sg.at<unsigned long long>(at[i] + ps_bytes),
+                             sg.at<PlanState>(at[i]), infos ? &infos[i] : nullptr);
     if (rc && !status) status = rc;
   }
   return status;
@@ -1341,29 +1500,44 @@ int gmco_set_state(gmco_ctx* c, const void* blob, size_t bytes) {
   return GMCO_OK;
 }
 
+}  // extern "C"
+
+namespace {
+// x of every plan, row by row to emit(plan, first dwell weight)
+template <class F>
+int each_x(gmco_ctx* c, F emit) {
+  GMCO_HIP(c, hipSetDevice(c->device));
+  const size_t bytes = (size_t)c->P * c->dim.Kp * 4;
+  Staging st(bytes, c->stream);
+  GMCO_STAGED(c, st);
+  GMCO_HIP(c, hipMemcpyAsync(st.at<void>(0), c->at<void>(c->lay.x), bytes, hipMemcpyDeviceToHost, c->stream));
+  GMCO_HIP(c, hipStreamSynchronize(c->stream));
+  st.settled = true;
+  for (int p = 0; p < c->P; ++p) emit(p, st.at<float>((size_t)p * c->dim.Kp * 4));
+  return GMCO_OK;
+}
+}  // namespace
+
+extern "C" {
+
 int gmco_get_dwell_times(gmco_ctx* c, double* t) {
   if (!c || !t) return GMCO_EINVAL;
   if (!c->case_loaded || c->P == 0) return fail(c, GMCO_ESTATE, "gmco_set_weights first");
-  GMCO_HIP(c, hipSetDevice(c->device));
   const int K = c->dim.K;
-  double* tst = c->at<double>(c->lay.gst);
-  GMCO_HIP(c, launch_export_t(c->at<float>(c->lay.x), c->P, K, c->dim.Kp, tst, K, c->stream));
-  GMCO_HIP(c, hipMemcpyAsync(t, tst, (size_t)c->P * K * 8, hipMemcpyDeviceToHost, c->stream));
-  GMCO_HIP(c, hipStreamSynchronize(c->stream));
-  return GMCO_OK;
+  return each_x(c, [&](int p, const float* x) {
+    double* row = t + (size_t)p * K;
+    for (int l = 0; l < K; ++l) row[l] = (double)x[l] * (double)x[l];
+  });
 }
 
 int gmco_get_weights_x(gmco_ctx* c, double* x) {
   if (!c || !x) return GMCO_EINVAL;
   if (!c->case_loaded || c->P == 0) return fail(c, GMCO_ESTATE, "gmco_set_weights first");
-  GMCO_HIP(c, hipSetDevice(c->device));
-  const int K = c->dim.K, Kp = c->dim.Kp;
-  std::vector<float> xs((size_t)c->P * Kp);
-  GMCO_HIP(c, hipMemcpyAsync(xs.data(), c->at<void>(c->lay.x), xs.size() * 4, hipMemcpyDeviceToHost, c->stream));
-  GMCO_HIP(c, hipStreamSynchronize(c->stream));
-  for (int p = 0; p < c->P; ++p)
-    for (int l = 0; l < K; ++l) x[(size_t)p * K + l] = xs[(size_t)p * Kp + l];
-  return GMCO_OK;
+  const int K = c->dim.K;
+  return each_x(c, [&](int p, const float* xp) {
+    double* row = x + (size_t)p * K;
+    for (int l = 0; l < K; ++l) row[l] = (double)xp[l];
+  });
 }
 
 }  // extern "C"
@@ -1429,11 +1603,15 @@ int gmco_select_plan(gmco_ctx* c, const gmco_select_opts* opts, int* best, int* 
   int* nd = tu + Pp;
   int* res = nd + Pp;
   GMCO_HIP(c, launch_select(c->at<gmco_plan_metrics>(c->lay.metrics), P, c->O, o, cls, tu, nd, res, c->stream));
-  int h[2] = {0, 0};
-  GMCO_HIP(c, hipMemcpyAsync(h, res, 8, hipMemcpyDeviceToHost, c->stream));
-  if (plan_class) GMCO_HIP(c, hipMemcpyAsync(plan_class, cls, (size_t)P * 4, hipMemcpyDeviceToHost, c->stream));
-  if (nondominated) GMCO_HIP(c, hipMemcpyAsync(nondominated, nd, (size_t)P * 4, hipMemcpyDeviceToHost, c->stream));
+  const size_t bytes = (size_t)Pp * 12 + 8;  // classes, (criteria met), dominance, result
+  Staging st(bytes, c->stream);
+  GMCO_STAGED(c, st);
+  GMCO_HIP(c, hipMemcpyAsync(st.at<void>(0), cls, bytes, hipMemcpyDeviceToHost, c->stream));
   GMCO_HIP(c, hipStreamSynchronize(c->stream));
+  st.settled = true;
+  const int* h = st.at<int>((size_t)Pp * 12);
+  if (plan_class) std::memcpy(plan_class, st.at<int>(0), (size_t)P * 4);
+  if (nondominated) std::memcpy(nondominated, st.at<int>((size_t)Pp * 8), (size_t)P * 4);
   if (best) *best = h[0];
   if (nondominated_fraction) *nondominated_fraction = (double)h[1] / (double)P;
   return GMCO_OK;
@@ -1446,9 +1624,13 @@ int gmco_get_metrics(gmco_ctx* c, gmco_plan_metrics* out) {
   const Layout& L = c->lay;
   const int rc = compute_metrics(c);
   if (rc) return rc;
-  GMCO_HIP(c, hipMemcpyAsync(out, c->at<void>(L.metrics), (size_t)c->P * sizeof(gmco_plan_metrics),
-                             hipMemcpyDeviceToHost, c->stream));
+  const size_t bytes = (size_t)c->P * sizeof(gmco_plan_metrics);
+  Staging st(bytes, c->stream);
+  GMCO_STAGED(c, st);
+  GMCO_HIP(c, hipMemcpyAsync(st.at<void>(0), c->at<void>(L.metrics), bytes, hipMemcpyDeviceToHost, c->stream));
   GMCO_HIP(c, hipStreamSynchronize(c->stream));
+  st.settled = true;
+  std::memcpy(out, st.at<void>(0), bytes);
   return GMCO_OK;
 }
 
@@ -1512,9 +1694,8 @@ int gmco_case_features(gmco_ctx* c, float* out) {
   GMCO_HIP(c, hipSetDevice(c->device));
   const Layout& L = c->lay;
   const Dims& d = c->dim;
-  double* stage = c->at<double>(L.stage);
-  const double* dw = stage + (size_t)d.M * d.K;
-  const double* pts = dw + (size_t)d.K * 3;
+  const double* dw = c->at<double>(L.dwell);
+  const double* pts = c->at<double>(L.pts);
   GMCO_HIP(c, launch_features(dw, pts, c->at<int>(L.perm), c->at<int>(L.goff), c->at<int>(L.gcnt), d.K,
                               c->O, c->at<unsigned>(L.hist), c->at<float>(L.feat), c->stream));
   GMCO_HIP(c, hipMemcpyAsync(out, c->at<void>(L.feat), (size_t)c->O * 16 * 4, hipMemcpyDeviceToHost, c->stream));

@@ -186,15 +186,17 @@ hipError_t launch_update(const UpdateArgs& a, hipStream_t st);
 hipError_t launch_finish_eval(const float* Gpart, const double* Fpart, const float* x, int S,
                               int P, int Pp, int K, int Kp, double* F, double* g,
                               hipStream_t st);
+// (the gradient as computed, in FP32)
+hipError_t launch_finish_eval_f32(const float* Gpart, const double* Fpart, const float* x, int S,
+                                  int P, int Pp, int K, int Kp, double* F, float* g,
+                                  hipStream_t st);
 // Resumes stopped plans, sets every plan's flag and clears the running
 // counts and the work counts of the call.
 hipError_t launch_resume(PlanState* ps, const float* x, float* xt, int* flag, int* active,
                          unsigned long long* work, int Pp, int Kp, int max_iter, int resume_stopped,
                          hipStream_t st);
-hipError_t launch_export_t(const float* x, int P, int K, int Kp, double* t64, int Kp_out,
-                           hipStream_t st);
-hipError_t launch_x_to_device(const double* x_host_dev, int P, int Pp, int K, int Kp, float* xe,
-                              hipStream_t st);
+hipError_t launch_x_to_device(const double* x, int P, int Pp, int K, int Kp, float* xe, hipStream_t st);
+hipError_t launch_x32_to_device(const float* x, int P, int Pp, int K, int Kp, float* xe, hipStream_t st);
 // FP64 doses d64 (P rows of stride Mp) of the first P plans at t = x^2
 hipError_t launch_dose64(const double* D64, const float* x, int Mp, int K, int Kp, int P, double* d64,
                          hipStream_t st);

@@ -550,12 +550,12 @@ hipError_t launch_update_grouped_e(const UpdateArgs* args, int n, int P_max, int
 // from 86 to 82 us; the same bits.
 constexpr int kFinishDirect = 48;
 
-template <int NW>
+template <int NW, class T>
 __global__ __launch_bounds__(64 * NW) void k_finish_eval(const float* __restrict__ Gpart,
                                                          const double* __restrict__ Fpart,
                                                          const float* __restrict__ x, int S, int P, int Pp,
                                                          int K, int Kp, double* __restrict__ F,
-                                                         double* __restrict__ g) {
+                                                         T* __restrict__ g) {
   constexpr int U = 16;  // loads in flight per lane
   __shared__ float sG[NW > 1 ? NW * U : 1][64];
   __shared__ double sF[NW > 1 ? NW * U : 1];
@@ -603,7 +603,7 @@ __global__ __launch_bounds__(64 * NW) void k_finish_eval(const float* __restrict
       }
     }
   }
-  if (wave == 0 && in) g[(size_t)p * K + l] = (double)(4.f * xv * G);
+  if (wave == 0 && in) g[(size_t)p * K + l] = (T)(4.f * xv * G);
   if (with_f && lane == 0 && wave == (NW == 1 ? 0 : 1)) F[p] = f;
 }
 
@@ -648,15 +648,29 @@ hipError_t launch_update_grouped(const UpdateArgs* args, int n, int E, int P_max
   return hipErrorInvalidValue;
 }
 
+namespace {
+template <class T>
+hipError_t finish_eval(const float* Gpart, const double* Fpart, const float* x, int S, int P, int Pp, int K, int Kp,
+                       double* F, T* g, hipStream_t st) {
+  const dim3 grid((K + 63) / 64, P);
+  if (S <= kFinishDirect)
+    hipLaunchKernelGGL((k_finish_eval<1, T>), grid, dim3(64), 0, st, Gpart, Fpart, x, S, P, Pp, K, Kp, F, g);
+  else
+    hipLaunchKernelGGL((k_finish_eval<8, T>), grid, dim3(512), 0, st, Gpart, Fpart, x, S, P, Pp, K, Kp, F, g);
+  return hipGetLastError();
+}
+}  // namespace
+
 hipError_t launch_finish_eval(const float* Gpart, const double* Fpart, const float* x, int S,
                               int P, int Pp, int K, int Kp, double* F, double* g,
                               hipStream_t st) {
-  const dim3 grid((K + 63) / 64, P);
-  if (S <= kFinishDirect)
-    hipLaunchKernelGGL((k_finish_eval<1>), grid, dim3(64), 0, st, Gpart, Fpart, x, S, P, Pp, K, Kp, F, g);
-  else
-    hipLaunchKernelGGL((k_finish_eval<8>), grid, dim3(512), 0, st, Gpart, Fpart, x, S, P, Pp, K, Kp, F, g);
-  return hipGetLastError();
+  return finish_eval(Gpart, Fpart, x, S, P, Pp, K, Kp, F, g, st);
+}
+
+hipError_t launch_finish_eval_f32(const float* Gpart, const double* Fpart, const float* x, int S,
+                                  int P, int Pp, int K, int Kp, double* F, float* g,
+                                  hipStream_t st) {
+  return finish_eval(Gpart, Fpart, x, S, P, Pp, K, Kp, F, g, st);
 }
 
 hipError_t launch_resume(PlanState* ps, const float* x, float* xt, int* flag, int* active,

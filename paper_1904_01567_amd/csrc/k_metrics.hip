@@ -5,20 +5,6 @@
 namespace gmco {
 namespace {
 
-__global__ void k_export_t(const float* __restrict__ x, int P, int K, int Kp,
-                           double* __restrict__ t64, int Kp_out) {
-  const int p = blockIdx.x;
-  if (p >= P) return;
-  for (int l = threadIdx.x; l < Kp_out; l += blockDim.x) {
-    double v = 0.0;
-    if (l < K) {
-      const double xv = (double)x[(size_t)p * Kp + l];
-      v = xv * xv;
-    }
-    t64[(size_t)p * Kp_out + l] = v;
-  }
-}
-
 typedef double d4v __attribute__((ext_vector_type(4)));
 
 // d64[p][i] = sum_l D64[i][l] x[p][l]^2 on the 16x16x4 FP64 matrix op, bound
@@ -496,12 +482,6 @@ hipError_t launch_select(const gmco_plan_metrics* m, int P, int G, const gmco_se
   const hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
   hipLaunchKernelGGL(k_select, dim3(1), dim3(1024), 0, st, m, cls, meets_tu, nd, P, o, out);
-  return hipGetLastError();
-}
-
-hipError_t launch_export_t(const float* x, int P, int K, int Kp, double* t64, int Kp_out,
-                           hipStream_t st) {
-  hipLaunchKernelGGL(k_export_t, dim3(P), dim3(128), 0, st, x, P, K, Kp, t64, Kp_out);
   return hipGetLastError();
 }
 

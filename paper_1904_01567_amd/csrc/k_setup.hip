@@ -252,9 +252,9 @@ __global__ void k_init_plans(int P, int Pp, int K, int Kp, const double* __restr
   }
 }
 
-// Dwell weights given by the caller (FP64, P x K) into the padded FP32 layout.
-__global__ void k_x_to_device(const double* __restrict__ xin, int P, int K, int Kp,
-                              float* __restrict__ xe) {
+// Dwell weights given by the caller (P x K) into the padded FP32 layout.
+template <class T>
+__global__ void k_x_to_device(const T* __restrict__ xin, int P, int K, int Kp, float* __restrict__ xe) {
   const int p = blockIdx.x;
   for (int l = threadIdx.x; l < Kp; l += blockDim.x)
     xe[(size_t)p * Kp + l] = (p < P && l < K) ? (float)xin[(size_t)p * K + l] : 0.f;
@@ -404,9 +404,13 @@ hipError_t launch_init_plans(int P, int Pp, int K, int Kp, const double* t0, con
   return hipGetLastError();
 }
 
-hipError_t launch_x_to_device(const double* x_host_dev, int P, int Pp, int K, int Kp, float* xe,
-                              hipStream_t st) {
-  hipLaunchKernelGGL(k_x_to_device, dim3(Pp), dim3(128), 0, st, x_host_dev, P, K, Kp, xe);
+hipError_t launch_x_to_device(const double* x, int P, int Pp, int K, int Kp, float* xe, hipStream_t st) {
+  hipLaunchKernelGGL((k_x_to_device<double>), dim3(Pp), dim3(128), 0, st, x, P, K, Kp, xe);
+  return hipGetLastError();
+}
+
+hipError_t launch_x32_to_device(const float* x, int P, int Pp, int K, int Kp, float* xe, hipStream_t st) {
+  hipLaunchKernelGGL((k_x_to_device<float>), dim3(Pp), dim3(128), 0, st, x, P, K, Kp, xe);
   return hipGetLastError();
 }
 

@@ -210,3 +210,32 @@ def test_metrics_of_equal_and_extreme_doses(scale):
     pl.load_case(c.dwell_xyz, None, c.group, PARAMS, c.volume_cc, 15.0, 0, dose_rate=D)
     pl.set_weights(W, t0)
     _check_metrics(pl, D, t0, c, W)
+
+
+# The test for finite values runs on blocks of 2,048; every place counts, and
+# the largest finite FP64 values pass it (they overflow FP32, so the objective
+# does not stay finite).
+def test_nonfinite_inputs_are_refused_at_every_place():
+    from paper_1904_01567_amd import GmcoError
+    announce("non-finite inputs")
+    c = cases.make_case(8, 16, (40, 10, 15, 15), seed=4)  # 128 dwells
+    W = cases.hidden_weights(40, seed=1)
+    pl = planner(c, W)
+    x = np.full((40, c.K), 0.1)
+    F0, g0 = pl.evaluate(x)
+    for at in (0, 2047, 2048, 4095, 40 * c.K - 1):
+        for bad in (np.inf, -np.inf, np.nan):
+            y = x.copy()
+            y.reshape(-1)[at] = bad
+            with pytest.raises(GmcoError) as e:
+                pl.evaluate(y)
+            assert e.value.code == -1 and "finite" in str(e.value)
+    y = x.copy()
+    y[3, 5] = -np.finfo(np.float64).max
+    y[4, 6] = np.finfo(np.float64).tiny / 8
+    F1, _ = pl.evaluate(y)
+    keep = np.arange(40) != 3
+    assert not np.isfinite(F1[3]) and np.all(np.isfinite(F1[keep]))
+    F2, g2 = pl.evaluate(x)  # a refused call leaves nothing behind
+    np.testing.assert_array_equal(F2, F0)
+    np.testing.assert_array_equal(g2, g0)
