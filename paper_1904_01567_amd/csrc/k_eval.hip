@@ -197,6 +197,273 @@ __device__ inline void stage_weights(const EvalArgs& a, const int* sPlan, float*
 // float4-chunk swizzle of row `row` of the FP64-accumulating kernel's LDS tile
 __device__ inline int swz_row(int row) { return (row >> 1) & 3; }
 
+// Few plans (at most 16 in the workgroup): the other plan groups' waves would
+// idle, one SIMD doing the work of four.  The D blocks of a workgroup's point
+// range are taken kFewF32 (3) or kFewAcc (2) at a time and all eight waves share
+// them: the dose product by block and accumulator chain, eq. 1 by block and row,
+// the back-projection by dwell slice, with three barriers per chunk.  The chains,
+// the order of blocks in every gradient element and of rows in the objective are
+// those of the full shapes, so the bits are the same.  The next chunk's loads fly
+// during the work.  16 plans are one column group of the matrix instructions:
+// from 17 on a second group has work of its own and the full shape's waves fill.
+// An evaluate call of 1 plan at 360 dwells x 20,000 points in FP32: 27.7 us by the
+// full shape, 20.0 by this one; of 8 plans at 160 x 2,400, FP64-accumulated: 13.0
+// and 11.9 (what is left there is three launches).
+constexpr int kFewPlans = 16;
+constexpr int kFewF32 = 3, kFewAcc = 2;
+
+// Chunk c of nblk blocks in chunks of at most NB of about equal size.
+template <int NB>
+__device__ inline int few_chunk(int nblk, int c) {
+  const int nch = (nblk + NB - 1) / NB;
+  return nch > 0 ? nblk * c / nch : 0;
+}
+
+template <int KP>
+__device__ inline void eval_f32_few(const EvalArgs& a, const Tile& t, float* sD, float* sX, float* sPh,
+                                    const float* sW, const float4* sP, const int* sPlan, int* sG) {
+  constexpr int NT = 512, NB = kFewF32;
+  constexpr int KS = KP + 4;
+  constexpr int NK16 = KP / 16;
+  constexpr int NKS = (NK16 + 7) / 8;
+  constexpr int NF4 = 4 * KP;
+  constexpr int NPF = (NB * NF4 + NT - 1) / NT;
+  const int tid = threadIdx.x;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int lane = tid & 63, q = lane >> 4, n = lane & 15;
+  const int part = wave & 1, dblk = wave >> 1;
+  const int nk_used = a.last16 ? NK16 : NK16 - 1;
+  const int b_begin = (int)(((long long)t.s * a.nblocks) / t.S);
+  const int nblk = (int)(((long long)(t.s + 1) * a.nblocks) / t.S) - b_begin;
+  const int nch = (nblk + NB - 1) / NB;
+  const f4v* __restrict__ Dg = reinterpret_cast<const f4v*>(a.D) + (size_t)b_begin * NF4;
+  f4v pf[NPF];
+  int gpre = 0;
+  auto prefetch = [&](int c) {  // (past the chunk's end: its last float4 again, not stored)
+    const int f0 = few_chunk<NB>(nblk, c), n4 = (few_chunk<NB>(nblk, c + 1) - f0) * NF4;
+#pragma unroll
+    for (int i = 0; i < NPF; ++i) pf[i] = Dg[(size_t)f0 * NF4 + min(tid + NT * i, n4 - 1)];
+    if (tid < n4 / NF4 * kBM) gpre = a.grp[(b_begin + f0) * kBM + tid];
+  };
+  if (nch > 0) prefetch(0);
+  const int plan = sPlan[n];
+  const bool pv = plan >= 0;  // an empty column evaluates t = 0 with zero weights
+  const float* __restrict__ xrow = a.x + (size_t)(pv ? plan : 0) * KP + 4 * q + part;
+  float tf[2 * NK16];  // of chain `part`: dwells 16 k + 4 q + part and + 2
+#pragma unroll
+  for (int k = 0; k < NK16; ++k) {
+    const float x0 = xrow[16 * k], x1 = xrow[16 * k + 2];
+    tf[2 * k] = pv ? x0 * x0 : 0.f;
+    tf[2 * k + 1] = pv ? x1 * x1 : 0.f;
+  }
+  f4v gacc[NKS];
+#pragma unroll
+  for (int i = 0; i < NKS; ++i) gacc[i] = f4v{0.f, 0.f, 0.f, 0.f};
+  double facc = 0.0;
+  for (int c = 0; c < nch; ++c) {
+    const int nb = few_chunk<NB>(nblk, c + 1) - few_chunk<NB>(nblk, c);
+#pragma unroll
+    for (int i = 0; i < NPF; ++i) {
+      const int idx = tid + NT * i;
+      if (idx < nb * NF4) {
+        const int row = idx / (KP / 4);  // of the chunk: blocks follow each other
+        *reinterpret_cast<f4v*>(&sD[row * KS + 4 * (idx - row * (KP / 4))]) = pf[i];
+      }
+    }
+    if (tid < nb * kBM) sG[tid] = gpre;
+    __syncthreads();
+    if (c + 1 < nch) prefetch(c + 1);
+    if (dblk < nb) {
+      const float* __restrict__ Dc = sD + dblk * kBM * KS;
+      f4v acc = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+      for (int k = 0; k < NK16; ++k) {
+        if (k == NK16 - 1 && nk_used < NK16) continue;
+        const float4 av = *reinterpret_cast<const float4*>(&Dc[n * KS + 16 * k + 4 * q]);
+        acc = mfma_f32(part ? av.y : av.x, tf[2 * k], acc);
+        acc = mfma_f32(part ? av.w : av.z, tf[2 * k + 1], acc);
+      }
+#pragma unroll
+      for (int r = 0; r < 4; ++r) sX[((part * NB + dblk) * 4 + r) * 64 + lane] = acc[r];
+    }
+    __syncthreads();
+    for (int id = wave; id < 4 * nb; id += 8) {  // (block, row)
+      const float d = sX[id * 64 + lane] + sX[(NB * 4 + id) * 64 + lane];
+      const int gi = sG[(id >> 2) * kBM + 4 * q + (id & 3)];
+      const float4 pr = sP[gi];
+      const float w = (gi < kGmax) ? sW[n * kGmax + gi] : 0.f;
+      const float lo = fminf(d - pr.y, 0.f);
+      const float hi = fmaxf(d - pr.z, 0.f);
+      const float kap = pr.x * lo + pr.w * hi;
+      sX[id * 64 + lane] = w * (kap * (lo + hi));
+      sPh[id * 64 + lane] = w * kap;
+    }
+    __syncthreads();
+    if (wave == 0)
+      for (int id = 0; id < 4 * nb; ++id) facc += (double)sX[id * 64 + lane];
+    for (int b = 0; b < nb; ++b) {
+      const float* __restrict__ Dp = sD + b * kBM * KS;
+      float phi[4];
+#pragma unroll
+      for (int r = 0; r < 4; ++r) phi[r] = sPh[(4 * b + r) * 64 + lane];
+      if (!wave_any_nonzero(phi)) continue;
+#pragma unroll
+      for (int i = 0; i < NKS; ++i) {
+        const int k = wave + 8 * i;
+        if (k >= nk_used) continue;
+#pragma unroll
+        for (int r = 0; r < 4; ++r) gacc[i] = mfma_f32(Dp[(4 * q + r) * KS + 16 * k + n], phi[r], gacc[i]);
+      }
+    }
+    __syncthreads();
+  }
+  if (wave == 0) {
+    facc += __shfl_xor(facc, 16);
+    facc += __shfl_xor(facc, 32);
+    if (q == 0 && pv) a.Fpart[(size_t)t.s * t.stride + t.j0 + n] = facc;
+  }
+  if (!pv) return;
+  float* __restrict__ gout = a.Gpart + ((size_t)t.s * t.stride + t.j0 + n) * KP + 4 * q;
+#pragma unroll
+  for (int i = 0; i < NKS; ++i) {
+    const int k = wave + 8 * i;
+    if (k < NK16)
+      *reinterpret_cast<float4*>(gout + 16 * k) = make_float4(gacc[i][0], gacc[i][1], gacc[i][2], gacc[i][3]);
+  }
+}
+
+// The same with the FP64-accumulated dose: the eight accumulator chains of a
+// block (four per dwell half) by four waves, two chains each.
+template <int KP>
+__device__ inline void eval_acc64_few(const EvalArgs& a, const Tile& t, float* sD, double* sX, float* sPh,
+                                      const float* sW, const double* sP64, const int* sPlan, int* sG) {
+  constexpr int NT = 512, NB = kFewAcc;
+  constexpr int KS = KP + 16;
+  constexpr int NK = KP / 16, NKH = NK / 2;
+  constexpr int NKS = (NK + 7) / 8;
+  constexpr int NF4 = 4 * KP;
+  constexpr int NPF = (NB * NF4 + NT - 1) / NT;
+  const int tid = threadIdx.x;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int lane = tid & 63, q = lane >> 4, n = lane & 15;
+  const int part = wave & 3, half = part >> 1, pr = part & 1, dblk = wave >> 2;
+  const int nk_used = a.last16 ? NK : NK - 1;
+  const int b_begin = (int)(((long long)t.s * a.nblocks) / t.S);
+  const int nblk = (int)(((long long)(t.s + 1) * a.nblocks) / t.S) - b_begin;
+  const int nch = (nblk + NB - 1) / NB;
+  const f4v* __restrict__ Dg = reinterpret_cast<const f4v*>(a.D) + (size_t)b_begin * NF4;
+  f4v pf[NPF];
+  int gpre = 0;
+  auto prefetch = [&](int c) {  // (past the chunk's end: its last float4 again, not stored)
+    const int f0 = few_chunk<NB>(nblk, c), n4 = (few_chunk<NB>(nblk, c + 1) - f0) * NF4;
+#pragma unroll
+    for (int i = 0; i < NPF; ++i) pf[i] = Dg[(size_t)f0 * NF4 + min(tid + NT * i, n4 - 1)];
+    if (tid < n4 / NF4 * kBM) gpre = a.grp[(b_begin + f0) * kBM + tid];
+  };
+  if (nch > 0) prefetch(0);
+  const int plan = sPlan[n];
+  const bool pv = plan >= 0;  // an empty column evaluates t = 0 with zero weights
+  const float* __restrict__ xrow = a.x + (size_t)(pv ? plan : 0) * KP + half * (KP / 2) + 4 * q + 2 * pr;
+  float tf[2 * NKH];  // of the chains 2 pr and 2 pr + 1 of the half
+#pragma unroll
+  for (int k = 0; k < NKH; ++k) {
+    const float2 xv = *reinterpret_cast<const float2*>(xrow + 16 * k);
+    tf[2 * k] = pv ? xv.x * xv.x : 0.f;
+    tf[2 * k + 1] = pv ? xv.y * xv.y : 0.f;
+  }
+  f4v gacc[NKS];
+#pragma unroll
+  for (int i = 0; i < NKS; ++i) gacc[i] = f4v{0.f, 0.f, 0.f, 0.f};
+  double facc = 0.0;  // waves 0 and 1: rows 0-1 and 2-3
+  for (int c = 0; c < nch; ++c) {
+    const int nb = few_chunk<NB>(nblk, c + 1) - few_chunk<NB>(nblk, c);
+#pragma unroll
+    for (int i = 0; i < NPF; ++i) {
+      const int idx = tid + NT * i;
+      if (idx < nb * NF4) {
+        const int row = idx / (KP / 4);  // of the chunk: blocks follow each other
+        const int c4 = idx - row * (KP / 4);
+        *reinterpret_cast<f4v*>(&sD[row * KS + 4 * (c4 ^ swz_row(row & (kBM - 1)))]) = pf[i];
+      }
+    }
+    if (tid < nb * kBM) sG[tid] = gpre;
+    __syncthreads();
+    if (c + 1 < nch) prefetch(c + 1);
+    if (dblk < nb) {
+      const float* __restrict__ Dc = sD + dblk * kBM * KS;
+      d4v acc0 = {0.0, 0.0, 0.0, 0.0}, acc1 = acc0;
+#pragma unroll
+      for (int k = 0; k < NKH; ++k) {
+        const int kg = half * NKH + k;
+        if (k == NKH - 1 && kg >= nk_used) continue;
+        const float2 av = *reinterpret_cast<const float2*>(&Dc[n * KS + 16 * kg + 4 * (q ^ swz_row(n)) + 2 * pr]);
+        acc0 = mfma_f64(av.x, tf[2 * k], acc0);
+        acc1 = mfma_f64(av.y, tf[2 * k + 1], acc1);
+      }
+#pragma unroll
+      for (int r = 0; r < 4; ++r) sX[((part * NB + dblk) * 4 + r) * 64 + lane] = acc0[r] + acc1[r];
+    }
+    __syncthreads();
+    if (wave < 4 * nb) {  // (block, row)
+      const int id = wave, r = id & 3;
+      constexpr int PS = NB * 4 * 64;
+      double* x = sX + id * 64 + lane;
+      const double d = (x[0] + x[PS]) + (x[2 * PS] + x[3 * PS]);
+      const int gi = sG[(id >> 2) * kBM + q + 4 * r];
+      const float w = (gi < kGmax) ? sW[n * kGmax + gi] : 0.f;
+      const double* p = sP64 + 4 * gi;
+      const double lo = fmin(d - p[1], 0.0);
+      const double hi = fmax(d - p[2], 0.0);
+      const double kap = p[0] * lo + p[3] * hi;
+      x[0] = kap * (lo + hi);
+      sPh[id * 64 + lane] = (float)((double)w * kap);
+    }
+    __syncthreads();
+    if (wave < 2) {
+      for (int b = 0; b < nb; ++b)
+#pragma unroll
+        for (int rr = 0; rr < 2; ++rr) {
+          const int r = 2 * wave + rr;
+          const int gi = sG[b * kBM + q + 4 * r];
+          const float w = (gi < kGmax) ? sW[n * kGmax + gi] : 0.f;
+          facc += (double)w * sX[(4 * b + r) * 64 + lane];
+        }
+    }
+    for (int b = 0; b < nb; ++b) {
+      const float* __restrict__ Dp = sD + b * kBM * KS;
+      float phi[4];
+#pragma unroll
+      for (int r = 0; r < 4; ++r) phi[r] = sPh[(4 * b + r) * 64 + lane];
+      if (!wave_any_nonzero(phi)) continue;
+#pragma unroll
+      for (int i = 0; i < NKS; ++i) {
+        const int k = wave + 8 * i;
+        if (k >= nk_used) continue;
+#pragma unroll
+        for (int r = 0; r < 4; ++r)
+          gacc[i] = mfma_f32(Dp[(q + 4 * r) * KS + 16 * k + (n ^ (swz_row(q + 4 * r) << 2))], phi[r], gacc[i]);
+      }
+    }
+    __syncthreads();
+  }
+  if (wave == 1) sX[lane] = facc;
+  __syncthreads();
+  if (wave == 0) {
+    facc += sX[lane];
+    facc += __shfl_xor(facc, 16);
+    facc += __shfl_xor(facc, 32);
+    if (q == 0 && pv) a.Fpart[(size_t)t.s * t.stride + t.j0 + n] = facc;
+  }
+  if (!pv) return;
+  float* __restrict__ gout = a.Gpart + ((size_t)t.s * t.stride + t.j0 + n) * KP + 4 * q;
+#pragma unroll
+  for (int i = 0; i < NKS; ++i) {
+    const int k = wave + 8 * i;
+    if (k < NK)
+      *reinterpret_cast<float4*>(gout + 16 * k) = make_float4(gacc[i][0], gacc[i][1], gacc[i][2], gacc[i][3]);
+  }
+}
+
 // MODE_F32    : FP32 operands, FP32 accumulation (v_mfma_f32_16x16x4_f32).
 // MODE_CHUNK64: FP32 matrix ops sum 16 dwells at a time from zero; those
 //               partial doses are accumulated in FP64 on the vector ALU and
@@ -413,11 +680,13 @@ __device__ inline void eval_f32_ws(const EvalArgs& a, int bid) {
 
   __shared__ __attribute__((aligned(16))) float sD[3][kBM * KS];
   __shared__ float sPhi[2][NG][4][64];  // phi of a block [buffer][group][r][lane]
+  __shared__ float sFew[kFewF32 * 4 * 64];
   __shared__ float sW[kPT * kGmax];
   __shared__ int sPlan[kPT];
   __shared__ int sScan[NT / 64];
   __shared__ float4 sP[kGmax + 1];
   __shared__ int sG[3][kBM];
+  static_assert(kFewF32 == 3 && 2 * kFewF32 <= 2 * NG, "the few-plan form's chunk fits these arrays");
 
   const int tid = threadIdx.x;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);  // uniform per wavefront
@@ -429,6 +698,12 @@ __device__ inline void eval_f32_ws(const EvalArgs& a, int bid) {
 
   Tile t;
   if (!tile_setup<NT, kPT>(a, bid, sPlan, sScan, t)) return;
+  if (t.nval <= kFewPlans) {
+    stage_weights<NT, kFewPlans>(a, sPlan, sW);
+    stage_params<NT>(a, &sP[0].x);
+    eval_f32_few<KP>(a, t, &sD[0][0], &sPhi[0][0][0][0], sFew, sW, sP, sPlan, &sG[0][0]);
+    return;
+  }
   const int s = t.s, S = t.S, stride = t.stride, j0 = t.j0;
   const int col = grp * 16 + n;
   const int b_begin = (int)(((long long)s * a.nblocks) / S);
@@ -614,6 +889,15 @@ __device__ inline void eval_acc64(const EvalArgs& a, int bid) {
 
   Tile t;
   if (!tile_setup<NT, NCOL>(a, bid, sPlan, sScan, t)) return;
+  if constexpr (NG == 4 && NH == 2) {
+    static_assert(kFewAcc == 2, "the few-plan form's chunk fits sD, sX and sPhi");
+    if (t.nval <= kFewPlans) {
+      stage_weights<NT, kFewPlans>(a, sPlan, sW);
+      stage_params<NT>(a, &sP64[0][0]);
+      eval_acc64_few<KP>(a, t, &sD[0][0], &sX[0][0][0][0], &sPhi[0][0][0], sW, &sP64[0][0], sPlan, &sG[0][0]);
+      return;
+    }
+  }
   const int s = t.s, S = t.S, stride = t.stride, j0 = t.j0;
   const int b_begin = (int)(((long long)s * a.nblocks) / S);
   const int b_end = (int)(((long long)(s + 1) * a.nblocks) / S);

@@ -63,6 +63,37 @@ def test_update_forms_agree_bitwise(n_cath, n_dw, M, m):
         np.testing.assert_array_equal(a, b)
 
 
+# At most 16 plans in a workgroup take the form that shares a chunk of three
+# (FP32) or two (FP64-accumulated) point blocks among all waves; the chains and
+# the order of every sum are those of the form for more plans, so the same plans
+# alone and among others give the same bits.  Sizes: one dwell slice and more
+# than eight, ranges of one block, of whole chunks and of a remainder, batches
+# that fill the group, leave it ragged, and end in a second tile of few plans.
+@pytest.mark.parametrize("n_cath,n_dw,M", [(1, 5, 15), (3, 11, 75), (5, 13, 160), (18, 20, 1005), (20, 20, 4096),
+                                           (20, 25, 333)])
+@pytest.mark.parametrize("dtype", ["f32", "f32acc64"])
+def test_few_plans_agree_bitwise(n_cath, n_dw, M, dtype):
+    announce(f"few plans K={n_cath * n_dw} M={M} {dtype}")
+    c = _case(n_cath, n_dw, M)
+    D = O.dose_rate_matrix(c.dwell_xyz, c.pt_xyz)
+    W = cases.hidden_weights(64, seed=6)
+    x = np.sqrt(O.uniform_start_time(D, c.group, 15.0)) * (0.2 + 1.6 * cases.uniform_draws((64, c.K), seed=7))
+    x[2] = 0.0
+    full = planner(c, W, dtype=dtype)
+    alone = [(P, planner(c, np.concatenate([np.tile(W[:1], (P // 64 * 64, 1)), W[:P % 64]]), dtype=dtype))
+             for P in (1, 5, 16, 17, 67)]
+    for s in (1, 2, 3, (M + 15) // 16 // 2):
+        if s < 1 or s > min(32, (M + 31) // 32 * 2):
+            continue
+        full.set_split(s)
+        F, g = full.evaluate(x)
+        for P, pl in alone:
+            pl.set_split(s)
+            Fp, gp = pl.evaluate(np.concatenate([x] * (P // 64) + [x[:P % 64]]))
+            np.testing.assert_array_equal(Fp[P // 64 * 64:], F[:P % 64])
+            np.testing.assert_array_equal(gp[P // 64 * 64:], g[:P % 64])
+
+
 # The set-up kernel takes 32 rows and 64 columns at a time; the row sums of the
 # start time start and end inside a block of rows when the target does not
 # come first.  Tolerances: the matrix within 8 FP64 roundings of the oracle's,
