@@ -9,6 +9,7 @@
 #include <cstring>
 #include <new>
 #include <string>
+#include <type_traits>
 #include <vector>
 
 #include "gmco_internal.h"
@@ -25,17 +26,21 @@ typedef __bf16 bf8v __attribute__((ext_vector_type(8)));
 //   DACT  dact = (G W) masked by act > 0: A contiguous in k, B in j;
 //   DW    dW = G^T act, contraction over the batch: A contiguous in i, B in j.
 // A workgroup of four wavefronts (2 x 2) computes a T x T tile.  Slices of 64
-// k are read along the contiguous dimension into registers, two slices ahead,
-// and staged in LDS as BF16 (two buffers, one barrier per slice).  The sizes of
-// this network leave every product bound by latency: few tiles, each a chain
-// of slices.  So T = 32 unless 64 x 64 tiles already fill the chip twice
-// (kGemmWide), and all weight gradients of a step are one launch.  The
+// k are read along the contiguous dimension into registers, four slices ahead
+// (two with T = 64), and staged in LDS as BF16, 16 bytes a store (two buffers,
+// one barrier per slice).  The sizes of this network leave every product bound
+// by latency: few tiles, each a chain of slices.  So T = 32 unless 64 x 64 tiles
+// already fill the chip twice (kGemmWide), all weight gradients of a step are
+// one launch, and what the epilogue reads is loaded before the chain.  The
 // contraction runs in ascending steps of 32 in every form and tile, so the
 // tile does not change a bit of the result.
 // Measured (batch 1,024, layers 68-256-256-256-360): 73 us per product with
-// 64 x 64 tiles, strided scalar loads and no prefetch, 11 products a step;
-// the training step went from 1,785 to 87 us (7 to 12 us per product, 21 for the
-// weight gradients with their Adam update).
+// 64 x 64 tiles, strided scalar loads and no prefetch, 11 products a step, 1,785
+// us.  With 32 x 32 tiles, two slices ahead, 2-byte stores and the bias sums' adds
+// each waiting for LDS: 8.6 (forward), 12.4 (with the loss), 6.5 (activations) and
+// 21.3 us (weights), a step 87.  Now 4.2, 7.2, 5.3 and 16.4, a step 59.  (Giving
+// each XCD a rectangle of the weight gradients' tiles, which halves what its L2
+// reads, changes nothing: 16.2.)
 enum { GEMM_FWD = 0, GEMM_FWD_MSE = 1, GEMM_DACT = 2, GEMM_DW = 3, GEMM_DW_ADAM = 4 };
 
 struct AdamArgs {
@@ -72,37 +77,95 @@ __device__ inline void adam_update(float gi, float& p, float& m, float& v, const
   p -= a.lr * (m / a.c1) / (sqrtf(v / a.c2) + a.eps);
 }
 
-// One slice of an operand, T rows (i or j) x 64 k, into registers.  KC: the
-// stored rows are this operand's rows, contiguous in k (row r at rows[r] if
-// given); otherwise the stored rows are k, contiguous in the operand's rows.
-template <int T, bool KC>
-__device__ inline void gemm_load(const float* __restrict__ src, const int* __restrict__ rows, int ld, int r0, int R,
-                                 int k0, int K, int tid, float (&v)[T * kKS / 256]) {
+// A thread's share of the slices of an operand, T rows (i or j) x 64 k: NU
+// groups of 8 consecutive k of one row, so that a group is one 16-byte store to
+// LDS.  KC: the stored rows are this operand's rows, contiguous in k (row r at
+// rows[r] if given), by 16-byte loads if WIDE (rows of whole, aligned float4);
+// otherwise the stored rows are k, contiguous in the operand's rows: a scalar
+// address for each and one 32-bit offset per thread.  Places past the matrix
+// read its last row or column: a load inside a branch that issues none on its
+// other side would make every wait for an older one a wait for all (the count
+// of those in flight is then unknown to the compiler).  Past K they are staged
+// as zero; past the rows they reach only results that are not stored.
+template <int T, bool KC, bool WIDE>
+struct Operand {
+  static constexpr int NU = T * kKS / 8 / 256;
+  const float* src;
+  const float* base[NU];  // KC: the row
+  unsigned off[NU];       // otherwise: bytes from the slice's first stored row
+  int r0, R, K, ld;
+
+  __device__ static int row(int u) { return KC ? (threadIdx.x + 256 * u) / 8 : (threadIdx.x + 256 * u) % T; }
+  __device__ static int kgrp(int u) { return KC ? (threadIdx.x + 256 * u) % 8 : (threadIdx.x + 256 * u) / T; }
+
+  __device__ Operand(const float* src_, const int* rows, int ld_, int r0_, int R_, int K_)
+      : src(src_), r0(r0_), R(R_), K(K_), ld(ld_) {
 #pragma unroll
-  for (int u = 0; u < T * kKS / 256; ++u) {
-    const int e = tid + 256 * u;
-    const int r = r0 + (KC ? e / kKS : e % T), k = k0 + (KC ? e % kKS : e / T);
-    v[u] = 0.f;
-    if (r < R && k < K) {
-      const int s = KC ? r : k, c = KC ? k : r;
-      v[u] = src[(size_t)(rows ? rows[s] : s) * ld + c];
+    for (int u = 0; u < NU; ++u) {
+      const int r = min(r0 + row(u), R - 1);
+      if constexpr (KC) base[u] = src + (size_t)(rows ? rows[r] : r) * ld;
+      else off[u] = 4u * (8u * kgrp(u) * ld + (r - r0));
     }
   }
-}
-
-template <int T, bool KC>
-__device__ inline void gemm_stage(__bf16* dst, int tid, const float (&v)[T * kKS / 256]) {
+  // INSIDE: the slice ends at or before K
+  template <bool INSIDE>
+  __device__ void load(int k0, float (&v)[8 * NU]) const {
+    if constexpr (KC) {
 #pragma unroll
-  for (int u = 0; u < T * kKS / 256; ++u) {
-    const int e = tid + 256 * u;
-    dst[(KC ? e / kKS : e % T) * kTS + (KC ? e % kKS : e / T)] = (__bf16)v[u];
+      for (int u = 0; u < NU; ++u) {
+        const int k = k0 + 8 * kgrp(u);
+        if constexpr (WIDE) {
+          const f4v lo = *reinterpret_cast<const f4v*>(base[u] + min(k, K - 4));
+          const f4v hi = *reinterpret_cast<const f4v*>(base[u] + min(k + 4, K - 4));
+#pragma unroll
+          for (int e = 0; e < 4; ++e) {
+            v[8 * u + e] = lo[e];
+            v[8 * u + 4 + e] = hi[e];
+          }
+        } else {
+#pragma unroll
+          for (int e = 0; e < 8; ++e) v[8 * u + e] = base[u][min(k + e, K - 1)];
+        }
+      }
+    } else if constexpr (INSIDE) {
+      const char* s0 = reinterpret_cast<const char*>(src + (size_t)k0 * ld + r0);
+#pragma unroll
+      for (int u = 0; u < NU; ++u)
+#pragma unroll
+        for (int e = 0; e < 8; ++e)
+          v[8 * u + e] = *reinterpret_cast<const float*>(s0 + (size_t)(4 * e) * ld + off[u]);
+    } else {
+#pragma unroll
+      for (int u = 0; u < NU; ++u)
+#pragma unroll
+        for (int e = 0; e < 8; ++e)
+          v[8 * u + e] =
+              src[(size_t)min(k0 + 8 * kgrp(u) + e, K - 1) * ld + min(r0 + row(u), R - 1)];
+    }
   }
-}
+  // LAST: the slice may end past K
+  template <bool LAST>
+  __device__ void stage(__bf16* dst, int k0, const float (&v)[8 * NU]) const {
+#pragma unroll
+    for (int u = 0; u < NU; ++u) {
+      bf8v w;
+#pragma unroll
+      for (int e = 0; e < 8; ++e) {
+        float x = v[8 * u + e];
+        if (LAST && k0 + 8 * kgrp(u) + e >= K) x = 0.f;
+        w[e] = (__bf16)x;
+      }
+      *reinterpret_cast<bf8v*>(&dst[row(u) * kTS + 8 * kgrp(u)]) = w;
+    }
+  }
+};
 
-template <int T, int FORM>
+template <int T, int FORM, bool WIDE>
 __device__ inline void gemm_tile(const GemmArgs& g, int bi, int bj, const AdamArgs& ad) {
   constexpr bool AK = FORM <= GEMM_DACT, BK = FORM <= GEMM_FWD_MSE;
-  constexpr int NL = T * kKS / 256;
+  constexpr int NL = 8 * Operand<T, true, false>::NU;
+  constexpr int NP = T == 32 ? 4 : 2;  // slices in flight (even: two LDS buffers in turn)
+  enum { NONE, CLAMPED, INSIDE };      // what a step loads: nothing, a slice that may end past K, one that does not
   constexpr int S = T / 32;  // 16-wide sub-tiles per wavefront and side
   __shared__ __attribute__((aligned(16))) __bf16 sA[2][T * kTS];
   __shared__ __attribute__((aligned(16))) __bf16 sB[2][T * kTS];
@@ -111,38 +174,64 @@ __device__ inline void gemm_tile(const GemmArgs& g, int bi, int bj, const AdamAr
   const int wave = tid >> 6, lane = tid & 63, q = lane >> 4, n = lane & 15;
   const int i0 = bi * T, j0 = bj * T;
   const int wr = (wave >> 1) * (T / 2), wc = (wave & 1) * (T / 2);
-  const int* arows = FORM <= GEMM_FWD_MSE ? g.rows : nullptr;
   f4v acc[S][S];
 #pragma unroll
   for (int a = 0; a < S; ++a)
 #pragma unroll
     for (int b = 0; b < S; ++b) acc[a][b] = f4v{0.f, 0.f, 0.f, 0.f};
-  float ra[2][NL], rb[2][NL];
-  auto load = [&](int s, float (&va)[NL], float (&vb)[NL]) {
-    gemm_load<T, AK>(g.A, arows, g.lda, i0, g.M, s * kKS, g.K, tid, va);
-    gemm_load<T, BK>(g.B, nullptr, g.ldb, j0, g.N, s * kKS, g.K, tid, vb);
-  };
+  const Operand<T, BK, WIDE> opB(g.B, nullptr, g.ldb, j0, g.N, g.K);
+  const Operand<T, AK, WIDE> opA(g.A, FORM <= GEMM_FWD_MSE ? g.rows : nullptr, g.lda, i0, g.M, g.K);
+  float ra[NP][NL], rb[NP][NL];
   const int ns = (g.K + kKS - 1) / kKS;
-  auto step = [&](int s, __bf16* cA, __bf16* cB, float (&va)[NL], float (&vb)[NL]) {
-    gemm_stage<T, AK>(cA, tid, va);
-    gemm_stage<T, BK>(cB, tid, vb);
+#pragma unroll
+  for (int u = 0; u < NP; ++u) {
+    opB.template load<false>(u * kKS, rb[u]);
+    opA.template load<false>(u * kKS, ra[u]);
+  }
+  // element e = (a, b, r) of the tile: row and column of accumulator register r
+  auto row = [&](int e) { return i0 + wr + 16 * (e / (4 * S)) + 4 * q + e % 4; };
+  auto col = [&](int e) { return j0 + wc + 16 * (e / 4 % S) + n; };
+  constexpr int NE = 4 * S * S;
+  float e0[NE], e1[NE], e2[NE];  // what the epilogue reads, all loads in flight together
+  auto epilogue_loads = [&]() {
+#pragma unroll
+    for (int e = 0; e < NE; ++e) {
+      const int i = min(row(e), g.M - 1), j = min(col(e), g.N - 1);
+      const size_t at = (size_t)i * g.N + j;
+      if constexpr (FORM <= GEMM_FWD_MSE) e0[e] = g.bias[j];
+      if constexpr (FORM == GEMM_FWD_MSE) e1[e] = g.y[(size_t)(g.yrows ? g.yrows[i] : i) * g.N + j];
+      if constexpr (FORM == GEMM_DACT) e0[e] = g.act[at];
+      if constexpr (FORM == GEMM_DW_ADAM) {
+        e0[e] = g.p[at];
+        e1[e] = g.m[at];
+        e2[e] = g.v[at];
+      }
+    }
+  };
+  if constexpr (T == 32) epilogue_loads();  // (64 x 64: the registers are the accumulators')
+  auto step = [&](int s, __bf16* cA, __bf16* cB, float (&va)[NL], float (&vb)[NL], auto next) {
+    __builtin_amdgcn_sched_barrier(0);  // (no wait for a later slice moves up)
+    opA.template stage<next() == NONE>(cA, s * kKS, va);
+    opB.template stage<next() == NONE>(cB, s * kKS, vb);
     if constexpr (FORM <= GEMM_FWD_MSE) {
       // the gathered rows, for the weight gradient (whose contraction over
       // them would otherwise wait for each slice's row indices)
       if (g.rows && bj == 0) {
 #pragma unroll
-        for (int u = 0; u < NL; ++u) {
-          const int e = tid + 256 * u;
-          const int i = i0 + e / kKS, k = s * kKS + e % kKS;
-          if (i < g.M && k < g.K) g.gathered[(size_t)i * g.K + k] = va[u];
+        for (int e = 0; e < NL; ++e) {
+          const int i = i0 + opA.row(e / 8), k = s * kKS + 8 * opA.kgrp(e / 8) + e % 8;
+          if (i < g.M && k < g.K) g.gathered[(size_t)i * g.K + k] = va[e];
         }
       }
     }
-    if (s + 2 < ns) load(s + 2, va, vb);
+    if constexpr (next() != NONE) {
+      opB.template load<next() == INSIDE>((s + NP) * kKS, vb);
+      opA.template load<next() == INSIDE>((s + NP) * kKS, va);
+    }
     __syncthreads();
 #pragma unroll
     for (int h = 0; h < kKS / 32; ++h) {
-      if (s * kKS + 32 * h >= g.K) break;
+      if (next() == NONE && s * kKS + 32 * h >= g.K) break;
       bf8v af[S], bfr[S];
 #pragma unroll
       for (int a = 0; a < S; ++a) {
@@ -156,32 +245,20 @@ __device__ inline void gemm_tile(const GemmArgs& g, int bi, int bj, const AdamAr
           acc[a][b] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(af[a], bfr[b], acc[a][b], 0, 0, 0);
     }
   };
-  load(0, ra[0], rb[0]);
-  if (ns > 1) load(1, ra[1], rb[1]);
-  for (int s = 0; s < ns; s += 2) {
-    step(s, sA[0], sB[0], ra[0], rb[0]);
-    if (s + 1 < ns) step(s + 1, sA[1], sB[1], ra[1], rb[1]);
-  }
-  double sq = 0.0;
-  // element e = (a, b, r) of the tile: row and column of accumulator register r
-  auto row = [&](int e) { return i0 + wr + 16 * (e / (4 * S)) + 4 * q + e % 4; };
-  auto col = [&](int e) { return j0 + wc + 16 * (e / 4 % S) + n; };
-  constexpr int NE = 4 * S * S;
-  float e0[NE], e1[NE], e2[NE];  // what the epilogue reads, all loads in flight together
+  auto steps = [&](int s, auto next) {
 #pragma unroll
-  for (int e = 0; e < NE; ++e) {
-    const int i = row(e), j = col(e);
-    if (i >= g.M || j >= g.N) continue;
-    const size_t at = (size_t)i * g.N + j;
-    if constexpr (FORM <= GEMM_FWD_MSE) e0[e] = g.bias[j];
-    if constexpr (FORM == GEMM_FWD_MSE) e1[e] = g.y[(size_t)(g.yrows ? g.yrows[i] : i) * g.N + j];
-    if constexpr (FORM == GEMM_DACT) e0[e] = g.act[at];
-    if constexpr (FORM == GEMM_DW_ADAM) {
-      e0[e] = g.p[at];
-      e1[e] = g.m[at];
-      e2[e] = g.v[at];
-    }
+    for (int u = 0; u < NP; ++u)
+      if (next() != NONE || s + u < ns) step(s + u, sA[u & 1], sB[u & 1], ra[u], rb[u], next);
+  };
+  int s = 0;
+  for (; (s + 2 * NP) * kKS <= g.K; s += NP) steps(s, std::integral_constant<int, INSIDE>());
+  if (s + NP < ns) {
+    steps(s, std::integral_constant<int, CLAMPED>());
+    s += NP;
   }
+  steps(s, std::integral_constant<int, NONE>());
+  if constexpr (T != 32) epilogue_loads();
+  double sq = 0.0;
 #pragma unroll
   for (int e = 0; e < NE; ++e) {
     const int i = row(e), j = col(e);
@@ -219,41 +296,51 @@ __device__ inline void gemm_tile(const GemmArgs& g, int bi, int bj, const AdamAr
   }
 }
 
-template <int T, int FORM>
+template <int T, int FORM, bool WIDE>
 __global__ __launch_bounds__(256, 2) void k_gemm(GemmArgs g) {
-  gemm_tile<T, FORM>(g, blockIdx.x, blockIdx.y, AdamArgs{});
+  gemm_tile<T, FORM, WIDE>(g, blockIdx.x, blockIdx.y, AdamArgs{});
 }
 
 // Bias gradient db[j] = sum_i g[i][j] of 64 columns, in row order: chunks of
-// 128 rows through registers (the next chunk in flight) into LDS, added by one
-// wavefront.
-__device__ inline float bias_sum(const float* __restrict__ G, int B, int N, int j0) {
-  constexpr int R = 32;
-  __shared__ float sG[4 * R][64];
+// 64 rows through registers (the next four in flight) into LDS (two buffers),
+// added by one wavefront, whose reads of a chunk are all issued before its adds.
+__device__ __forceinline__ float bias_sum(const float* __restrict__ G, int B, int N, int j0) {
+  constexpr int R = 16, NP = 4;
+  __shared__ float sG[2][4 * R][64];
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
   const int j = min(j0 + lane, N - 1);
-  float v[R];
-  auto load = [&](int b) {
+  float v[NP][R];
+  auto load = [&](int b, float (&w)[R]) {
 #pragma unroll
-    for (int u = 0; u < R; ++u) {
-      const int i = b + wave * R + u;
-      v[u] = i < B ? G[(size_t)i * N + j] : 0.f;
+    for (int u = 0; u < R; ++u) w[u] = G[(size_t)min(b + wave * R + u, B - 1) * N + j];
+  };
+  float s = 0.f;
+#pragma unroll
+  for (int c = 0; c < NP; ++c) load(4 * R * c, v[c]);
+  auto step = [&](int b, float (&w)[R], float (*sg)[64], auto more) {
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int u = 0; u < R; ++u) sg[wave * R + u][lane] = w[u];
+    if constexpr (more()) load(b + 4 * R * NP, w);
+    __syncthreads();
+    if (wave == 0) {
+      float w64[4 * R];
+#pragma unroll
+      for (int i = 0; i < 4 * R; ++i) w64[i] = sg[i][lane];
+      __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+      for (int i = 0; i < 4 * R; ++i)
+        if (more() || b + i < B) s += w64[i];
     }
   };
-  load(0);
-  float s = 0.f;
-  for (int b = 0; b < B; b += 4 * R) {
+  int b = 0;  // (the last 1 to NP chunks apart: their steps load nothing)
+  for (; b + 4 * R * NP < B; b += 4 * R * NP) {
 #pragma unroll
-    for (int u = 0; u < R; ++u) sG[wave * R + u][lane] = v[u];
-    __syncthreads();
-    if (b + 4 * R < B) load(b + 4 * R);
-    if (wave == 0) {
-      const int n = min(4 * R, B - b);
-#pragma unroll 16
-      for (int i = 0; i < n; ++i) s += sG[i][lane];
-    }
-    __syncthreads();
+    for (int c = 0; c < NP; ++c) step(b + 4 * R * c, v[c], sG[c & 1], std::true_type());
   }
+#pragma unroll
+  for (int c = 0; c < NP; ++c)
+    if (b + 4 * R * c < B) step(b + 4 * R * c, v[c], sG[c & 1], std::false_type());
   return s;
 }
 
@@ -280,14 +367,26 @@ __global__ __launch_bounds__(256, 2) void k_dw(DwArgs a) {
   const int t = blockIdx.x - a.first[l];
   const int tj = (g.N + T - 1) / T, tiles = tj * ((g.M + T - 1) / T);
   if (t < tiles) {
-    gemm_tile<T, ADAM ? GEMM_DW_ADAM : GEMM_DW>(g, t / tj, t % tj, a.ad);
+    gemm_tile<T, ADAM ? GEMM_DW_ADAM : GEMM_DW, false>(g, t / tj, t % tj, a.ad);
   } else {
     const int j0 = (t - tiles) * 64;
-    const float s = bias_sum(g.A, g.K, g.M, j0);
     const int j = j0 + (int)threadIdx.x;
-    if (threadIdx.x < 64 && j < g.M) {
-      if constexpr (ADAM) adam_update(s, a.db[l][j], a.dbm[l][j], a.dbv[l][j], a.ad);
-      else a.db[l][j] = s;
+    const bool own = threadIdx.x < 64 && j < g.M;
+    float p = 0.f, m = 0.f, v = 0.f;
+    if (ADAM && own) {
+      p = a.db[l][j];
+      m = a.dbm[l][j];
+      v = a.dbv[l][j];
+    }
+    const float s = bias_sum(g.A, g.K, g.M, j0);
+    if (!own) return;
+    if constexpr (ADAM) {
+      adam_update(s, p, m, v, a.ad);
+      a.db[l][j] = p;
+      a.dbm[l][j] = m;
+      a.dbv[l][j] = v;
+    } else {
+      a.db[l][j] = s;
     }
   }
 }
@@ -388,16 +487,25 @@ int layers(const gmco_mlp* m) { return (int)m->sizes.size() - 1; }
 
 int tiles_of(int rows, int cols, int T) { return ((rows + T - 1) / T) * ((cols + T - 1) / T); }
 
-template <int FORM>
-hipError_t gemm(hipStream_t st, const GemmArgs& a) {
+template <int FORM, bool WIDE>
+hipError_t gemm_launch(hipStream_t st, const GemmArgs& a) {
   if constexpr (FORM != GEMM_FWD_MSE) {  // (whose tile losses are laid out for 32 x 32 tiles)
     if (tiles_of(a.M, a.N, 64) >= kGemmWide) {
-      hipLaunchKernelGGL((k_gemm<64, FORM>), dim3((a.M + 63) / 64, (a.N + 63) / 64), dim3(256), 0, st, a);
+      hipLaunchKernelGGL((k_gemm<64, FORM, WIDE>), dim3((a.M + 63) / 64, (a.N + 63) / 64), dim3(256), 0, st, a);
       return hipGetLastError();
     }
   }
-  hipLaunchKernelGGL((k_gemm<32, FORM>), dim3((a.M + 31) / 32, (a.N + 31) / 32), dim3(256), 0, st, a);
+  hipLaunchKernelGGL((k_gemm<32, FORM, WIDE>), dim3((a.M + 31) / 32, (a.N + 31) / 32), dim3(256), 0, st, a);
   return hipGetLastError();
+}
+
+// The operands that are contiguous in k (A, and B of the forward products) are
+// read by whole float4 where their rows are of whole, aligned ones.
+template <int FORM>
+hipError_t gemm(hipStream_t st, const GemmArgs& a) {
+  auto whole = [&](const float* p, int ld) { return ld % 4 == 0 && (reinterpret_cast<size_t>(p) & 15) == 0; };
+  const bool wide = a.K % 4 == 0 && whole(a.A, a.lda) && (FORM > GEMM_FWD_MSE || whole(a.B, a.ldb));
+  return wide ? gemm_launch<FORM, true>(st, a) : gemm_launch<FORM, false>(st, a);
 }
 
 GemmArgs forward_args(const gmco_mlp* m, int B, int k, const float* in, const int* rows) {

@@ -188,6 +188,31 @@ def test_network_tile_sizes_agree_bitwise():
     assert np.abs(g - gr).max() <= 5e-2 * np.abs(gr).max()
 
 
+# Rows of whole, aligned float4 are read 16 bytes at a time, others by element.
+# A network of 67 inputs and the same one with a 68th that is always zero take
+# different forms of the first forward product: the same bits.
+@pytest.mark.parametrize("hidden,B", [(32, 33), (64, 130)])
+def test_network_row_loads_agree_bitwise(hidden, B):
+    from paper_1904_01567_amd import Network
+    announce(f"network row loads hidden={hidden} B={B}")
+    rng = np.random.default_rng(B)
+    narrow, wide = [67, hidden, 8], [68, hidden, 8]
+    p = cases.mlp_init(narrow, seed=2).astype(np.float32)
+    W0 = p[:67 * hidden].reshape(hidden, 67)
+    q = np.concatenate([np.pad(W0, ((0, 0), (0, 1))).ravel(), p[67 * hidden:]])
+    X = rng.uniform(0, 1, size=(B, 67)).astype(np.float32)
+    Y = rng.uniform(0, 2, size=(B, 8)).astype(np.float32)
+    out = []
+    for sizes, par, x in ((narrow, p, X), (wide, q, np.pad(X, ((0, 0), (0, 1))))):
+        net = Network(sizes, max_batch=B)
+        net.set_params(par)
+        L, g = net.loss_grad(x, Y)
+        gW = g[:sizes[0] * hidden].reshape(hidden, sizes[0])
+        out.append((np.float64(L), net.predict(x), gW[:, :67], g[sizes[0] * hidden:]))
+    for a, b in zip(*out):
+        np.testing.assert_array_equal(a, b)
+
+
 def _check_metrics(pl, D, t, c, W, params=PARAMS):
     m = pl.metrics()
     mref = O.plan_metrics(D, t, c.group, params, W, c.volume_cc, 15.0)
