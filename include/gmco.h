@@ -325,7 +325,7 @@ typedef struct {
                     (the same bits).  FP32 with FP64-summed chunks: 0.  Defaults
                     after gmco_load_case: BF16 2 (up to 384 padded dwells), FP8 0,
                     FP32 3, FP64-accumulated 0 (3 from 448 padded dwells) */
-  int xcd_map;   /* 1: tiles of one point range on one XCD when the grid allows */
+  int xcd_map;   /* 1: tiles of one point range on one XCD */
 } gmco_tuning;
 
 /* Read or set the launch shape of dtype's kernel family (-1: the context's

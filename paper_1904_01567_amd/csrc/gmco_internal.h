@@ -121,7 +121,7 @@ struct EvalArgs {
   int ntiles;             // Pp / kPT (uncompacted form)
   int grid;               // workgroups launched; those past the round's grid exit
   int lp_shape;           // BF16 / FP8 workgroup shape (lp_threads, lp_halves)
-  int xcd_map;            // 1: tiles of one point range on one XCD when the grid allows
+  int xcd_map;            // 1: tiles of one point range on one XCD
   int last16;             // 0: dwells Kp - 16 .. Kp - 1 are all padding (FP32-operand
                           // kernels skip that 16-dwell slice: its products are zero)
   const double* gparams;  // [kGmax][4] eq. 1 row per structure: (w_min, D_min, D_max, w_max)
