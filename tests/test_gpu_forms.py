@@ -62,3 +62,43 @@ def test_wide_update_agrees_with_large_batch_bitwise(n_cath, n_dw, M, m, split):
             out.append(_result(pl))
         for a, b in zip(*out):
             np.testing.assert_array_equal(np.broadcast_to(a, b.shape), b)
+
+
+# Weight gradients take 64 x 64 tiles from 512 of them (1,536 x 1,500: 24 x 24)
+# and 32 x 32 below.  The first 96 outputs alone are 48 tiles, and their gradient
+# is 16 times as large (the mean is over a sixteenth of the outputs), a scaling
+# that no rounding sees.
+@pytest.mark.parametrize("B", [5, 64, 200])
+def test_weight_gradient_tiles_agree_bitwise(B):
+    from oracle import mlp_oracle as MO
+    from paper_1904_01567_amd import Network
+    announce(f"weight gradient tiles B={B}")
+    n_in, n_out, part = 1500, 1536, 96
+    rng = np.random.default_rng(B)
+    p = cases.mlp_init([n_in, n_out], seed=1).astype(np.float32)
+    X = rng.uniform(0, 1, size=(B, n_in)).astype(np.float32)
+    Y = rng.uniform(0, 2, size=(B, n_out)).astype(np.float32)
+    net = Network([n_in, n_out], max_batch=B)
+    net.set_params(p)
+    L, g = net.loss_grad(X, Y)
+    gW, gb = g[:n_in * n_out].reshape(n_out, n_in), g[n_in * n_out:]
+    Lr, gr = MO.loss_and_grad(p.astype(np.float64), [n_in, n_out], X.astype(np.float64), Y.astype(np.float64))
+    assert L == pytest.approx(Lr, rel=2e-2)
+    assert np.abs(g - gr).max() <= 5e-2 * np.abs(gr).max()
+    W = p[:n_in * n_out].reshape(n_out, n_in)
+    small = Network([n_in, part], max_batch=B)
+    small.set_params(np.concatenate([W[:part].ravel(), p[n_in * n_out:][:part]]))
+    _, h = small.loss_grad(X, np.ascontiguousarray(Y[:, :part]))
+    np.testing.assert_array_equal(h[:n_in * part].reshape(part, n_in), np.float32(n_out / part) * gW[:part])
+    np.testing.assert_array_equal(h[n_in * part:], np.float32(n_out / part) * gb[:part])
+    # the form that updates the parameters in place of storing the gradient: the
+    # first Adam step from this gradient, within a few FP32 roundings
+    net.set_data(X, Y)
+    lr = 1e-3
+    net.train(np.arange(B, dtype=np.int32), B, lr)
+    m = np.float32(0.1) * g
+    v = g * (np.float32(0.001) * g)
+    step = lr * (m.astype(np.float64) / 0.1) / (np.sqrt(v.astype(np.float64) / 0.001) + 1e-8)
+    # (the first step's moments and their corrections have the same factors)
+    assert np.abs(net.params() - (p - step)).max() <= 2.0 ** -23 * np.abs(p).max() + 2e-6 * lr
+    assert np.abs(net.params() - p).max() > 0.5 * lr
