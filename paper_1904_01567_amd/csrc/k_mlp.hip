@@ -606,15 +606,22 @@ hipError_t step_products(gmco_mlp* m, int B, const float* in, const float* y, co
 int loss_tiles(const gmco_mlp* m, int B) { return tiles_of(B, m->sizes.back(), 32); }
 
 // Device memory of a training call, kept for the next one and grown when a
-// call needs more (its last work has ended: every call synchronises).
+// call needs more (its last work has ended: every call synchronises).  The order
+// of a long call is as long as the call, so past kStepsKeep it goes back when the
+// call returns.
+constexpr size_t kStepsKeep = size_t(16) << 20;
+
+void release_steps(gmco_mlp* m) {
+  if (!m->steps) return;
+  m->owned.erase(std::find(m->owned.begin(), m->owned.end(), m->steps));
+  (void)hipFree(m->steps);
+  m->steps = nullptr;
+  m->steps_bytes = 0;
+}
+
 hipError_t reserve_steps(gmco_mlp* m, size_t bytes) {
   if (m->steps_bytes >= bytes) return hipSuccess;
-  if (m->steps) {
-    m->owned.erase(std::find(m->owned.begin(), m->owned.end(), m->steps));
-    (void)hipFree(m->steps);
-    m->steps = nullptr;
-    m->steps_bytes = 0;
-  }
+  release_steps(m);
   void* p = nullptr;
   const hipError_t e = hipMalloc(&p, bytes);
   if (e != hipSuccess) return e;
@@ -774,6 +781,12 @@ int gmco_mlp_train(gmco_mlp* m, int n_steps, int B, const int32_t* order, float 
   constexpr int kLossSteps = 64;
   if (reserve_steps(m, order_bytes + ((size_t)n_steps + (size_t)std::min(n_steps, kLossSteps) * nt) * 8) != hipSuccess)
     return mfail(m, GMCO_ENOMEM, "training buffers");
+  struct Release {
+    gmco_mlp* m;
+    ~Release() {
+      if (m->steps_bytes > kStepsKeep) release_steps(m);
+    }
+  } release{m};
   int* dorder = (int*)m->steps;
   double* losses = (double*)((char*)m->steps + order_bytes);
   double* tile_loss = losses + n_steps;
