@@ -61,6 +61,7 @@ struct Dims {
 };
 
 constexpr int kSplitTuneMax = 32;
+constexpr int kMaxPlans = 1 << 20;  // largest batch of a context
 
 // Split count for ntiles plan tiles over nblocks point blocks on n_cu compute
 // units (one evaluation workgroup per CU at a time): minimises the number of
@@ -292,8 +293,13 @@ bool finite_all(const double* v, size_t n, float* y = nullptr) {
 // Pinned host memory that calls borrow to stage their copies: a copy from or to
 // pageable memory goes through the runtime's own staging and takes two to three
 // times as long (2.9 MB: 100 us up and 157 down, against 58).  Blocks
-// outlive a call, since pinning costs far more than a call saves; up to
-// kPinKeep bytes stay while any context exists, all of them go with the last.
+// outlive a call, since pinning costs far more than a call saves, and all of
+// them go with the last context.  Copies cross in pieces of at most kPinBlock,
+// so that a block serves any of them, and nothing is pinned that would not be
+// kept: past kPinTotal in use and kept together a call does without.
+constexpr size_t kPinBlock = size_t(16) << 20;
+constexpr size_t kPinTotal = size_t(64) << 20;
+
 class PinPool {
  public:
   void enter() {
@@ -305,10 +311,16 @@ class PinPool {
     if (--users_ > 0) return;
     for (int i = 0; i < n_; ++i) (void)hipHostFree(free_[i].p);
     n_ = 0;
+    total_ -= kept_;
     kept_ = 0;
   }
   // nullptr when no memory can be pinned
   void* get(size_t bytes, size_t* size) {
+    if (bytes > kPinBlock) return nullptr;
+    size_t n = kPinMin;
+    while (n < bytes) n <<= 1;
+    Block out[kPinBlocks];
+    int n_out = 0;
     {
       std::lock_guard<std::mutex> lk(mu_);
       int best = -1;
@@ -321,12 +333,20 @@ class PinPool {
         *size = b.size;
         return b.p;
       }
+      if (total_ - kept_ + n > kPinTotal) return nullptr;  // (blocks in use stay)
+      while (total_ + n > kPinTotal) {  // make room: every kept block is a smaller one
+        out[n_out++] = free_[--n_];
+        kept_ -= free_[n_].size;
+        total_ -= free_[n_].size;
+      }
+      total_ += n;
     }
-    size_t n = size_t(1) << 20;
-    while (n < bytes) n <<= 1;
+    for (int i = 0; i < n_out; ++i) (void)hipHostFree(out[i].p);
     void* p = nullptr;
     if (hipHostMalloc(&p, n, hipHostMallocPortable) != hipSuccess) {
       (void)hipGetLastError();
+      std::lock_guard<std::mutex> lk(mu_);
+      total_ -= n;
       return nullptr;
     }
     *size = n;
@@ -335,18 +355,19 @@ class PinPool {
   void put(void* p, size_t size) {
     {
       std::lock_guard<std::mutex> lk(mu_);
-      if (users_ > 0 && n_ < kPinBlocks && kept_ + size <= kPinKeep) {
+      if (users_ > 0) {
         free_[n_++] = {p, size};
         kept_ += size;
         return;
       }
+      total_ -= size;
     }
     (void)hipHostFree(p);
   }
 
  private:
-  static constexpr size_t kPinKeep = size_t(64) << 20;
-  static constexpr int kPinBlocks = 16;
+  static constexpr size_t kPinMin = size_t(1) << 20;
+  static constexpr int kPinBlocks = kPinTotal / kPinMin;  // (as many as can exist)
   struct Block {
     void* p;
     size_t size;
@@ -354,17 +375,18 @@ class PinPool {
   std::mutex mu_;
   Block free_[kPinBlocks] = {};
   int n_ = 0;
-  size_t kept_ = 0;
+  size_t kept_ = 0;   // bytes of the free blocks
+  size_t total_ = 0;  // and of those in use
   int users_ = 0;
 };
 PinPool g_pin;
 
-// One call's staging memory (pageable when none can be pinned; ok() is false
-// when there is none at all).  Copies from and to it are over once the call has
-// synchronised its stream (settled); a call that returns early waits for them
-// here.
+// One call's staging memory, `bytes` of what it asked for and at most kPinBlock
+// (pageable when none can be pinned; ok() is false when there is none at all).
+// Copies from and to it are over once the call has synchronised its stream
+// (settled); a call that returns early waits for them here.
 struct Staging {
-  Staging(size_t bytes, hipStream_t s) : stream(s) {
+  Staging(size_t want, hipStream_t s) : stream(s), bytes(std::min(want, kPinBlock)) {
     p = g_pin.get(bytes, &size);
     if (!p) p = plain = std::malloc(bytes);
   }
@@ -381,6 +403,7 @@ struct Staging {
     return reinterpret_cast<T*>(static_cast<char*>(p) + off);
   }
   hipStream_t stream;
+  size_t bytes;
   void* p = nullptr;
   void* plain = nullptr;
   size_t size = 0;
@@ -393,6 +416,24 @@ struct Staging {
 int copy_h2d(gmco_ctx* c, void* dst, const void* src, size_t bytes) {
   if (bytes == 0) return GMCO_OK;
   GMCO_HIP(c, hipMemcpyAsync(dst, src, bytes, hipMemcpyHostToDevice, c->stream));
+  return GMCO_OK;
+}
+
+// n units of device memory to the host through staging memory from byte `at` on,
+// in pieces of whole units: use(first unit, units, data) after each.  The call's
+// earlier copies are over with the first.
+template <class F>
+int read_back(gmco_ctx* c, Staging& st, size_t at, const void* src, size_t n, size_t unit, F use) {
+  const size_t per = (st.bytes - at) / unit;
+  for (size_t i = 0; i < n; i += per) {
+    const size_t k = std::min(per, n - i);
+    st.settled = false;
+    GMCO_HIP(c, hipMemcpyAsync(st.at<void>(at), static_cast<const char*>(src) + i * unit, k * unit,
+                               hipMemcpyDeviceToHost, c->stream));
+    GMCO_HIP(c, hipStreamSynchronize(c->stream));
+    st.settled = true;
+    use(i, k, st.at<char>(at));
+  }
   return GMCO_OK;
 }
 
@@ -477,11 +518,8 @@ int check_run(gmco_ctx* c, const gmco_run* r, int* dtype) {
   return GMCO_OK;
 }
 
-int summarize(gmco_ctx* c, long long rounds, float ms, double eval_ms, double update_ms,
-              unsigned long long work, const PlanState* ps, gmco_run_info* info) {
-  gmco_run_info inf{};
-  inf.rounds = (int)rounds;
-  for (int p = 0; p < c->P; ++p) {
+void add_states(gmco_run_info& inf, const PlanState* ps, size_t n) {
+  for (size_t p = 0; p < n; ++p) {
     const PlanState& s = ps[p];
     inf.n_converged += s.status == ST_CONVERGED;
     inf.n_maxiter += s.status == ST_MAXITER;
@@ -489,6 +527,12 @@ int summarize(gmco_ctx* c, long long rounds, float ms, double eval_ms, double up
     inf.n_nonfinite += s.status == ST_NONFINITE;
     inf.max_iters = std::max(inf.max_iters, s.iter);
   }
+}
+
+// inf holds the counts of every plan's state already
+int summarize(gmco_ctx* c, long long rounds, float ms, double eval_ms, double update_ms,
+              unsigned long long work, gmco_run_info inf, gmco_run_info* info) {
+  inf.rounds = (int)rounds;
   inf.device_ms = ms;
   inf.eval_ms = (float)eval_ms;
   inf.update_ms = (float)update_ms;
@@ -523,7 +567,7 @@ int gmco_create(gmco_ctx** out, const gmco_opts* o) {
   *out = nullptr;
   if (o->dtype < GMCO_DTYPE_F32 || o->dtype > GMCO_DTYPE_F32_CHUNK64) return GMCO_EINVAL;
   if (o->history < 1 || o->history > GMCO_MAX_HISTORY) return GMCO_EINVAL;
-  if (o->max_plans < 1 || o->max_plans > (1 << 20)) return GMCO_EINVAL;
+  if (o->max_plans < 1 || o->max_plans > kMaxPlans) return GMCO_EINVAL;
   int ndev = 0;
   if (hipGetDeviceCount(&ndev) != hipSuccess || ndev <= 0) return GMCO_ENOLIB;
   if (o->device < 0 || o->device >= ndev) return GMCO_EINVAL;
@@ -699,19 +743,25 @@ int gmco_load_case(gmco_ctx* c, const gmco_case* cs) {
     for (int i = 0; i < Md; ++i) dperm[cur[cs->dvh_organ[i]]++] = i;
   }
 
-  // the small arrays as one block, laid out as in the arena
-  Staging st(L.up_end - L.up, c->stream);
+  std::vector<double> gp(kGmax * 4, 0.0), vol(kGmax, 0.0);
+  std::copy(cs->group_params, cs->group_params + 4 * G, gp.begin());
+  if (cs->group_volume_cc) std::copy(cs->group_volume_cc, cs->group_volume_cc + O, vol.begin());
+
+  // the small arrays as one block, laid out as in the arena; past a piece of
+  // staging memory (about 500,000 points) each by itself
+  const bool block = L.up_end - L.up <= kPinBlock;
+  Staging st(block ? L.up_end - L.up : 1, c->stream);
   GMCO_STAGED(c, st);
+  int rc = GMCO_OK;
   auto put = [&](size_t off, const void* src, size_t bytes) {
-    if (bytes) std::memcpy(st.at<char>(off - L.up), src, bytes);
+    if (rc || bytes == 0) return;
+    if (block) std::memcpy(st.at<char>(off - L.up), src, bytes);
+    else rc = copy_h2d(c, c->at<void>(off), src, bytes);
   };
   put(L.perm, c->perm.data(), (size_t)M * 4);
   put(L.grp, grp.data(), (size_t)d.Mp * 4);
   put(L.dwell, cs->dwell_xyz, (size_t)K * 3 * 8);
   if (cs->point_xyz) put(L.pts, cs->point_xyz, (size_t)M * 3 * 8);
-  std::vector<double> gp(kGmax * 4, 0.0), vol(kGmax, 0.0);
-  std::copy(cs->group_params, cs->group_params + 4 * G, gp.begin());
-  if (cs->group_volume_cc) std::copy(cs->group_volume_cc, cs->group_volume_cc + O, vol.begin());
   put(L.gparams, gp.data(), gp.size() * 8);
   put(L.volume, vol.data(), vol.size() * 8);
   put(L.goff, c->offsets.data(), kGmax * 4);
@@ -726,8 +776,8 @@ int gmco_load_case(gmco_ctx* c, const gmco_case* cs) {
   }
   put(L.split_tab, d.split16.data(), d.split16.size() * 4);
   put(L.split_tab + d.split16.size() * 4, d.split32.data(), d.split32.size() * 4);
-  int rc;
-  if ((rc = copy_h2d(c, c->at<void>(L.up), st.at<void>(0), L.up_end - L.up))) return rc;
+  if (rc) return rc;
+  if (block && (rc = copy_h2d(c, c->at<void>(L.up), st.at<void>(0), L.up_end - L.up))) return rc;
   double* st_D = c->at<double>(L.stage);
   const double* st_dw = c->at<double>(L.dwell);
   const double* st_pt = c->at<double>(L.pts);
@@ -785,24 +835,31 @@ int gmco_evaluate(gmco_ctx* c, const double* x, double* F, double* g) {
   const Layout& L = c->lay;
   // x crosses in FP32, as the kernels use it, and the gradient in FP32, as they
   // compute it; F and g come back as one block
-  const size_t n = (size_t)P * K, back = L.gst - L.Fst + n * 4;
+  const size_t n = (size_t)P * K, g0 = L.gst - L.Fst, back = g0 + n * 4;
   Staging st(std::max(n * 4, back), c->stream);
   GMCO_STAGED(c, st);
-  if (!finite_all(x, n, st.at<float>(0))) return fail(c, GMCO_EINVAL, "x must be finite");
-  int rc;
-  if ((rc = copy_h2d(c, c->at<void>(L.xst), st.at<void>(0), n * 4))) return rc;
+  const size_t per = st.bytes / 4;
+  for (size_t i = 0; i < n; i += per) {
+    const size_t k = std::min(per, n - i);
+    if (i) GMCO_HIP(c, hipStreamSynchronize(c->stream));  // the piece before is up
+    if (!finite_all(x + i, k, st.at<float>(0))) return fail(c, GMCO_EINVAL, "x must be finite");
+    const int rc = copy_h2d(c, c->at<char>(L.xst) + i * 4, st.at<void>(0), k * 4);
+    if (rc) return rc;
+  }
   GMCO_HIP(c, launch_x32_to_device(c->at<float>(L.xst), P, c->dim.Pp, K, c->dim.Kp, c->at<float>(L.xe), c->stream));
   EvalArgs a = eval_args(c, c->at<float>(L.xe), false, c->dtype);
   GMCO_HIP(c, launch_eval(a, c->dtype, c->stream));
   GMCO_HIP(c, launch_finish_eval_f32(a.Gpart, a.Fpart, c->at<float>(L.xe), a.S, P, c->dim.Pp, K, c->dim.Kp,
                                      c->at<double>(L.Fst), c->at<float>(L.gst), c->stream));
-  GMCO_HIP(c, hipMemcpyAsync(st.at<void>(0), c->at<void>(L.Fst), back, hipMemcpyDeviceToHost, c->stream));
-  GMCO_HIP(c, hipStreamSynchronize(c->stream));
-  st.settled = true;
-  std::memcpy(F, st.at<double>(0), (size_t)P * 8);
-  const float* g32 = st.at<float>(L.gst - L.Fst);
-  for (size_t i = 0; i < n; ++i) g[i] = (double)g32[i];
-  return GMCO_OK;
+  return read_back(c, st, 0, c->at<void>(L.Fst), back / 4, 4, [&](size_t i, size_t k, const char* p) {
+    const size_t b0 = 4 * i, b1 = b0 + 4 * k, f1 = (size_t)P * 8;  // bytes of the block: F, then g from g0
+    if (b0 < f1) std::memcpy(reinterpret_cast<char*>(F) + b0, p, std::min(b1, f1) - b0);
+    if (b1 <= g0) return;
+    const size_t s0 = std::max(b0, g0);
+    const float* g32 = reinterpret_cast<const float*>(p + (s0 - b0));
+    double* out = g + (s0 - g0) / 4;
+    for (size_t l = 0; l < (b1 - s0) / 4; ++l) out[l] = (double)g32[l];
+  });
 }
 
 int gmco_set_weights_learned(gmco_ctx* c, gmco_mlp* net, int P, const double* W, double x_floor, int* use_warm,
@@ -950,17 +1007,19 @@ int gmco_optimize(gmco_ctx* c, const gmco_run* r, gmco_run_info* info) {
   }
   while (harvested < timed) GMCO_HIP(c, harvest());
   GMCO_HIP(c, hipEventRecord(c->ev1, c->stream));
-  const size_t ps_bytes = (size_t)c->P * sizeof(PlanState);
-  Staging st(ps_bytes + 16, c->stream);
+  constexpr size_t kHead = 64;  // the work counts, then the plans' states
+  Staging st(kHead + (size_t)c->P * sizeof(PlanState), c->stream);
   GMCO_STAGED(c, st);
-  GMCO_HIP(c, hipMemcpyAsync(st.at<void>(0), c->at<void>(L.ps), ps_bytes, hipMemcpyDeviceToHost, c->stream));
-  GMCO_HIP(c, hipMemcpyAsync(st.at<void>(ps_bytes), work, 16, hipMemcpyDeviceToHost, c->stream));
-  GMCO_HIP(c, hipStreamSynchronize(c->stream));
-  st.settled = true;
-  const unsigned long long* done = st.at<unsigned long long>(ps_bytes);
+  GMCO_HIP(c, hipMemcpyAsync(st.at<void>(0), work, 16, hipMemcpyDeviceToHost, c->stream));
+  gmco_run_info inf{};
+  rc = read_back(c, st, kHead, c->at<void>(L.ps), c->P, sizeof(PlanState), [&](size_t, size_t k, const char* p) {
+    add_states(inf, reinterpret_cast<const PlanState*>(p), k);
+  });
+  if (rc) return rc;
+  const unsigned long long* done = st.at<unsigned long long>(0);
   float ms = 0.f;
   GMCO_HIP(c, hipEventElapsedTime(&ms, c->ev0, c->ev1));
-  rc = summarize(c, round, ms, eval_ms, update_ms, done[0], st.at<PlanState>(0), info);
+  rc = summarize(c, round, ms, eval_ms, update_ms, done[0], inf, info);
   if (info) {
     info->timed_launches = timed;
     info->timed_work = (double)done[1] / (double)c->P;
@@ -1186,27 +1245,53 @@ int gmco_optimize_many(gmco_ctx* const* ctxs, int n, const gmco_run* r, gmco_run
   float ms = 0.f;
   GMCO_HIP(c0, hipEventElapsedTime(&ms, c0->ev0, c0->ev1));
   int status = GMCO_OK;
+  // every case's work count and its plans' states, as many as fit a piece
   size_t bytes = 0;
-  std::vector<size_t> at(n);
-  for (int i = 0; i < n; ++i) {
-    at[i] = bytes;
-    bytes += (size_t)ctxs[i]->P * sizeof(PlanState) + 64;  // the plans' states, then the work count
-  }
+  for (int i = 0; i < n; ++i) bytes += 8 + (size_t)ctxs[i]->P * sizeof(PlanState);
   Staging sg(bytes, st);
   GMCO_STAGED(c0, sg);
+  std::vector<gmco_run_info> sums(n);
+  std::vector<unsigned long long> work(n);
+  struct Part {
+    int i;
+    size_t n, at;  // n states, or the work count (0)
+  };
+  std::vector<Part> parts;
+  size_t at = 0;
+  auto settle = [&]() -> int {
+    GMCO_HIP(c0, hipStreamSynchronize(st));
+    sg.settled = true;
+    for (const Part& q : parts) {
+      if (q.n == 0) work[q.i] = *sg.at<unsigned long long>(q.at);
+      else add_states(sums[q.i], sg.at<PlanState>(q.at), q.n);
+    }
+    parts.clear();
+    at = 0;
+    return GMCO_OK;
+  };
+  auto take = [&](int i, const void* src, size_t k, size_t size) -> int {
+    sg.settled = false;
+    GMCO_HIP(ctxs[i], hipMemcpyAsync(sg.at<void>(at), src, size, hipMemcpyDeviceToHost, st));
+    parts.push_back({i, k, at});
+    at += size;
+    return GMCO_OK;
+  };
   for (int i = 0; i < n; ++i) {
-    const size_t ps_bytes = (size_t)ctxs[i]->P * sizeof(PlanState);
-    GMCO_HIP(ctxs[i], hipMemcpyAsync(sg.at<void>(at[i]), ctxs[i]->at<void>(ctxs[i]->lay.ps), ps_bytes,
-                                     hipMemcpyDeviceToHost, st));
-    GMCO_HIP(ctxs[i], hipMemcpyAsync(sg.at<void>(at[i] + ps_bytes), ctxs[i]->at<void>(ctxs[i]->lay.work), 8,
-                                     hipMemcpyDeviceToHost, st));
+    const gmco_ctx* c = ctxs[i];
+    const size_t P = c->P;
+    int rc = sg.bytes - at < 8 ? settle() : GMCO_OK;
+    if (!rc) rc = take(i, c->at<void>(c->lay.work), 0, 8);
+    for (size_t p = 0, k; p < P && !rc; p += k) {
+      if (sg.bytes - at < sizeof(PlanState) && (rc = settle())) break;
+      k = std::min(P - p, (sg.bytes - at) / sizeof(PlanState));
+      rc = take(i, c->at<PlanState>(c->lay.ps) + p, k, k * sizeof(PlanState));
+    }
+    if (rc) return rc;
   }
-  GMCO_HIP(c0, hipStreamSynchronize(st));
-  sg.settled = true;
+  if (const int rc = settle()) return rc;
   for (int i = 0; i < n; ++i) {
-    const size_t ps_bytes = (size_t)ctxs[i]->P * sizeof(PlanState);
-    const int rc = summarize(ctxs[i], round, ms, 0.0, 0.0, *sg.at<unsigned long long>(at[i] + ps_bytes),
-                             sg.at<PlanState>(at[i]), infos ? &infos[i] : nullptr);
+    const int rc = summarize(ctxs[i], round, ms, 0.0, 0.0, work[i], sums[i],
+                             infos ? &infos[i] : nullptr);
     if (rc && !status) status = rc;
   }
   return status;
@@ -1507,14 +1592,12 @@ namespace {
 template <class F>
 int each_x(gmco_ctx* c, F emit) {
   GMCO_HIP(c, hipSetDevice(c->device));
-  const size_t bytes = (size_t)c->P * c->dim.Kp * 4;
-  Staging st(bytes, c->stream);
+  const size_t row = (size_t)c->dim.Kp * 4;
+  Staging st(c->P * row, c->stream);
   GMCO_STAGED(c, st);
-  GMCO_HIP(c, hipMemcpyAsync(st.at<void>(0), c->at<void>(c->lay.x), bytes, hipMemcpyDeviceToHost, c->stream));
-  GMCO_HIP(c, hipStreamSynchronize(c->stream));
-  st.settled = true;
-  for (int p = 0; p < c->P; ++p) emit(p, st.at<float>((size_t)p * c->dim.Kp * 4));
-  return GMCO_OK;
+  return read_back(c, st, 0, c->at<void>(c->lay.x), c->P, row, [&](size_t i, size_t k, const char* x) {
+    for (size_t p = 0; p < k; ++p) emit(i + p, reinterpret_cast<const float*>(x + p * row));
+  });
 }
 }  // namespace
 
@@ -1524,8 +1607,8 @@ int gmco_get_dwell_times(gmco_ctx* c, double* t) {
   if (!c || !t) return GMCO_EINVAL;
   if (!c->case_loaded || c->P == 0) return fail(c, GMCO_ESTATE, "gmco_set_weights first");
   const int K = c->dim.K;
-  return each_x(c, [&](int p, const float* x) {
-    double* row = t + (size_t)p * K;
+  return each_x(c, [&](size_t p, const float* x) {
+    double* row = t + p * K;
     for (int l = 0; l < K; ++l) row[l] = (double)x[l] * (double)x[l];
   });
 }
@@ -1534,8 +1617,8 @@ int gmco_get_weights_x(gmco_ctx* c, double* x) {
   if (!c || !x) return GMCO_EINVAL;
   if (!c->case_loaded || c->P == 0) return fail(c, GMCO_ESTATE, "gmco_set_weights first");
   const int K = c->dim.K;
-  return each_x(c, [&](int p, const float* xp) {
-    double* row = x + (size_t)p * K;
+  return each_x(c, [&](size_t p, const float* xp) {
+    double* row = x + p * K;
     for (int l = 0; l < K; ++l) row[l] = (double)xp[l];
   });
 }
@@ -1604,6 +1687,7 @@ int gmco_select_plan(gmco_ctx* c, const gmco_select_opts* opts, int* best, int* 
   int* res = nd + Pp;
   GMCO_HIP(c, launch_select(c->at<gmco_plan_metrics>(c->lay.metrics), P, c->O, o, cls, tu, nd, res, c->stream));
   const size_t bytes = (size_t)Pp * 12 + 8;  // classes, (criteria met), dominance, result
+  static_assert((size_t)kMaxPlans * 12 + 8 <= kPinBlock, "one piece of staging memory");
   Staging st(bytes, c->stream);
   GMCO_STAGED(c, st);
   GMCO_HIP(c, hipMemcpyAsync(st.at<void>(0), cls, bytes, hipMemcpyDeviceToHost, c->stream));
@@ -1624,14 +1708,11 @@ int gmco_get_metrics(gmco_ctx* c, gmco_plan_metrics* out) {
   const Layout& L = c->lay;
   const int rc = compute_metrics(c);
   if (rc) return rc;
-  const size_t bytes = (size_t)c->P * sizeof(gmco_plan_metrics);
-  Staging st(bytes, c->stream);
+  constexpr size_t unit = sizeof(gmco_plan_metrics);
+  Staging st(c->P * unit, c->stream);
   GMCO_STAGED(c, st);
-  GMCO_HIP(c, hipMemcpyAsync(st.at<void>(0), c->at<void>(L.metrics), bytes, hipMemcpyDeviceToHost, c->stream));
-  GMCO_HIP(c, hipStreamSynchronize(c->stream));
-  st.settled = true;
-  std::memcpy(out, st.at<void>(0), bytes);
-  return GMCO_OK;
+  return read_back(c, st, 0, c->at<void>(L.metrics), c->P, unit,
+                   [&](size_t i, size_t k, const char* p) { std::memcpy(out + i, p, k * unit); });
 }
 
 int gmco_get_dose_rate(gmco_ctx* c, double* D64, double* Drun) {
