@@ -961,6 +961,15 @@ int gmco_optimize(gmco_ctx* c, const gmco_run* r, gmco_run_info* info) {
     ++harvested;
     return er;
   };
+  // a call that returns early waits for the rounds it has issued: a report of
+  // theirs would be taken for one of the next run
+  struct Drain {
+    hipStream_t stream;
+    bool done = false;
+    ~Drain() {
+      if (!done) (void)hipStreamSynchronize(stream);
+    }
+  } drain{c->stream};
   volatile unsigned long long* word = c->host_word;
   *word = 0;
   GMCO_HIP(c, hipEventRecord(c->ev0, c->stream));
@@ -1016,6 +1025,7 @@ int gmco_optimize(gmco_ctx* c, const gmco_run* r, gmco_run_info* info) {
     add_states(inf, reinterpret_cast<const PlanState*>(p), k);
   });
   if (rc) return rc;
+  drain.done = true;
   const unsigned long long* done = st.at<unsigned long long>(0);
   float ms = 0.f;
   GMCO_HIP(c, hipEventElapsedTime(&ms, c->ev0, c->ev1));

@@ -149,6 +149,8 @@ hipError_t hipStreamEndCapture(hipStream_t, hipGraph_t*) { return hipErrorNotSup
 static float x_value(size_t p, int l) { return 0.25f + (float)(p % 977) + 0.001f * (float)l; }
 static bool g_case_ok = true;       // the uploaded case, as the set-up kernel sees it
 static const gmco_case* g_case = nullptr;
+static long g_evals = 0, g_fail_at = -1;  // evaluations launched; the one that fails
+static int g_live = 0;                    // rounds with running plans
 
 namespace gmco {
 hipError_t launch_dose_setup(const double* dwell_xyz, const double* pt_xyz, const double*, const int* perm, int M,
@@ -206,15 +208,34 @@ hipError_t launch_metrics_final(const MetricsArgs& m, hipStream_t) {
   });
   return hipSuccess;
 }
-hipError_t launch_eval(const EvalArgs&, int, hipStream_t) {
-  later([] {});
+// A run whose plans all stop in round g_live - 1; a running evaluation takes 1 ms,
+// an empty one 0.01, an update a tenth of that.
+hipError_t launch_eval(const EvalArgs& a, int, hipStream_t) {
+  if (g_evals++ == g_fail_at) return hipErrorLaunchFailure;
+  const int nact = a.flag && a.round >= g_live ? 0 : a.P;
+  later([=] {
+    g_clock += nact > 0 ? 1.0 : 0.01;
+    if (a.flag == nullptr) return;
+    if (a.host_word != nullptr && (a.round & (kReportRounds - 1)) == kReportRounds - 1)
+      *a.host_word = ((unsigned long long)(a.round + 1) << 32) | (unsigned)nact;
+    *a.work += nact;
+    if (a.work2 != nullptr) *a.work2 += nact;
+  });
   return hipSuccess;
 }
-hipError_t launch_resume(PlanState*, const float*, float*, int*, int*, unsigned long long*, int, int, int, int,
+hipError_t launch_resume(PlanState*, const float*, float*, int*, int*, unsigned long long* work, int, int, int, int,
                          hipStream_t) {
+  later([=] { work[0] = work[1] = 0; });
   return hipSuccess;
 }
-hipError_t launch_update(const UpdateArgs&, hipStream_t) { return hipSuccess; }
+hipError_t launch_update(const UpdateArgs& u, hipStream_t) {
+  const int live = g_live;
+  later([=] {
+    g_clock += u.round < live ? 0.1 : 0.001;
+    for (int p = 0; p < u.P && u.round == live - 1; ++p) u.ps[p].status = ST_CONVERGED;
+  });
+  return hipSuccess;
+}
 hipError_t launch_dose64(const double*, const float*, int, int, int, int, double*, hipStream_t) { return hipSuccess; }
 // not reached by any scenario
 hipError_t launch_select(const gmco_plan_metrics*, int, int, const gmco_select_opts&, int*, int*, int*, int*,
@@ -328,9 +349,40 @@ static int copies(int P, int K, int M, bool pinning) {
   return 0;
 }
 
+static gmco_run run_options() {
+  gmco_run r{};
+  r.max_iter = 1000;
+  r.c1 = 1e-4;
+  r.beta = 0.5;
+  r.max_ls = 5;
+  r.dtype = -1;
+  return r;
+}
+
+// A run of which an evaluation fails to launch while the report of no running
+// plan is on its way, and a run after it.
+static int failed_launch(int live, int fail_at, int live2) {
+  Case cs(5, 40);
+  start(cs, 3);
+  gmco_run r = run_options();
+  gmco_run_info info{};
+  g_live = live;
+  g_fail_at = fail_at;
+  const int rc = gmco_optimize(g_ctx, &r, &info);
+  const size_t pending = g_queue.size();
+  g_live = live2;
+  g_fail_at = -1;
+  CHECK(gmco_optimize(g_ctx, &r, &info));
+  CHECK(gmco_destroy(g_ctx));
+  std::printf("{\"rc\": %d, \"pending\": %zu, \"rounds\": %d, \"converged\": %d, \"work\": %g}\n", rc, pending,
+              info.rounds, info.n_converged, info.eval_work);
+  return 0;
+}
+
 int main(int argc, char** argv) {
   const std::string what = argc > 1 ? argv[1] : "";
   auto arg = [&](int i) { return i < argc ? std::atoi(argv[i]) : 0; };
   if (what == "copies") return copies(arg(2), arg(3), arg(4), arg(5) != 0);
+  if (what == "failed_launch") return failed_launch(arg(2), arg(3), arg(4));
   return 2;
 }

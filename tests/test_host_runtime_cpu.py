@@ -39,3 +39,13 @@ def test_copies_of_any_size(runtime, P, K, M, pinning):
     assert r["pins"][0] == r["pins"][-1]
     assert r["peak"] <= (64 << 20) + 4096
     assert r["left"] == 0
+
+
+# Work that a failed call has issued ends before the call returns: its report of
+# running plans would otherwise end the next run, here before its first round.
+def test_failed_call_leaves_no_report_behind(runtime):
+    r = runtime("failed_launch", 14, 18, 40)
+    assert r["rc"] == -3
+    assert r["pending"] == 0
+    assert r["converged"] == 3 and r["work"] == 40
+    assert 40 <= r["rounds"] <= 60
