@@ -150,13 +150,14 @@ typedef struct {
   int n_nonfinite;
   int max_iters;       /* largest accepted-step count of any plan */
   float device_ms;     /* GPU time of the whole run (HIP events on the context stream) */
-  float eval_ms;       /* sum of the timed evaluation-kernel durations */
+  float eval_ms;       /* sum of the timed evaluation-kernel durations (timed_launches) */
   float update_ms;     /* sum of the timed split-reduction + L-BFGS update durations */
   int eval_launches;   /* evaluation launches */
   double eval_work;    /* plan evaluations done / batch size: full-batch launch
                           equivalents (stopped plans are compacted out of every
                           evaluation) */
-  int timed_launches;  /* evaluation launches timed (time_kernels > 0) */
+  int timed_launches;  /* evaluation launches timed (time_kernels > 0), those of the
+                          rounds issued after the last plan stopped left out */
   double timed_work;   /* plan evaluations of the timed launches / batch size */
 } gmco_run_info;
 

@@ -518,15 +518,20 @@ int check_run(gmco_ctx* c, const gmco_run* r, int* dtype) {
   return GMCO_OK;
 }
 
-void add_states(gmco_run_info& inf, const PlanState* ps, size_t n) {
+// Counts n plans in and returns the rounds until the last of them had stopped (a
+// running plan is evaluated once a round).
+int add_states(gmco_run_info& inf, const PlanState* ps, size_t n) {
+  int rounds = 0;
   for (size_t p = 0; p < n; ++p) {
     const PlanState& s = ps[p];
+    rounds = std::max(rounds, s.nevals - s.nevals0);
     inf.n_converged += s.status == ST_CONVERGED;
     inf.n_maxiter += s.status == ST_MAXITER;
     inf.n_ls_fail += s.status == ST_LSFAIL;
     inf.n_nonfinite += s.status == ST_NONFINITE;
     inf.max_iters = std::max(inf.max_iters, s.iter);
   }
+  return rounds;
 }
 
 // inf holds the counts of every plan's state already
@@ -949,15 +954,15 @@ int gmco_optimize(gmco_ctx* c, const gmco_run* r, gmco_run_info* info) {
   for (auto& e : ev)
     if (hipEventCreate(&e) != hipSuccess) return fail(c, GMCO_EHIP, "hipEventCreate failed");
   int timed = 0, harvested = 0;
-  double eval_ms = 0.0, update_ms = 0.0;
+  std::vector<float> ms2;  // evaluation and update of each timed round
   auto harvest = [&]() -> hipError_t {  // the oldest timed round
     hipEvent_t* e = ev.data() + (size_t)4 * (harvested % ring);
     float a_ms = 0.f, b_ms = 0.f;
     hipError_t er = hipEventSynchronize(e[3]);
     if (er == hipSuccess) er = hipEventElapsedTime(&a_ms, e[0], e[1]);
     if (er == hipSuccess) er = hipEventElapsedTime(&b_ms, e[2], e[3]);
-    eval_ms += a_ms;
-    update_ms += b_ms;
+    ms2.push_back(a_ms);
+    ms2.push_back(b_ms);
     ++harvested;
     return er;
   };
@@ -1021,14 +1026,22 @@ int gmco_optimize(gmco_ctx* c, const gmco_run* r, gmco_run_info* info) {
   GMCO_STAGED(c, st);
   GMCO_HIP(c, hipMemcpyAsync(st.at<void>(0), work, 16, hipMemcpyDeviceToHost, c->stream));
   gmco_run_info inf{};
+  int running = 0;  // rounds with running plans: the first of the run
   rc = read_back(c, st, kHead, c->at<void>(L.ps), c->P, sizeof(PlanState), [&](size_t, size_t k, const char* p) {
-    add_states(inf, reinterpret_cast<const PlanState*>(p), k);
+    running = std::max(running, add_states(inf, reinterpret_cast<const PlanState*>(p), k));
   });
   if (rc) return rc;
   drain.done = true;
   const unsigned long long* done = st.at<unsigned long long>(0);
   float ms = 0.f;
   GMCO_HIP(c, hipEventElapsedTime(&ms, c->ev0, c->ev1));
+  // (an empty round exits at once: it would count as a launch of no work)
+  if (every > 0) timed = std::min(timed, (running + every - 1) / every);
+  double eval_ms = 0.0, update_ms = 0.0;
+  for (int i = 0; i < timed; ++i) {
+    eval_ms += ms2[2 * i];
+    update_ms += ms2[2 * i + 1];
+  }
   rc = summarize(c, round, ms, eval_ms, update_ms, done[0], inf, info);
   if (info) {
     info->timed_launches = timed;

@@ -69,7 +69,8 @@ struct PlanState {
   int hcount;    // history pairs held
   int hhead;     // next ring slot
   int nevals;    // objective evaluations
-  int pad0, pad1;
+  int nevals0;   // of them before the current run
+  int pad;
 };
 static_assert(sizeof(PlanState) == 64, "PlanState layout");
 
@@ -190,8 +191,8 @@ hipError_t launch_finish_eval(const float* Gpart, const double* Fpart, const flo
 hipError_t launch_finish_eval_f32(const float* Gpart, const double* Fpart, const float* x, int S,
                                   int P, int Pp, int K, int Kp, double* F, float* g,
                                   hipStream_t st);
-// Resumes stopped plans, sets every plan's flag and clears the running
-// counts and the work counts of the call.
+// Resumes stopped plans, sets every plan's flag, notes its evaluations before the
+// call and clears the running counts and the work counts of the call.
 hipError_t launch_resume(PlanState* ps, const float* x, float* xt, int* flag, int* active,
                          unsigned long long* work, int Pp, int Kp, int max_iter, int resume_stopped,
                          hipStream_t st);

@@ -623,14 +623,15 @@ __global__ void k_resume(PlanState* ps, const float* __restrict__ x, float* __re
   const bool resume = (s == ST_MAXITER && ps[p].iter < max_iter) ||
                       (resume_stopped && (s == ST_CONVERGED || s == ST_LSFAIL) &&
                        ps[p].iter < max_iter);
-  if (threadIdx.x == 0) flag[p] = (resume || state_active(s)) ? 1 : 0;
+  if (threadIdx.x == 0) {
+    flag[p] = (resume || state_active(s)) ? 1 : 0;
+    // (the re-evaluation of a resumed plan's point is not counted)
+    ps[p].nevals0 = ps[p].nevals -= resume ? 1 : 0;
+  }
   if (!resume) return;
   for (int l = threadIdx.x; l < Kp; l += blockDim.x) xt[(size_t)p * Kp + l] = x[(size_t)p * Kp + l];
   __syncthreads();
-  if (threadIdx.x == 0) {
-    ps[p].status = ST_INIT;
-    ps[p].nevals -= 1;  // the re-evaluation of the same point is not counted
-  }
+  if (threadIdx.x == 0) ps[p].status = ST_INIT;
 }
 
 }  // namespace

@@ -246,8 +246,8 @@ __global__ void k_init_plans(int P, int Pp, int K, int Kp, const double* __restr
     s.hcount = 0;
     s.hhead = 0;
     s.nevals = 0;
-    s.pad0 = 0;
-    s.pad1 = 0;
+    s.nevals0 = 0;
+    s.pad = 0;
     ps[p] = s;
   }
 }

@@ -223,16 +223,22 @@ hipError_t launch_eval(const EvalArgs& a, int, hipStream_t) {
   });
   return hipSuccess;
 }
-hipError_t launch_resume(PlanState*, const float*, float*, int*, int*, unsigned long long* work, int, int, int, int,
-                         hipStream_t) {
-  later([=] { work[0] = work[1] = 0; });
+hipError_t launch_resume(PlanState* ps, const float*, float*, int*, int*, unsigned long long* work, int Pp, int, int,
+                         int, hipStream_t) {
+  later([=] {
+    work[0] = work[1] = 0;
+    for (int p = 0; p < Pp; ++p) ps[p].nevals0 = ps[p].nevals;
+  });
   return hipSuccess;
 }
 hipError_t launch_update(const UpdateArgs& u, hipStream_t) {
   const int live = g_live;
   later([=] {
     g_clock += u.round < live ? 0.1 : 0.001;
-    for (int p = 0; p < u.P && u.round == live - 1; ++p) u.ps[p].status = ST_CONVERGED;
+    for (int p = 0; p < u.P && u.round < live; ++p) {  // plan 0 stops last
+      if (p == 0 || u.round < live / 2) u.ps[p].nevals += 1;
+      if (u.round == live - 1) u.ps[p].status = ST_CONVERGED;
+    }
   });
   return hipSuccess;
 }
@@ -379,10 +385,32 @@ static int failed_launch(int live, int fail_at, int live2) {
   return 0;
 }
 
+// Sampled timing of two runs one after the other.
+static int timing(int live, int every) {
+  Case cs(5, 40);
+  start(cs, 3);
+  gmco_run r = run_options();
+  r.time_kernels = every;
+  std::string out;
+  for (int run = 0; run < 2; ++run) {
+    gmco_run_info info{};
+    g_live = live + run;
+    CHECK(gmco_optimize(g_ctx, &r, &info));
+    char line[200];
+    std::snprintf(line, sizeof(line), "%s[%d, %.6f, %.6f, %.6f, %d]", run ? ", " : "", info.timed_launches,
+                  info.timed_work, info.eval_ms, info.update_ms, info.rounds);
+    out += line;
+  }
+  CHECK(gmco_destroy(g_ctx));
+  std::printf("{\"runs\": [%s]}\n", out.c_str());
+  return 0;
+}
+
 int main(int argc, char** argv) {
   const std::string what = argc > 1 ? argv[1] : "";
   auto arg = [&](int i) { return i < argc ? std::atoi(argv[i]) : 0; };
   if (what == "copies") return copies(arg(2), arg(3), arg(4), arg(5) != 0);
   if (what == "failed_launch") return failed_launch(arg(2), arg(3), arg(4));
+  if (what == "timing") return timing(arg(2), arg(3));
   return 2;
 }

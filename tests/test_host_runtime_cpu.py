@@ -49,3 +49,15 @@ def test_failed_call_leaves_no_report_behind(runtime):
     assert r["pending"] == 0
     assert r["converged"] == 3 and r["work"] == 40
     assert 40 <= r["rounds"] <= 60
+
+
+# Sampled timing counts the rounds that had running plans and no others: every
+# `every`-th of the first `live`, 1 ms an evaluation and 0.1 an update.
+@pytest.mark.parametrize("live", [1, 13, 40, 200])
+@pytest.mark.parametrize("every", [1, 3, 16])
+def test_timing_leaves_empty_rounds_out(runtime, live, every):
+    for n, (launches, work, eval_ms, update_ms, rounds) in zip((live, live + 1), runtime("timing", live, every)["runs"]):
+        want = -(-n // every)
+        assert launches == want and work == want
+        assert eval_ms == pytest.approx(want, abs=1e-3) and update_ms == pytest.approx(0.1 * want, abs=1e-3)
+        assert rounds >= n
