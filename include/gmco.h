@@ -124,9 +124,9 @@ typedef struct {
   double c1;          /* Armijo constant, e.g. 1e-4 */
   double beta;        /* backtracking factor in (0, 1), e.g. 0.5 */
   int max_ls;         /* trials per iteration before LS_FAIL, >= 1 */
-  int check_every;    /* gmco_optimize_many with plain launches: rounds between host checks of
-                         the active-plan count (0 -> 16).  gmco_optimize is told by the
-                         device and issues up to 12 rounds ahead */
+  int check_every;    /* rounds between host checks of the active-plan count.  gmco_optimize:
+                         at most 8 (0 -> 8), with up to 4 more rounds issued meanwhile;
+                         gmco_optimize_many with plain launches: as given (0 -> 16) */
   int time_kernels;   /* n > 0: time the evaluation and the update launches of rounds
                          0, n, 2n, ... with HIP events on the context stream; 0: none */
   int resume_stopped; /* 1: plans stopped as CONVERGED or LS_FAIL iterate again

@@ -927,9 +927,8 @@ int gmco_optimize(gmco_ctx* c, const gmco_run* r, gmco_run_info* info) {
                             c->at<int>(L.active), work, d.Pp, d.Kp, r->max_iter, r->resume_stopped, c->stream));
   UpdateArgs u = update_args(c, r);
   EvalArgs a = eval_args(c, c->at<float>(L.xt), true, dtype);
-  a.host_word = c->host_word;
   const long long max_rounds = 1 + (long long)std::max(r->max_iter, 1) * r->max_ls + 1;
-  // The evaluation of every kReportRounds-th round writes its number and the
+  // The evaluation of every `period`-th round writes its number and the
   // count of running plans to pinned host memory.  The host issues rounds up to
   // `ahead` past the last one reported, so the device never idles, and stops at
   // a report of no running plan; the rounds issued past it run empty (every
@@ -940,7 +939,8 @@ int gmco_optimize(gmco_ctx* c, const gmco_run* r, gmco_run_info* info) {
   // Optional sampled timing: events around the evaluation and the update of
   // every time_kernels-th round, 4 per timed round, in a ring that outlasts the
   // rounds in flight.
-  const int ahead = kReportRounds + 4;
+  const int period = r->check_every > 0 ? std::min(r->check_every, kReportRounds) : kReportRounds;
+  const int ahead = period + 4;
   const int every = r->time_kernels;
   const int ring = every > 0 ? ahead + 1 : 0;
   std::vector<hipEvent_t> ev((size_t)4 * ring, nullptr);
@@ -989,6 +989,7 @@ int gmco_optimize(gmco_ctx* c, const gmco_run* r, gmco_run_info* info) {
     if (round >= max_rounds) break;  // every plan has stopped by then
     if (round - seen < ahead) {
       u.round = a.round = (int)round;
+      a.host_word = round % period == period - 1 ? c->host_word : nullptr;
       const bool tk = every > 0 && round % every == 0;
       hipEvent_t* e = nullptr;
       a.work2 = nullptr;

@@ -39,8 +39,8 @@ __host__ __device__ constexpr bool acc_quarters_ok(int Kp) { return Kp % 64 == 0
 __host__ __device__ constexpr int lp_tiles(int Kp) { return lp_threads(Kp) / 64 * 16 * lp_halves(Kp) / kPT; }
 constexpr int kKAlign = 32;
 constexpr int kMAlign = 32;  // points: a multiple of every kernel's block
-// Rounds between reports of the running plans to the host: a store to host
-// memory holds its kernel's end for about 2.7 us.
+// Rounds between reports of the running plans to the host, unless the caller wants
+// them closer: a store to host memory holds its kernel's end for about 2.7 us.
 constexpr int kReportRounds = 8;
 constexpr int kSplitMax = 256;  // largest split-M count the heuristic picks
 
@@ -107,8 +107,8 @@ struct EvalArgs {
   const int* split_tab;   // [ntiles + 1] split count per active tile count
   int* slot;              // [Pp] compact rank of each running plan
   RoundTable* rt;
-  unsigned long long* host_word;  // pinned host memory, NULL: no report.  Every
-                          // kReportRounds-th round: (round + 1) << 32 | nact
+  unsigned long long* host_word;  // pinned host memory that this round reports to:
+                          // (round + 1) << 32 | nact; NULL: no report
   int round;
   unsigned long long* work;
   unsigned long long* work2;  // optional second count (the timed launches)

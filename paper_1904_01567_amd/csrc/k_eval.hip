@@ -155,7 +155,7 @@ __device__ inline bool tile_setup(const EvalArgs& a, int bid, int* sPlan, int* s
       r.S = t.S;
       r.pad = 0;
       *a.rt = r;
-      if (a.host_word != nullptr && (a.round & (kReportRounds - 1)) == kReportRounds - 1)
+      if (a.host_word != nullptr)
         __hip_atomic_store(a.host_word, ((unsigned long long)(a.round + 1) << 32) | (unsigned)nact, __ATOMIC_RELAXED,
                            __HIP_MEMORY_SCOPE_SYSTEM);
       if (a.work != nullptr) *a.work += (unsigned long long)nact;

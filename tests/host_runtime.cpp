@@ -216,7 +216,7 @@ hipError_t launch_eval(const EvalArgs& a, int, hipStream_t) {
   later([=] {
     g_clock += nact > 0 ? 1.0 : 0.01;
     if (a.flag == nullptr) return;
-    if (a.host_word != nullptr && (a.round & (kReportRounds - 1)) == kReportRounds - 1)
+    if (a.host_word != nullptr)
       *a.host_word = ((unsigned long long)(a.round + 1) << 32) | (unsigned)nact;
     *a.work += nact;
     if (a.work2 != nullptr) *a.work2 += nact;
@@ -406,11 +406,25 @@ static int timing(int live, int every) {
   return 0;
 }
 
+static int checks(int live, int check_every) {
+  Case cs(5, 40);
+  start(cs, 3);
+  gmco_run r = run_options();
+  r.check_every = check_every;
+  gmco_run_info info{};
+  g_live = live;
+  CHECK(gmco_optimize(g_ctx, &r, &info));
+  CHECK(gmco_destroy(g_ctx));
+  std::printf("{\"rounds\": %d, \"converged\": %d}\n", info.rounds, info.n_converged);
+  return 0;
+}
+
 int main(int argc, char** argv) {
   const std::string what = argc > 1 ? argv[1] : "";
   auto arg = [&](int i) { return i < argc ? std::atoi(argv[i]) : 0; };
   if (what == "copies") return copies(arg(2), arg(3), arg(4), arg(5) != 0);
   if (what == "failed_launch") return failed_launch(arg(2), arg(3), arg(4));
   if (what == "timing") return timing(arg(2), arg(3));
+  if (what == "checks") return checks(arg(2), arg(3));
   return 2;
 }

@@ -61,3 +61,15 @@ def test_timing_leaves_empty_rounds_out(runtime, live, every):
         assert launches == want and work == want
         assert eval_ms == pytest.approx(want, abs=1e-3) and update_ms == pytest.approx(0.1 * want, abs=1e-3)
         assert rounds >= n
+
+
+# check_every bounds the rounds between looks at the running plans (8 at most), and
+# so those that are issued after the last plan has stopped: a report's distance and
+# four more are on their way when the report of no running plan arrives.
+@pytest.mark.parametrize("live", [1, 9, 40])
+@pytest.mark.parametrize("check_every", [0, 1, 2, 5, 8, 16, 2 ** 31 - 1])
+def test_check_every_bounds_the_empty_rounds(runtime, live, check_every):
+    r = runtime("checks", live, check_every)
+    assert r["converged"] == 3
+    period = min(check_every, 8) if check_every else 8
+    assert live < r["rounds"] <= live + period + period + 4
