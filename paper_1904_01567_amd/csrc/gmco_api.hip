@@ -253,10 +253,11 @@ Layout make_layout(const Dims& d, int G, int m, int dtype, int Pmax) {
   L.rt = take(sizeof(RoundTable));
   L.active = take(2 * sizeof(int));
   L.work = take(2 * sizeof(unsigned long long));
-  // final doses (Pp x Mp, then Pp x Mdp for the DVH points); an FP8 context
-  // also widens its matrix (Mp x Kp) here
-  L.d64 = take(std::max((size_t)d.Pp * std::max(d.Mp, d.Mdp),
-                        (size_t)(dtype == GMCO_DTYPE_FP8 ? d.Kp : 0) * d.Mp) * 8);
+  // final doses (Pp x Mp, then Pp x Mdp for the DVH points); the case set-up has its
+  // scratch here before there are any, and an FP8 context widens its matrix
+  // (Mp x Kp) here
+  L.d64 = take(std::max({(size_t)d.Pp * std::max(d.Mp, d.Mdp), dose_scratch(d.Mp, d.Kp),
+                         (size_t)(dtype == GMCO_DTYPE_FP8 ? d.Kp : 0) * d.Mp}) * 8);
   L.metrics = take((size_t)d.Pp * sizeof(gmco_plan_metrics));
   L.hist = take(kGmax * 16 * 4);
   L.sel = take((size_t)d.Pp * 3 * 4 + 16);
@@ -788,7 +789,7 @@ int gmco_load_case(gmco_ctx* c, const gmco_case* cs) {
   const double* st_pt = c->at<double>(L.pts);
   if (cs->dose_rate && (rc = copy_h2d(c, st_D, cs->dose_rate, (size_t)M * K * 8))) return rc;
 
-  // (the doses' array is free until the metrics: scratch of the row sums and column maxima)
+  // (the doses' array is free until the metrics)
   const int r0 = c->offsets[cs->target_group];
   GMCO_HIP(c, launch_dose_setup(st_dw, cs->point_xyz ? st_pt : nullptr, cs->dose_rate ? st_D : nullptr,
                                 c->at<int>(L.perm), M, K, d.Mp, d.Kp, c->dtype, r0,

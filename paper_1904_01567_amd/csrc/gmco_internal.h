@@ -165,7 +165,7 @@ hipError_t launch_dose_setup(const double* dwell_xyz, const double* pt_xyz, cons
                              const int* perm, int M, int K, int Mp, int Kp, int dtype, int row_begin,
                              int row_end, double prescription, double* D64, float* D32, void* Dlp, void* DTlp,
                              float* colscale, double* scratch, double* t_bar, hipStream_t st);
-// row sums, and the column maxima of each 32-point block
+// the row sums, and the column maxima of each 32-point block
 inline size_t dose_scratch(int Mp, int Kp) { return (size_t)Mp + (size_t)(Mp / 32) * Kp; }
 hipError_t launch_widen_fp8(const void* D8, const float* colscale, int Mp, int Kp, double* out,
                             hipStream_t st);

@@ -154,9 +154,10 @@ static int g_live = 0;                    // rounds with running plans
 
 namespace gmco {
 hipError_t launch_dose_setup(const double* dwell_xyz, const double* pt_xyz, const double*, const int* perm, int M,
-                             int K, int, int, int, int, int, double, double*, float*, void*, void*, float*, double*,
-                             double* t_bar, hipStream_t) {
+                             int K, int Mp, int Kp, int, int, int, double, double*, float*, void*, void*, float*,
+                             double* scratch, double* t_bar, hipStream_t) {
   later([=] {
+    for (size_t i = 0; i < dose_scratch(Mp, Kp); ++i) scratch[i] = -1.0;  // (nothing else is there)
     g_case_ok = std::memcmp(dwell_xyz, g_case->dwell_xyz, (size_t)K * 24) == 0 &&
                 std::memcmp(pt_xyz, g_case->point_xyz, (size_t)M * 24) == 0;
     int last = -1, group = -1;  // stable order by group
