@@ -274,8 +274,11 @@ Layout make_layout(const Dims& d, int G, int m, int dtype, int Pmax) {
 
 // True when every value is finite; with y, also their FP32 values.  The test is
 // on the bits, without a branch per value, so that the loop vectorises (an
-// exponent of all ones carries into the sign bit).
-bool finite_all(const double* v, size_t n, float* y = nullptr) {
+// exponent of all ones carries into the sign bit).  Out of line and on a line of
+// its own: inlined, the speed of its loops went with the length of the code before
+// them (evaluate calls of 1,000 x 360 values, builds that differ only there: 228
+// and 235 us, 221 so).
+__attribute__((noinline, aligned(64))) bool finite_all(const double* v, size_t n, float* y = nullptr) {
   for (size_t i0 = 0; i0 < n; i0 += 2048) {
     const size_t e = std::min(n, i0 + 2048);
     uint64_t bad = 0;
