@@ -296,11 +296,14 @@ __attribute__((noinline, aligned(64))) bool finite_all(const double* v, size_t n
 
 // Pinned host memory that calls borrow to stage their copies: a copy from or to
 // pageable memory goes through the runtime's own staging and takes two to three
-// times as long (2.9 MB: 100 us up and 157 down, against 58).  Blocks
-// outlive a call, since pinning costs far more than a call saves, and all of
-// them go with the last context.  Copies cross in pieces of at most kPinBlock,
-// so that a block serves any of them, and nothing is pinned that would not be
-// kept: past kPinTotal in use and kept together a call does without.
+// times as long (2.9 MB: 100 us up and 157 down, against 58).  Blocks outlive a
+// call, and all of them go with the last context.  (Pinning 128 MiB takes 913 us
+// and freeing it 372; up to 64 MiB the runtime keeps freed blocks itself, 9 and 7 us
+// a pair.)  Copies cross in pieces of at most kPinBlock, so that a block serves any
+// of them, and nothing is pinned that would not be kept: past kPinTotal in use and
+// kept together a call does without.  evaluate on host arrays of 24,000 plans x 360
+// dwells, 400 points: 8.1 to 8.7 ms in such pieces, 8.4 to 9.0 as one block a copy,
+// pinned and freed by each call.
 constexpr size_t kPinBlock = size_t(16) << 20;
 constexpr size_t kPinTotal = size_t(64) << 20;
 
@@ -717,7 +720,10 @@ int gmco_load_case(gmco_ctx* c, const gmco_case* cs) {
   }
   c->dim = d;
   // BF16: the role-split workgroup where it exists (measured faster at the
-  // paper-scale case; FP8 keeps shape 0, which measured as fast)
+  // paper-scale case).  FP8 keeps shape 0, the faster one until the role split's
+  // back-projection read its operands ahead (70.1 against 70.3 us); a call of
+  // 1,000 plans has since taken 95.2 us in the role split and 100.6 in shape 0,
+  // and the autotuner picks between them
   if (c->dtype == GMCO_DTYPE_BF16 && lp_shape_ok(d.Kp, 2)) c->dim.lp_shape = 2;
   // FP64-accumulated dose from 448 padded dwells: the role-split workgroup,
   // which needs no register spill there (shape 0 spills; 655 against 784 us

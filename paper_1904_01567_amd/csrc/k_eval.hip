@@ -203,14 +203,17 @@ __device__ inline int swz_row(int row) { return (row >> 1) & 3; }
 // idle, one SIMD doing the work of four.  The D blocks of a workgroup's point
 // range are taken kFewF32 (3) or kFewAcc (2) at a time and all eight waves share
 // them: the dose product by block and accumulator chain, eq. 1 by block and row,
-// the back-projection by dwell slice, with three barriers per chunk.  The chains,
+// the back-projection by dwell slice, with four barriers per chunk.  The chains,
 // the order of blocks in every gradient element and of rows in the objective are
 // those of the full shapes, so the bits are the same.  The next chunk's loads fly
 // during the work.  16 plans are one column group of the matrix instructions:
 // from 17 on a second group has work of its own and the full shape's waves fill.
 // An evaluate call of 1 plan at 360 dwells x 20,000 points in FP32: 27.7 us by the
 // full shape, 20.0 by this one; of 8 plans at 160 x 2,400, FP64-accumulated: 13.0
-// and 11.9 (what is left there is three launches).
+// and 11.9 (what is left there is three launches).  The FP32 role-split shape and
+// the FP64-accumulated shape 0 have this form; the others (FP64-accumulated from
+// 448 padded dwells, chunked, BF16 and FP8) run their full shape for any batch:
+// such a form has not been built for them.
 constexpr int kFewPlans = 16;
 constexpr int kFewF32 = 3, kFewAcc = 2;
 

@@ -544,9 +544,9 @@ hipError_t launch_update_grouped_e(const UpdateArgs* args, int n, int P_max, int
 // NW = 1 for few splits (S <= kFinishDirect), where a single wavefront has the
 // whole range in flight in at most three trips and many plans fill the chip;
 // NW = 8 above, where few plans leave most of the chip idle.  A serial loop
-// with one load in flight took 63 us at 150 splits (8 plans) and 114 us at 250
+// with one load in flight took 63 us at 150 splits (8 plans) and 114 us at 256
 // (one plan): whole evaluations went from 75 to 17 us and from 143 to 34 us,
-// at 80 splits (333 plans, FP8) from 79 to 48 us, at 32 (1,000 plans, BF16)
+// at 74 splits (333 plans, FP8) from 79 to 48 us, at 20 (1,000 plans, BF16)
 // from 86 to 82 us; the same bits.
 constexpr int kFinishDirect = 48;
 
