@@ -217,13 +217,6 @@ __device__ inline int swz_row(int row) { return (row >> 1) & 3; }
 constexpr int kFewPlans = 16;
 constexpr int kFewF32 = 3, kFewAcc = 2;
 
-// Chunk c of nblk blocks in chunks of at most NB of about equal size.
-template <int NB>
-__device__ inline int few_chunk(int nblk, int c) {
-  const int nch = (nblk + NB - 1) / NB;
-  return nch > 0 ? nblk * c / nch : 0;
-}
-
 template <int KP>
 __device__ inline void eval_f32_few(const EvalArgs& a, const Tile& t, float* sD, float* sX, float* sPh,
                                     const float* sW, const float4* sP, const int* sPlan, int* sG) {

@@ -17,6 +17,8 @@
 
 #include "gmco_internal.h"
 
+using gmco::few_chunk;
+
 // ---- the device: a queue of work, run in order ----
 static std::deque<std::function<void()>> g_queue;
 static void later(std::function<void()> f) { g_queue.push_back(std::move(f)); }
@@ -420,6 +422,27 @@ static int checks(int live, int check_every) {
   return 0;
 }
 
+// The chunks of ranges of up to n blocks: in order, whole, none too long.
+template <int NB>
+static bool chunks_ok(int nblk) {
+  const int nch = (nblk + NB - 1) / NB;
+  bool ok = few_chunk<NB>(nblk, 0) == 0 && few_chunk<NB>(nblk, nch) == nblk;
+  for (int c = 0; c < nch && ok; ++c) {
+    const int n = few_chunk<NB>(nblk, c + 1) - few_chunk<NB>(nblk, c);
+    ok = few_chunk<NB>(nblk, c) >= 0 && n >= 1 && n <= NB;
+  }
+  return ok;
+}
+
+static int few_chunks() {
+  std::string bad;
+  for (int n : {0, 1, 2, 3, 4, 5, 6, 7, 8, 9, 20, 63, 64, 65, 1000, 1250, 46341, 65536, 65537, 80265, 100003, 131072,
+                1000000, 67108863})
+    if (!chunks_ok<2>(n) || !chunks_ok<3>(n)) bad += (bad.empty() ? "" : ", ") + std::to_string(n);
+  std::printf("{\"bad\": [%s]}\n", bad.c_str());
+  return 0;
+}
+
 int main(int argc, char** argv) {
   const std::string what = argc > 1 ? argv[1] : "";
   auto arg = [&](int i) { return i < argc ? std::atoi(argv[i]) : 0; };
@@ -427,5 +450,6 @@ int main(int argc, char** argv) {
   if (what == "failed_launch") return failed_launch(arg(2), arg(3), arg(4));
   if (what == "timing") return timing(arg(2), arg(3));
   if (what == "checks") return checks(arg(2), arg(3));
+  if (what == "few_chunks") return few_chunks();
   return 2;
 }

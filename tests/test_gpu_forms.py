@@ -102,3 +102,25 @@ def test_weight_gradient_tiles_agree_bitwise(B):
     # (the first step's moments and their corrections have the same factors)
     assert np.abs(net.params() - (p - step)).max() <= 2.0 ** -23 * np.abs(p).max() + 2e-6 * lr
     assert np.abs(net.params() - p).max() > 0.5 * lr
+
+
+# A range of more than 65,536 point blocks in one workgroup (a million points and
+# one split, as batches of thousands of plans have): the form for few plans walks
+# it in chunks whose places were once computed in 32 bits past their range.
+@pytest.mark.parametrize("dtype", ["f32", "f32acc64"])
+def test_few_plans_over_a_long_range(dtype):
+    M = 1_300_000
+    announce(f"few plans over {M} points in one split, {dtype}")
+    c = _case(1, 5, M)
+    W = cases.hidden_weights(64, seed=6)
+    x = 0.5 + cases.uniform_draws((64, c.K), seed=7)
+    out = []
+    for P in (64, 1):
+        pl = planner(c, W[:P], dtype=dtype)
+        pl.set_split(1)
+        out.append(pl.evaluate(x[:P]))
+        pl.close()
+    (F, g), (F1, g1) = out
+    np.testing.assert_array_equal(F1, F[:1])
+    np.testing.assert_array_equal(g1, g[:1])
+    assert np.all(np.isfinite(F)) and np.all(F > 0.0)

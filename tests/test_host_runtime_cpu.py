@@ -73,3 +73,9 @@ def test_check_every_bounds_the_empty_rounds(runtime, live, check_every):
     assert r["converged"] == 3
     period = min(check_every, 8) if check_every else 8
     assert live < r["rounds"] <= live + period + period + 4
+
+
+# The few-plan forms of the evaluation take a range of 16-point blocks in chunks:
+# every block once, in order, up to the largest range that a 32-bit point count has.
+def test_few_plan_chunks_cover_every_range(runtime):
+    assert runtime("few_chunks")["bad"] == []
